@@ -363,17 +363,18 @@ __global__ __launch_bounds__(WAVES * kWave) void gemm_decode_kernel(GemmArgs a, 
             static_assert(!FUSEQ || (W <= 16 && (W & (W - 1)) == 0), "one absmax word per wave, read by lane & (W - 1)");
             const float amax = wave_max(lds_amax[lane & (W - 1)]);
             const float s_a = amax / 127.0f;
-            float xv[2 * XS], qv[2 * XS];
+            float xv[2 * XS];
+            uint32_t code[2 * XS];
 #pragma unroll
             for (int i = 0; i < XS; ++i) {
                 xv[2 * i] = xf0[i];
                 xv[2 * i + 1] = xf1[i];
             }
-            quant_codes<2 * XS>(xv, s_a, qv);
+            offset_codes(xv, s_a, code);
 #pragma unroll
             for (int i = 0; i < XS; ++i) {
-                qstage[i * 128 + lane] = (signed char)(int)qv[2 * i];
-                qstage[i * 128 + 64 + lane] = (signed char)(int)qv[2 * i + 1];
+                qstage[i * 128 + lane] = (signed char)(code[2 * i] ^ 0x80u);
+                qstage[i * 128 + 64 + lane] = (signed char)(code[2 * i + 1] ^ 0x80u);
             }
             if constexpr (!XLDS) {
 #pragma unroll
