@@ -100,35 +100,37 @@ constexpr int kActThreads = 256;
 // rounding (r, its neighbours and the quotient are off by at most a few 2^-24 of their size), and rounding to an integer is
 // monotone, so where the two agree the quotient rounds to the same integer.  Where they differ anywhere in a wave (at
 // |x / s| <= 127 about one chunk of 512 values in fifty) all its values are redone with the division itself.
-// One fused multiply-add per product does everything: added to 2^23 + 2^22 + 128 the exact product is rounded to an integer,
-// ties to even, and the sum's lowest byte is the code + 128.  The fp16 operand is converted inside the instruction
+// One fused multiply-add per product does everything: added to 2^23 + 2^22 + an offset the exact product is rounded to an integer,
+// ties to even, and the sum's lowest byte is the code + the offset.  The fp16 operand is converted inside the instruction
 // (v_fma_mix_f32), the comparison is one or-of-xor per value, the packing three byte permutes per four codes: 4 instructions a
 // value where multiply, round, distance, running maximum, offset and saturating conversion took 7.  Stand-alone quantiser,
 // 4096 x 14336: 31.0 -> 29.6 us (5.9 TB/s: bound by memory now); quantising preparation of the tiled kernel, 4096 x 4096: 22.8
 // -> 20.3 us.
-constexpr float kCodeMagic = 12582912.0f + 128.0f;
+constexpr float kCodeMagic = 12582912.0f;  // + the offset
 
 __device__ __forceinline__ uint32_t low_bytes(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
     const uint32_t ab = __builtin_amdgcn_perm(b, a, 0x0C0C0400u), cd = __builtin_amdgcn_perm(d, c, 0x0C0C0400u);
     return __builtin_amdgcn_perm(cd, ab, 0x05040100u);
 }
 
-// N values' codes + 128 in the low bytes of c[] (a value that is no number gives byte 0, code -128, as the clamp of a NaN does)
-template <int N>
+// N values' codes + OFFSET in the low bytes of c[] (a value that is no number gives byte 0, the lowest code, as the clamp of a
+// NaN does)
+template <int OFFSET, int N>
 __device__ __forceinline__ void offset_codes(const float (&x)[N], float s, uint32_t (&c)[N]) {
     const float r = s > 0.0f ? 1.0f / s : 0.0f;  // a row of zeros: codes 0
     const float r_lo = r * (1.0f - 0x1p-21f), r_hi = r * (1.0f + 0x1p-21f);
     uint32_t apart = 0;
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-        c[i] = __float_as_uint(fmaf(x[i], r_lo, kCodeMagic));
-        const uint32_t other = __float_as_uint(fmaf(x[i], r_hi, kCodeMagic));
+        c[i] = __float_as_uint(fmaf(x[i], r_lo, kCodeMagic + OFFSET));
+        const uint32_t other = __float_as_uint(fmaf(x[i], r_hi, kCodeMagic + OFFSET));
         // apart |= c[i] ^ other, in one instruction (written out in C it becomes a flag per value and the flags are packed)
         asm("v_bitop3_b32 %0, %1, %2, %0 bitop3:0xbe" : "+v"(apart) : "v"(c[i]), "v"(other));
     }
     if (__any(apart != 0)) {
+        const float by = s > 0.0f ? s : 1.0f;
 #pragma unroll
-        for (int i = 0; i < N; ++i) c[i] = __float_as_uint(rintf(s > 0.0f ? x[i] / s : 0.0f) + kCodeMagic);
+        for (int i = 0; i < N; ++i) c[i] = __float_as_uint(rintf(x[i] / by) + (kCodeMagic + OFFSET));
     }
 }
 
@@ -142,7 +144,7 @@ __device__ __forceinline__ uint2 quantize8(uint4 v, float s) {
         x[2 * i + 1] = f.y;
     }
     uint32_t c[8];
-    offset_codes(x, s, c);  // (flipping the top bit of a byte turns code + 128 into two's complement)
+    offset_codes<128>(x, s, c);  // (flipping the top bit of a byte turns code + 128 into two's complement)
     return make_uint2(low_bytes(c[0], c[1], c[2], c[3]) ^ 0x80808080u, low_bytes(c[4], c[5], c[6], c[7]) ^ 0x80808080u);
 }
 

@@ -370,7 +370,7 @@ __global__ __launch_bounds__(WAVES * kWave) void gemm_decode_kernel(GemmArgs a, 
                 xv[2 * i] = xf0[i];
                 xv[2 * i + 1] = xf1[i];
             }
-            offset_codes(xv, s_a, code);
+            offset_codes<128>(xv, s_a, code);
 #pragma unroll
             for (int i = 0; i < XS; ++i) {
                 qstage[i * 128 + lane] = (signed char)(code[2 * i] ^ 0x80u);

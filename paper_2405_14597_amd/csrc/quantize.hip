@@ -3,6 +3,8 @@
 // (s = absmax / (2^(n-1) - 1), Q = clamp(round(x / s))), the integer scale INT(s * alpha) follows Eq. (2) and the
 // amplifier search follows Sec. 4.1.  Rounding is round-half-to-even and the quotient x / s is a true IEEE fp32
 // division, because that quotient decides the integer code.
+#include <algorithm>
+
 #include "act_common.h"
 #include "is_common.h"
 
@@ -65,13 +67,116 @@ __global__ __launch_bounds__(kActThreads) void quantize_act_kernel(const __half*
     for (int c = tid; c < nchunk; c += kActThreads) dst[c] = quantize8(row[c], s);
 }
 
-// ---------------------------------------------------------------------------------------------------------
-// Weights, step 1: one wave per (row, group).  Each lane owns pairs of neighbouring k so that it writes whole
-// bytes of the canonical packing (even k in the low nibble).  BITS = 4: codes -8..7, s = absmax / 7, two codes per
-// byte; BITS = 8 (the fine-grained W8A8 recipe): codes -128..127, s = absmax / 127, one code per byte, row-major.
-// ---------------------------------------------------------------------------------------------------------
-constexpr int kWqThreads = 256;
+__device__ __forceinline__ float amplified_value(float s, float c, int scale_mode) {
+    if (scale_mode == IS_SCALE_NORM) return c > 0.0f ? s / c : 0.0f;
+    return s;
+}
 
+__device__ __forceinline__ int amplifier_log2_for(float smin) {
+    // smallest i >= 0 with smin * 2^i >= 1, capped (Sec. 4.1)
+    int i = 0;
+    while (i < IS_ALPHA_LOG2_MAX && ldexpf(smin, i) < 1.0f) ++i;
+    return i;
+}
+
+// ---------------------------------------------------------------------------------------------------------
+// Weights, all steps in one pass (groups of 8 * LPG values, LPG a power of two; fixed amplifier).  A workgroup takes whole rows,
+// a lane 16 bytes (8 values) at a time, so that LPG neighbouring lanes hold a group and a wave's load is one contiguous
+// kilobyte; four loads are in flight per lane.  The group maximum goes through lane swizzles, the codes as the activation
+// quantiser takes them (act_common.h), and the group scales stay in LDS until the row's are complete: then c[n] and the
+// integer scales follow without a kernel, and a trip through memory, of their own.  Bound by memory: 2.56 bytes a weight;
+// 28672 x 4096, int4: 59 us, 5.1 TB/s (separate
+// kernels, a wave per group with 4-byte loads: 220 + 6 us).
+// BITS = 4: codes -8..7, s = absmax / 7, two codes per byte, even k in the low nibble; BITS = 8 (the fine-grained W8A8
+// recipe): codes -128..127, s = absmax / 127, one code per byte, row-major.
+// ---------------------------------------------------------------------------------------------------------
+constexpr int kWqThreads = 256, kWqInFlight = 4;
+constexpr int kWqMaxGroups = 2048;  // group scales a workgroup keeps in LDS
+
+template <int LPG>
+__device__ __forceinline__ float group_max(float v) {  // values >= 0; over aligned sets of LPG lanes
+    unsigned x = __float_as_uint(v);
+    if constexpr (LPG >= 2) x = max(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xF, 0xF, true));
+    if constexpr (LPG >= 4) x = max(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xF, 0xF, true));
+    if constexpr (LPG >= 8) x = max(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x141, 0xF, 0xF, true));
+    if constexpr (LPG >= 16) x = max(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x140, 0xF, 0xF, true));
+    if constexpr (LPG >= 32) x = max(x, (unsigned)__shfl_xor((int)x, 16, kWave));
+    if constexpr (LPG >= 64) x = max(x, (unsigned)__shfl_xor((int)x, 32, kWave));
+    return __uint_as_float(x);
+}
+
+template <int BITS, int LPG>
+__global__ __launch_bounds__(kWqThreads) void quantize_weight_rows_kernel(const uint4* __restrict__ w, int N, int K, int rows_per_wg,
+                                                                          int alpha_log2, int scale_mode,
+                                                                          void* __restrict__ qweight,
+                                                                          float* __restrict__ scale_f32,
+                                                                          int32_t* __restrict__ scale_i32,
+                                                                          float* __restrict__ chan_scale,
+                                                                          int* __restrict__ alpha_log2_dev) {
+    constexpr float kHi = BITS == 4 ? 7.0f : 127.0f;
+    __shared__ float scales[kWqMaxGroups];
+    const int row0 = blockIdx.x * rows_per_wg, rows = min(rows_per_wg, N - row0);
+    const int chunks = rows * (K >> 3), NG = (K >> 3) / LPG;
+    const uint4* src = w + (size_t)row0 * (K >> 3);
+    float* sdst = scale_f32 + (size_t)row0 * NG;
+    for (int c0 = 0; c0 < chunks; c0 += kWqThreads * kWqInFlight) {
+        uint4 v[kWqInFlight];
+#pragma unroll
+        for (int i = 0; i < kWqInFlight; ++i) v[i] = src[min(c0 + i * kWqThreads + (int)threadIdx.x, chunks - 1)];
+#pragma unroll
+        for (int i = 0; i < kWqInFlight; ++i) {
+            if (c0 + i * kWqThreads >= chunks) break;  // uniform
+            const int c = c0 + i * kWqThreads + (int)threadIdx.x;
+            const float s = group_max<LPG>(absmax8(v[i])) / kHi;
+            const __half2* h = reinterpret_cast<const __half2*>(&v[i]);
+            float x[8];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float2 f = __half22float2(h[j]);
+                x[2 * j] = f.x;
+                x[2 * j + 1] = f.y;
+            }
+            uint32_t code[8];
+            offset_codes<BITS == 4 ? 8 : 128>(x, s, code);  // (flipping the top bit takes the offset out: two's complement)
+            if (c < chunks) {
+                if constexpr (BITS == 4) {
+                    const uint32_t even = low_bytes(code[0], code[2], code[4], code[6]) & 0x0F0F0F0Fu;
+                    const uint32_t odd = low_bytes(code[1], code[3], code[5], code[7]) & 0x0F0F0F0Fu;
+                    static_cast<uint32_t*>(qweight)[(size_t)row0 * (K >> 3) + c] = (even | (odd << 4)) ^ 0x88888888u;
+                } else {
+                    static_cast<uint2*>(qweight)[(size_t)row0 * (K >> 3) + c] =
+                        make_uint2(low_bytes(code[0], code[1], code[2], code[3]) ^ 0x80808080u,
+                                   low_bytes(code[4], code[5], code[6], code[7]) ^ 0x80808080u);
+                }
+                if ((threadIdx.x & (LPG - 1)) == 0) {
+                    scales[c / LPG] = s;
+                    sdst[c / LPG] = s;
+                }
+            }
+        }
+    }
+    __syncthreads();
+    const int lane = threadIdx.x & (kWave - 1);
+    for (int r = threadIdx.x / kWave; r < rows; r += kWqThreads / kWave) {  // a wave per row
+        const int n = row0 + r;
+        float c = 1.0f;
+        if (scale_mode == IS_SCALE_NORM) {
+            c = 0.0f;
+            for (int g = lane; g < NG; g += kWave) c = fmaxf(c, scales[r * NG + g]);
+            c = wave_max(c);
+        }
+        if (lane == 0) chan_scale[n] = c;
+        for (int g = lane; g < NG; g += kWave)
+            scale_i32[(size_t)n * NG + g] = (int32_t)rintf(ldexpf(amplified_value(scales[r * NG + g], c, scale_mode), alpha_log2));
+        if (n == 0 && lane == 0 && alpha_log2_dev) *alpha_log2_dev = alpha_log2;
+    }
+}
+
+// ---------------------------------------------------------------------------------------------------------
+// The same in separate steps, for the groups and rows the kernel above does not take, and for the amplifier search, which
+// needs all rows' scales before the first integer scale.  Step 1: one wave per (row, group); each lane owns pairs of
+// neighbouring k so that it writes whole bytes.
+// ---------------------------------------------------------------------------------------------------------
 template <int BITS>
 __global__ __launch_bounds__(kWqThreads) void quantize_weight_groups_kernel(const __half* __restrict__ w, int N, int K,
                                                                             int G, uint8_t* __restrict__ qweight,
@@ -110,18 +215,6 @@ __global__ __launch_bounds__(kWqThreads) void quantize_weight_groups_kernel(cons
             reinterpret_cast<uint16_t*>(dst)[p] = (uint16_t)(((uint32_t)q0 & 0xFFu) | (((uint32_t)q1 & 0xFFu) << 8));
         }
     }
-}
-
-__device__ __forceinline__ float amplified_value(float s, float c, int scale_mode) {
-    if (scale_mode == IS_SCALE_NORM) return c > 0.0f ? s / c : 0.0f;
-    return s;
-}
-
-__device__ __forceinline__ int amplifier_log2_for(float smin) {
-    // smallest i >= 0 with smin * 2^i >= 1, capped (Sec. 4.1)
-    int i = 0;
-    while (i < IS_ALPHA_LOG2_MAX && ldexpf(smin, i) < 1.0f) ++i;
-    return i;
 }
 
 // Weights, step 2: one wave per row.  Channel scale c[n], then either the integer scales (fixed amplifier) or this
@@ -204,6 +297,27 @@ hipError_t launch_quantize_weights(const __half* w, int N, int K, int group, int
                                    uint8_t* qweight, float* scale_f32, int32_t* scale_i32, float* chan_scale,
                                    int* alpha_log2_dev, hipStream_t stream, int bits) {
     const int NG = K / group;
+    const int lpg = group >> 3;
+    // (a search needs the largest amplifier of all rows first; rows of more scales than fit LDS, and groups that are not 8
+    // times a power of two up to 64 values, have lanes to spare in the kernels below)
+    if (alpha_log2 >= 0 && NG <= kWqMaxGroups && (group & 7) == 0 && lpg >= 4 && lpg <= 64 && (lpg & (lpg - 1)) == 0) {
+        // whole rows of up to one round of loads in flight; at least one
+        const int chunks = K >> 3;
+        const int rows = std::max(1, std::min(kWqThreads * kWqInFlight / chunks, kWqMaxGroups / NG));
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)((N + rows - 1) / rows)), dim3(kWqThreads), 0, stream,
+                               reinterpret_cast<const uint4*>(w), N, K, rows, alpha_log2, scale_mode,
+                               static_cast<void*>(qweight), scale_f32, scale_i32, chan_scale, alpha_log2_dev);
+            return hipGetLastError();
+        };
+        switch (lpg) {
+            case 4: return bits == 4 ? launch(quantize_weight_rows_kernel<4, 4>) : launch(quantize_weight_rows_kernel<8, 4>);
+            case 8: return bits == 4 ? launch(quantize_weight_rows_kernel<4, 8>) : launch(quantize_weight_rows_kernel<8, 8>);
+            case 16: return bits == 4 ? launch(quantize_weight_rows_kernel<4, 16>) : launch(quantize_weight_rows_kernel<8, 16>);
+            case 32: return bits == 4 ? launch(quantize_weight_rows_kernel<4, 32>) : launch(quantize_weight_rows_kernel<8, 32>);
+            default: return bits == 4 ? launch(quantize_weight_rows_kernel<4, 64>) : launch(quantize_weight_rows_kernel<8, 64>);
+        }
+    }
     const long long units = (long long)N * NG;
     const int waves_per_block = kWqThreads / kWave;
     const unsigned blocks1 = (unsigned)((units + waves_per_block - 1) / waves_per_block);

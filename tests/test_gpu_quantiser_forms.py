@@ -63,3 +63,26 @@ def test_silu_mul_on_every_gate_value(P):
     h = O.silu_mul_fp16(gu)
     ref, ref_s = O.quantize_act_int8_token(h)
     assert np.array_equal(host(sa), ref_s) and np.array_equal(host(xq), ref)
+
+
+@pytest.mark.parametrize("N,K,group", [(3, 128, 128), (130, 1024, 128), (5, 33792, 128), (9, 4096, 32), (70, 192, 64), (17, 2048, 256),
+                                       (6, 3584, 512), (2, 131072, 64), (2, 1 << 18, 64), (11, 960, 24), (5, 1024, 1024)])
+@pytest.mark.parametrize("bits", [4, 8])
+def test_weight_codes_and_scales(P, N, K, group, bits):
+    """One pass over whole rows, and the shapes it leaves to the kernels in steps (rows of more scales than LDS holds, groups
+    that are no power of two, groups beyond 512)."""
+    rng = np.random.default_rng(N + K + group)
+    w = (rng.standard_normal((N, K)) * 0.02).astype(np.float16)
+    w[0, :group] = 0                                                 # a group of zeros
+    hi = 7 if bits == 4 else 127
+    amax = np.abs(w[N - 1]).reshape(-1, group).max(axis=1).astype(np.float32)
+    half = (rng.integers(-hi, hi, size=(K // group, group)) + 0.5) * (amax / np.float32(hi)).astype(np.float64)[:, None]
+    half[:, 0] = amax
+    w[N - 1] = np.clip(half.astype(np.float16), -amax[:, None].astype(np.float16), amax[:, None].astype(np.float16)).reshape(-1)
+    quantise = P.is_quantize_weights_int4_group if bits == 4 else P.is_quantize_weights_int8_group
+    oracle = O.quantize_weights_int4_group if bits == 4 else O.quantize_weights_int8_group
+    for mode in (O.SCALE_RAW, O.SCALE_NORM):
+        got, ref = quantise(dev(w), group, 10, mode), oracle(w, group, 10, mode)
+        assert np.array_equal(host(got.scale_f32), ref.scale_f32) and np.array_equal(host(got.qweight), ref[0])
+        assert np.array_equal(host(got.scale_i32), ref.scale_i32) and np.array_equal(host(got.chan_scale), ref.chan_scale)
+        assert host(got.alpha_log2_dev)[0] == 10
