@@ -33,6 +33,28 @@ __device__ __forceinline__ void load_to_lds_b128(v4i desc, unsigned lds_base, un
                  : "s"(lds_base), "s"(lds_offset), "v"(voffset), "s"(desc), "s"(soffset)
                  : "memory", "scc");
 }
+// Four (two) such loads in a row with one setting of the LDS base: kilobyte i goes to lds_base + lds_offset + 1024 i, and
+// the instruction's offset of 1024 i counts for the global address as well (the caller's descriptors allow for it).
+__device__ __forceinline__ void load_to_lds_4x1k(v4i d0, v4i d1, v4i d2, v4i d3, unsigned lds_base, unsigned lds_offset,
+                                                 int voffset, int soffset) {
+    asm volatile("s_add_u32 m0, %0, %1\n\ts_nop 0\n\t"
+                 "buffer_load_dwordx4 %2, %3, %7 offen lds\n\t"
+                 "buffer_load_dwordx4 %2, %4, %7 offen offset:1024 lds\n\t"
+                 "buffer_load_dwordx4 %2, %5, %7 offen offset:2048 lds\n\t"
+                 "buffer_load_dwordx4 %2, %6, %7 offen offset:3072 lds"
+                 :
+                 : "s"(lds_base), "s"(lds_offset), "v"(voffset), "s"(d0), "s"(d1), "s"(d2), "s"(d3), "s"(soffset)
+                 : "memory", "scc");
+}
+__device__ __forceinline__ void load_to_lds_2x1k(v4i d0, unsigned lds_base, unsigned lds_offset, int voffset, int soffset) {
+    asm volatile("s_add_u32 m0, %0, %1\n\ts_nop 0\n\t"
+                 "buffer_load_dwordx4 %2, %3, %4 offen lds\n\t"
+                 "buffer_load_dwordx4 %2, %3, %4 offen offset:1024 lds"
+                 :
+                 : "s"(lds_base), "s"(lds_offset), "v"(voffset), "s"(d0), "s"(soffset)
+                 : "memory", "scc");
+}
+
 // Preparation of the scales: st[e][g][n] = scale[e][n][g] (32-bit words, integer or float alike), through a 64 x 64
 // LDS tile so that both sides are coalesced; CHECK also raises the flag if an integer scale does not fit 24 signed
 // bits (the limit of v_mad_i32_i24).
