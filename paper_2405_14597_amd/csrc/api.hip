@@ -6,6 +6,7 @@
 
 #include "is_common.h"
 #include "pk_common.h"
+#include "wavek_common.h"
 
 using namespace intscale;
 
@@ -45,7 +46,8 @@ int check_gemm_shape(int M, int N, int K, int group) {
 // Regime selection by the number of token rows.  More than 64 rows (per expert on average, for the grouped form)
 // go to the MFMA-bound tiled kernel, which needs workspace for its zero-point corrections.
 // Routing override (tests and experiments): 0 automatic, 1 everything the general kernel covers goes to it, 2 the
-// W8A8 GEMMs go to the tiled kernel whatever M is, 3 the prepacked calls of 33..64 rows go to the tiled kernel.  Starts from INTSCALE_FORCE_KERNEL=general|tiled, read once;
+// W8A8 GEMMs go to the tiled kernel whatever M is, 3 the prepacked calls of 33..64 rows go to the tiled kernel (with 2 and 3 the
+// prepacked calls of more rows stay there, too).  Starts from INTSCALE_FORCE_KERNEL=general|tiled, read once;
 // is_set_kernel_route changes it afterwards.  Nothing on the launch path reads the environment.
 std::atomic<int> g_route{-1};
 int kernel_route() {
@@ -109,6 +111,12 @@ int static_scratch(void** ptr_out) {
 }
 
 }  // namespace
+
+namespace intscale {
+// The calls of the tiled kernel that the kernel takes whose waves split K (more than 64 rows, where it is faster; routes 2
+// and 3 keep them on the tiled kernel).
+bool takes_wavek(int M, int N, int K) { return M > 64 && kernel_route() < 2 && wavek_is_faster(M, N, K); }
+}  // namespace intscale
 
 extern "C" {
 
@@ -744,6 +752,13 @@ int is_describe_prepacked(int M, int N, int K, int group, int int_scale, int fp1
     if (M < 1) return IS_ERR_INVALID_ARG;
     const int shape = check_pk_shape(N, K, group);
     if (shape != IS_OK) return shape;
+    if (pk_takes_tile(M, N, K) && takes_wavek(M, N, K)) {
+        const bool quantises = fp16_in != 0 && gemm_tile_pk_takes_fp16(K);
+        char name[64];
+        wavek_kernel_name(wavek_plan(M, N), int_scale != 0, false, false, name, sizeof name);
+        snprintf(names, names_len, "%s\n%s", quantises ? "quantize_prepare_rows_pk_kernel" : "prepare_activations_pk_kernel", name);
+        return IS_OK;
+    }
     if (pk_takes_tile(M, N, K)) {
         gemm_tile_pk_kernel_names(K, int_scale != 0, fp16_in != 0 && M > 64 && gemm_tile_pk_takes_fp16(K), names, names_len);
         return IS_OK;

@@ -41,6 +41,7 @@
 #include "act_common.h"
 #include "pk_common.h"
 #include "tile_common.h"
+#include "wavek_common.h"
 
 namespace intscale {
 namespace {
@@ -677,8 +678,15 @@ __device__ __forceinline__ void dense_tile_rows(const PkArgs& a, const int8_t* _
                                                 const TileSplit& sp, const TileGroups& none, unsigned char* smem) {
     if constexpr (INT_SCALE) {
         const int flags = *reinterpret_cast<const int32_t*>(a.spack);
-        if (flags & kPkFlagWide) tile_pk<true, true, false, MS, SILU>(a, xp, c0, sp, none, nullptr, 0, smem);
-        else tile_pk<true, false, false, MS, SILU>(a, xp, c0, sp, none, nullptr, 0, smem);
+        // (the statements keep the compiler from merging the ends of the two copies, which would lead from one copy's
+        // epilogue back into the other's)
+        if (flags & kPkFlagWide) {
+            tile_pk<true, true, false, MS, SILU>(a, xp, c0, sp, none, nullptr, 0, smem);
+            asm volatile("; 32-bit multiplies" ::: "memory");
+        } else {
+            tile_pk<true, false, false, MS, SILU>(a, xp, c0, sp, none, nullptr, 0, smem);
+            asm volatile("; 24-bit multiplies" ::: "memory");
+        }
     } else {
         tile_pk<false, false, false, MS, SILU>(a, xp, c0, sp, none, nullptr, 0, smem);
     }
@@ -835,6 +843,23 @@ hipError_t launch_gemm_tile_pk(const PkArgs& a, bool int_scale, void* workspace,
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
+    if (takes_wavek(a.M, a.N, a.K)) {  // the same prepared activations, another kernel behind them
+        WavekArgs w;
+        w.xp = xp;
+        w.a_scale = a.a_scale;
+        w.w = a.wpack;
+        w.scale = a.spack + kPkHeaderBytes;
+        w.flags = a.spack;
+        w.chan_scale = a.chan_scale;
+        w.out = a.out;
+        w.acc_out = a.acc_out;
+        w.M = a.M;
+        w.N = a.N;
+        w.K = a.K;
+        w.group = a.group;
+        w.alpha_log2 = a.alpha_log2;
+        return launch_gemm_wavek(w, wavek_plan(a.M, a.N), int_scale, false, a.pair != 0, stream);
+    }
     const size_t smem = 2 * (size_t)stage_bytes(kMS);
     const int tiles = sp.whole + sp.rem * sp.parts;  // workgroups
     static LdsLimit limits[4];

@@ -1,0 +1,392 @@
+// Fine-grained W4A8 and W8A8 GEMM for a moderate number of token rows (a prompt's chunk, a large decode batch): the
+// waves of a workgroup split K.  Integer-scale form: Eq. (2) / Table 2 "Ours" of the Integer Scale paper; float-scale form:
+// Eq. (1) / Table 2 "Atom".
+//
+// What bounds this regime.  A few hundred token rows make a few dozen tiles of 128 x 256, far fewer than the chip has
+// compute units; cutting their K range over workgroups moves partial tiles of 128 KB through memory, and one workgroup per tile
+// adds them up while the others are done (300 x 4096 x 4096: 8 K steps a workgroup, 31 us).  Here a workgroup owns a
+// small output tile (up to 64 x 64) over all of K, each of its waves multiplies the whole tile over its own run of K steps,
+// and the partial tiles meet in LDS.  300 rows make 320 workgroups of 4096 columns, no partial tile leaves the compute
+// unit, and no wave waits for another before the end: there is no barrier in the K loop.
+//
+// Operands go straight from global memory to the registers of the wave that multiplies them (no two waves of a workgroup
+// read the same bytes, so LDS would only pass them on): weights in the 1 KB blocks of the kernel layout, activations in the
+// 2 KB blocks that the tiled kernel's preparation writes, every load one contiguous kilobyte.  (Row-major activations, which
+// need no preparation, cost 71 cycles per load and compute unit in 16 pieces of 64 bytes against about 30: 2048 x 28672 x 4096
+// 519 against 344 us, and no gain at 65 rows.)  Each register is asked for again as soon as its last use has been
+// issued, a K step ahead; two waves per SIMD cover the rest of the latency.  12 KB of operands per 32 MFMAs of a wave leave
+// the kernel bound by the L2 (32 bytes per cycle and compute unit), not by the matrix pipe: large calls stay on the
+// tiled kernel, which shares its operands through LDS (takes_wavek says where the line lies).
+//
+// int4 -> int8 with a zero point, as in the tiled kernel: (word ^ 0x08..) & 0x0F.. is q + 8, and the MFMA chain starts from
+// -8 * sum_k x[m,k].  That sum comes from the matrix pipe as well (a multiplication by a constant operand of -8s gives it in every
+// column): 2 MFMAs per 8, where loading the preparation's sums costs a request per sub-tile (M = 300, 4096 x 14336:
+// 43.7 with the loads, 41.7 us without).
+//
+// Measured (GEMM on int8 codes, its preparation included, graph replay), the tiled kernel's time first: 65 x 4096 x 4096
+// 32.9 -> 12.6 us, 300 x 4096 x 4096 36.4 -> 19.5 us, 512 x 6144 x 4096 42.2 -> 28.5 us, 300 x 28672 x 4096 72.9 -> 63.0 us,
+// 128 x 4096 x 14336 46.2 -> 25.0 us; 1024 x 28672 x 4096 147 against 181 us (stays on the tiled kernel).
+#include <stdio.h>
+
+#include <algorithm>
+
+#include "act_common.h"
+#include "pk_common.h"
+#include "wavek_common.h"
+
+namespace intscale {
+namespace {
+
+typedef int v4i_t __attribute__((ext_vector_type(4)));
+typedef float v4f_t __attribute__((ext_vector_type(4)));
+
+constexpr int kNS = 4;                // 16-row weight sub-tiles of a tile: 64 output columns
+constexpr int kTN = kNS * 16;
+constexpr int kXcdCount = 8;          // workgroup i is dispatched to XCD i % 8
+constexpr int kGroupRows = 8;         // tile rows of the block of tiles an XCD works on at a time
+constexpr int kPitch = kTN + 8;       // halves per row of the output tile in LDS
+
+constexpr size_t lds_bytes(int MS, int W) { return (size_t)W * MS * kNS * 1024 + (size_t)MS * 16 * kPitch * 2; }
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* base, size_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes > 0x7FFFFFFFull ? 0x7FFFFFFFu : (unsigned)bytes,
+                                             0x00020000);
+}
+
+// MS: 16-row token sub-tiles of a tile.  W: waves.  W8: int8 weights and scales in their canonical layouts.  WIDE: 32-bit
+// multiplies in the integer scale step (some scale does not fit 24 signed bits).
+template <bool INT_SCALE, bool WIDE, bool W8, int MS, int W, bool SILU>
+__device__ __forceinline__ void wavek_tile(const WavekArgs& a, unsigned char* smem) {
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int li = lane & 15, kb = lane >> 4;
+    // ---- which tile: XCD x gets one contiguous range of tile numbers, and a range walks the output in blocks of kGroupRows
+    // tile rows, column by column (the row tiles that share weights meet in that XCD's L2)
+    const int tiles_n = (a.N + kTN - 1) / kTN, tiles_m = (a.M + MS * 16 - 1) / (MS * 16);
+    const int total = tiles_n * tiles_m;
+    const int q8 = total / kXcdCount, r8 = total - q8 * kXcdCount;
+    const int xcd = blockIdx.x % kXcdCount;
+    const int lid = xcd * q8 + min(xcd, r8) + blockIdx.x / kXcdCount;
+    const int gsz = kGroupRows * tiles_n;
+    const int grp = lid / gsz, in_grp = lid - grp * gsz;
+    const int gm = min(kGroupRows, tiles_m - grp * kGroupRows);
+    const int tile_n = in_grp / gm, tile_m = grp * kGroupRows + (in_grp - tile_n * gm);
+    const int m0 = tile_m * MS * 16, n0 = tile_n * kTN;
+    const int m_rows = min(MS * 16, a.M - m0), n_rows = min(kTN, a.N - n0);
+
+    const int steps = a.K >> 7, NG = a.K / a.group, spg = a.group >> 7;
+    const int s_begin = (wave * steps) / W, s_end = ((wave + 1) * steps) / W;
+    const int n16 = (a.N + 15) >> 4;
+
+    // ---- where the operands come from.  Rows and weight tiles past the end read the last one: what comes of them is
+    // never stored.
+    const int m16 = (a.M + 15) >> 4;
+    const auto xres = buffer_of(a.xp, (size_t)m16 * steps * 2048);
+    const auto wres = W8 ? buffer_of(a.w, (size_t)a.N * a.K) : buffer_of(a.w, (size_t)n16 * steps * kPkBlockBytes);
+    const auto sres = W8 ? buffer_of(a.scale, (size_t)a.N * NG * 4) : buffer_of(a.scale, (size_t)n16 * NG * 64);
+    int x_off[MS], w_off[kNS], s_off[kNS];
+#pragma unroll
+    for (int i = 0; i < MS; ++i) x_off[i] = min((m0 >> 4) + i, m16 - 1) * steps * 2048 + lane * 16;
+#pragma unroll
+    for (int j = 0; j < kNS; ++j) {
+        if constexpr (W8) {
+            const int n = min(n0 + 16 * j + li, a.N - 1);
+            w_off[j] = n * a.K + kb * 16;
+            s_off[j] = n * NG * 4;
+        } else {
+            const int nt = min((n0 >> 4) + j, n16 - 1);
+            w_off[j] = nt * steps * kPkBlockBytes + lane * 16;
+            s_off[j] = nt * NG * 64 + li * 4;
+        }
+    }
+    static_assert(!(W8 && WIDE), "int8 weights find wide scales themselves");
+    constexpr int kWRegs = W8 ? 2 : 1;
+    constexpr int kGroupBytes = W8 ? 4 : 64;
+    v4i_t xa[MS][2], wr[kNS][kWRegs];
+    int sc[kNS];
+    auto load_x = [&](int i, int s) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            xa[i][h] = __builtin_amdgcn_raw_buffer_load_b128(xres, x_off[i] + h * 1024, s * 2048, 0);
+    };
+    auto load_w = [&](int s, int g) {
+#pragma unroll
+        for (int j = 0; j < kNS; ++j) {
+#pragma unroll
+            for (int h = 0; h < kWRegs; ++h)
+                wr[j][h] = __builtin_amdgcn_raw_buffer_load_b128(wres, w_off[j] + h * 64, s * (W8 ? 128 : kPkBlockBytes), 0);
+            sc[j] = __builtin_amdgcn_raw_buffer_load_b32(sres, s_off[j], g * kGroupBytes, 0);
+        }
+    };
+
+    using acc4 = typename std::conditional<INT_SCALE, v4i_t, v4f_t>::type;
+    acc4 acc[MS][kNS];
+    // (int8 weights: the largest and smallest integer scale met; the kernel layout of int4 weights says it in its header)
+    int sc_max = 0, sc_min = 0;
+    auto k_loop = [&](auto wide_c) {
+        constexpr bool kWideNow = decltype(wide_c)::value;
+#pragma unroll
+        for (int i = 0; i < MS; ++i)
+#pragma unroll
+            for (int j = 0; j < kNS; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[i][j][r] = 0;
+        if (s_begin >= s_end) return;  // (a K range of fewer steps than waves leaves some without any)
+        auto correction = [&](int i) {
+            v4i_t c = {0, 0, 0, 0};
+            if constexpr (!W8) {
+                constexpr int kM8 = (int)0xF8F8F8F8u;
+                const v4i_t m8 = {kM8, kM8, kM8, kM8};
+                c = __builtin_amdgcn_mfma_i32_16x16x64_i8(xa[i][0], m8, c, 0, 0, 0);
+                c = __builtin_amdgcn_mfma_i32_16x16x64_i8(xa[i][1], m8, c, 0, 0, 0);
+            }
+            return c;
+        };
+        auto scale_into = [&](acc4& dst, const v4i_t& part, int sc_i) {
+            const float s_f = __int_as_float(sc_i);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                if constexpr (!INT_SCALE) dst[r] = fmaf((float)part[r], s_f, dst[r]);  // C' += float(C_g) * s_g
+                else if constexpr (kWideNow) {
+                    int prod = part[r] * sc_i;
+                    asm volatile("" : "+v"(prod));  // else a 64-bit multiply-add with register pairs
+                    dst[r] += prod;
+                } else dst[r] += __mul24(part[r], sc_i);  // C'' += C_g * s_g^INT
+            }
+        };
+        int g = s_begin / spg, sub = s_begin - g * spg;
+        load_w(s_begin, g);
+#pragma unroll
+        for (int i = 0; i < MS; ++i) load_x(i, s_begin);
+        for (int s = s_begin; s < s_end; ++s) {
+            const int next = min(s + 1, s_end - 1);  // (the last step asks for itself again: nobody uses it)
+            if (s + 1 < s_end && ++sub == spg) {
+                sub = 0;
+                ++g;
+            }
+            v4i_t bu[kNS][2];
+            int scl[kNS];
+#pragma unroll
+            for (int j = 0; j < kNS; ++j) {
+                scl[j] = sc[j];
+                if constexpr (W8) {
+                    bu[j][0] = wr[j][0];
+                    bu[j][1] = wr[j][kWRegs - 1];
+                } else {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const uint32_t pw = (uint32_t)wr[j][0][q];
+                        bu[j][0][q] = (int)((pw ^ 0x08080808u) & 0x0F0F0F0Fu);         // k 0..63 of the step: low nibbles
+                        bu[j][1][q] = (int)(((pw >> 4) ^ 0x08080808u) & 0x0F0F0F0Fu);  // k 64..127: high nibbles
+                    }
+                }
+            }
+            if constexpr (W8 && INT_SCALE && !kWideNow) {
+                static_assert(kNS == 4, "two three-way maxima");
+                sc_max = max(max(max(max(sc_max, scl[0]), scl[1]), scl[2]), scl[3]);
+                sc_min = min(min(min(min(sc_min, scl[0]), scl[1]), scl[2]), scl[3]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            load_w(next, g);
+            __builtin_amdgcn_sched_barrier(0);
+            v4i_t part[2][kNS];
+            v4i_t ci = correction(0);
+#pragma unroll
+            for (int i = 0; i < MS; ++i) {
+                const int cur = i & 1, prev = cur ^ 1;
+#pragma unroll
+                for (int j = 0; j < kNS; ++j)
+                    part[cur][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(xa[i][0], bu[j][0], ci, 0, 0, 0);
+#pragma unroll
+                for (int j = 0; j < kNS; ++j)
+                    part[cur][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(xa[i][1], bu[j][1], part[cur][j], 0, 0, 0);
+                if (i + 1 < MS) ci = correction(i + 1);
+                __builtin_amdgcn_sched_barrier(0);
+                load_x(i, next);
+                __builtin_amdgcn_sched_barrier(0);
+                if (i > 0) {  // the scale step of the sub-tile before, under this one's MFMAs
+#pragma unroll
+                    for (int j = 0; j < kNS; ++j) scale_into(acc[i - 1][j], part[prev][j], scl[j]);
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < kNS; ++j) scale_into(acc[MS - 1][j], part[(MS - 1) & 1][j], scl[j]);
+        }
+    };
+    k_loop(std::integral_constant<bool, WIDE>{});
+    if constexpr (W8 && INT_SCALE) {  // a scale of more than 24 signed bits was among them: once more, with full multiplies
+        if (__any(sc_max >= (1 << 23) || sc_min < -(1 << 23))) k_loop(std::true_type{});
+    }
+
+    // ---- the waves' partial tiles meet in LDS: [wave][sub-tile i][j][lane][4 rows], 16 bytes a lane, no bank conflicts.
+    // Units of one token sub-tile and two weight sub-tiles are dealt to the waves, which add them in wave order.
+    v4i_t* parts = reinterpret_cast<v4i_t*>(smem);
+    __half* otile = reinterpret_cast<__half*>(smem + (size_t)W * MS * kNS * 1024);
+#pragma unroll
+    for (int i = 0; i < MS; ++i)
+#pragma unroll
+        for (int j = 0; j < kNS; ++j) {
+            v4i_t o;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                if constexpr (INT_SCALE) o[r] = acc[i][j][r];
+                else o[r] = __float_as_int(acc[i][j][r]);
+            }
+            parts[((wave * MS + i) * kNS + j) * kWave + lane] = o;
+        }
+    __syncthreads();
+    const float inv_alpha = __int_as_float((127 - a.alpha_log2) << 23);
+    constexpr int kUnits = MS * kNS / 2;
+#pragma unroll
+    for (int u0 = 0; u0 < kUnits; u0 += W) {
+        const int u = u0 + wave;  // (uniform over the wave)
+        if (u >= kUnits) break;
+        const int i = u / (kNS / 2), jp = u - i * (kNS / 2);
+        acc4 v[2];
+        float c[2], sa[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sa[r] = a.a_scale[min(m0 + 16 * i + 4 * kb + r, a.M - 1)];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int nl = (2 * jp + j) * 16 + li;
+            c[j] = 1.0f;
+            if constexpr (INT_SCALE) {
+                if (a.chan_scale) c[j] = a.chan_scale[min(n0 + nl, a.N - 1)];
+                c[j] *= inv_alpha;
+            }
+            v4i_t got[W];
+#pragma unroll
+            for (int w = 0; w < W; ++w) got[w] = parts[((w * MS + i) * kNS + 2 * jp + j) * kWave + lane];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                if constexpr (INT_SCALE) {
+                    v[j][r] = got[0][r];
+#pragma unroll
+                    for (int w = 1; w < W; ++w) v[j][r] += got[w][r];
+                } else {
+                    v[j][r] = __int_as_float(got[0][r]);
+#pragma unroll
+                    for (int w = 1; w < W; ++w) v[j][r] += __int_as_float(got[w][r]);
+                }
+            }
+            if constexpr (INT_SCALE) {
+                if (a.acc_out) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int ml = 16 * i + 4 * kb + r;
+                        if (ml < m_rows && nl < n_rows) a.acc_out[(size_t)(m0 + ml) * a.N + n0 + nl] = v[j][r];
+                    }
+                }
+            }
+        }
+        // FLOAT(acc) * s_a[m] * c[n] / alpha (Eq. (2)), or facc * s_a[m] (Eq. (1))
+        auto result = [&](int j, int r) {
+            if constexpr (INT_SCALE) return __float2half_rn((float)v[j][r] * sa[r] * c[j]);
+            else return __float2half_rn(v[j][r] * sa[r]);
+        };
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            __half* row = otile + (16 * i + 4 * kb + r) * kPitch;
+            if constexpr (SILU) {  // the two weight sub-tiles are the gate and up rows of the same 16 outputs
+                row[jp * 16 + li] = __float2half_rn(silu_mul(__half2float(result(0, r)), __half2float(result(1, r))));
+            } else {
+                row[2 * jp * 16 + li] = result(0, r);
+                row[(2 * jp + 1) * 16 + li] = result(1, r);
+            }
+        }
+    }
+    __syncthreads();
+    const int out_n = SILU ? a.N >> 1 : a.N, out_n0 = SILU ? n0 >> 1 : n0, out_cols = SILU ? n_rows >> 1 : n_rows;
+    constexpr int kCols = SILU ? kTN / 2 : kTN;
+    __half* out = a.out + (size_t)m0 * out_n + out_n0;
+    if ((out_n & 7) == 0) {  // 16 bytes a lane
+        constexpr int kChunks = kCols / 8;
+        for (int e = tid; e < MS * 16 * kChunks; e += W * kWave) {
+            const int ml = e / kChunks, ch = e % kChunks;
+            if (ml < m_rows && ch * 8 < out_cols)
+                *reinterpret_cast<uint4*>(out + (size_t)ml * out_n + ch * 8) = *reinterpret_cast<const uint4*>(otile + ml * kPitch + ch * 8);
+        }
+    } else {
+        for (int e = tid; e < MS * 16 * kCols; e += W * kWave) {
+            const int ml = e / kCols, col = e % kCols;
+            if (ml < m_rows && col < out_cols) out[(size_t)ml * out_n + col] = otile[ml * kPitch + col];
+        }
+    }
+}
+
+// (two waves per SIMD: 256 registers a wave, and MFMA results in ordinary registers, where the scale step reads them)
+template <bool INT_SCALE, bool W8, int MS, int W, bool SILU>
+__global__ __launch_bounds__(W* kWave) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_wavek_kernel(WavekArgs a) {
+    extern __shared__ __align__(16) unsigned char smem_wk[];
+    if constexpr (INT_SCALE && !W8) {
+        if (*reinterpret_cast<const int32_t*>(a.flags) & kPkFlagWide) {
+            wavek_tile<true, true, false, MS, W, SILU>(a, smem_wk);
+            return;
+        }
+    }
+    wavek_tile<INT_SCALE, false, W8, MS, W, SILU>(a, smem_wk);
+}
+
+template <bool INT_SCALE, bool W8, int MS, int W, bool SILU>
+hipError_t launch_instance(const WavekArgs& a, hipStream_t stream) {
+    static LdsLimit limit;  // per instantiation
+    auto kernel = gemm_wavek_kernel<INT_SCALE, W8, MS, W, SILU>;
+    const hipError_t r = limit.raise(reinterpret_cast<const void*>(kernel), (int)lds_bytes(MS, W));
+    if (r != hipSuccess) return r;
+    const long long tiles = (long long)((a.N + kTN - 1) / kTN) * ((a.M + MS * 16 - 1) / (MS * 16));
+    hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(W * kWave), lds_bytes(MS, W), stream, a);
+    return hipGetLastError();
+}
+
+template <bool INT_SCALE, bool W8, bool SILU>
+hipError_t launch_shape(const WavekArgs& a, const WavekPlan& p, hipStream_t stream) {
+    if (p.ms == 3) return p.waves == 8 ? launch_instance<INT_SCALE, W8, 3, 8, SILU>(a, stream) : launch_instance<INT_SCALE, W8, 3, 4, SILU>(a, stream);
+    return p.waves == 8 ? launch_instance<INT_SCALE, W8, 4, 8, SILU>(a, stream) : launch_instance<INT_SCALE, W8, 4, 4, SILU>(a, stream);
+}
+
+}  // namespace
+
+WavekPlan wavek_plan(int M, int N) {
+    WavekPlan p;
+    // row tiles of 48 or 64 rows, whichever pads less
+    const int m16 = (M + 15) / 16;
+    p.ms = (m16 + 2) / 3 * 3 < (m16 + 3) / 4 * 4 ? 3 : 4;
+    p.tiles = (long long)((N + kTN - 1) / kTN) * ((M + p.ms * 16 - 1) / (p.ms * 16));
+    // Eight waves where workgroups of four would leave every compute unit with one wave per SIMD at most (65 x 4096 x 14336:
+    // 22.1 against 24.0 us); two workgroups of four share a unit otherwise, one's start and end under the other's K loop.
+    p.waves = p.tiles <= cu_count() ? 8 : 4;
+    return p;
+}
+
+// Both kernels' times from what bounds them, in microseconds; the constants are fits to 33 calls (65 to 2048 rows, 4096 to
+// 28672 columns, K 4096 and 14336; each within a fifth, and the wrong choice on one of them, by 3 %).
+// This kernel: 10 us of launches, preparation, start and end, and 0.76 us per K step of a wave on every SIMD (for 12 KB of
+// operands; 10 KB with 48 rows).  The tiled kernel: 6 us, 2.3 us per K step for a round of two tiles per unit (1.56 when a
+// unit has one), and 14 us more to pass the partial tiles of a cut K range through memory.
+bool wavek_is_faster(int M, int N, int K) {
+    const int steps = K >> 7, cus = cu_count();
+    const WavekPlan p = wavek_plan(M, N);
+    const double here = 10.0 + 0.76 * 0.25 * (double)((p.tiles + cus - 1) / cus) * steps * (2 * p.ms + 4) / 12.0;
+    const long long tiles = (long long)((N + 255) / 256) * ((M + 127) / 128);
+    const int left = (int)(tiles % (2 * cus));
+    double tiled = 6.0 + 2.3 * steps * (double)(tiles / (2 * cus));
+    if (left > cus) tiled += 2.3 * steps;
+    else if (left > 0) {
+        const int parts = std::min(std::min(cus / left, 8), std::max(steps / 8, 1));
+        tiled += 1.56 * steps / parts + (parts > 1 ? 14.0 : 0.0);
+    }
+    return here < tiled;
+}
+
+void wavek_kernel_name(const WavekPlan& p, bool int_scale, bool w8, bool silu, char* buf, size_t len) {
+    snprintf(buf, len, "gemm_wavek_kernel<%s, %s, %d, %d, %s>", int_scale ? "true" : "false", w8 ? "true" : "false", p.ms, p.waves,
+             silu ? "true" : "false");
+}
+
+hipError_t launch_gemm_wavek(const WavekArgs& a, const WavekPlan& p, bool int_scale, bool w8, bool silu, hipStream_t stream) {
+    if (w8) return int_scale ? launch_shape<true, true, false>(a, p, stream) : launch_shape<false, true, false>(a, p, stream);
+    if (silu) return int_scale ? launch_shape<true, false, true>(a, p, stream) : launch_shape<false, false, true>(a, p, stream);
+    return int_scale ? launch_shape<true, false, false>(a, p, stream) : launch_shape<false, false, false>(a, p, stream);
+}
+
+}  // namespace intscale
