@@ -2,6 +2,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "is_common.h"
@@ -115,7 +116,9 @@ int static_scratch(void** ptr_out) {
 namespace intscale {
 // The calls of the tiled kernel that the kernel takes whose waves split K (more than 64 rows, where it is faster; routes 2
 // and 3 keep them on the tiled kernel).
-bool takes_wavek(int M, int N, int K) { return M > 64 && kernel_route() < 2 && wavek_is_faster(M, N, K); }
+bool takes_wavek(int M, int N, int K, bool w8) {
+    return M > 64 && kernel_route() < 2 && (!w8 || (long long)((M + 15) / 16) * 16 * K < (1LL << 31)) && wavek_is_faster(M, N, K, w8);
+}
 }  // namespace intscale
 
 extern "C" {
@@ -791,7 +794,9 @@ static int check_w8_shape(int M, int N, int K, int group) {
 }
 
 size_t is_gemm_w8a8_workspace_bytes(int M, int N, int K, int group) {
-    return check_w8_shape(M, N, K, group) == IS_OK ? gemm_w8_workspace_bytes(1, M, N, K, group) : 0;
+    if (check_w8_shape(M, N, K, group) != IS_OK) return 0;
+    const size_t tiled = gemm_w8_workspace_bytes(1, M, N, K, group);
+    return takes_wavek(M, N, K, true) ? std::max(tiled, gemm_tile_pk_min_workspace_bytes(M, K)) : tiled;
 }
 
 static int gemm_w8_common(const int8_t* xq, const float* a_scale, const int8_t* qweight8, const void* scale,
@@ -826,6 +831,27 @@ static int gemm_w8_common(const int8_t* xq, const float* a_scale, const int8_t* 
     // up to 64 token rows the layer is a weight stream: the bandwidth-bound general kernel; else the tiled kernel
     if (M <= 64 && !general_forced_off())
         return hip_status(launch_gemm_skinny(a, int_scale, static_cast<hipStream_t>(stream)));
+    // a moderate number of rows: activations to the blocks the kernel reads, then the kernel whose waves split K (a
+    // workspace of the size that the tiled kernel alone needs keeps the call there)
+    if (takes_wavek(M, N, K, true) && workspace_bytes >= gemm_tile_pk_min_workspace_bytes(M, K)) {
+        const int st = hip_status(launch_prepare_activations_pk(xq, M, K, workspace, static_cast<hipStream_t>(stream)));
+        if (st != IS_OK) return st;
+        WavekArgs w;
+        w.xp = static_cast<const int8_t*>(workspace);
+        w.a_scale = a_scale;
+        w.w = qweight8;
+        w.scale = scale;
+        w.flags = nullptr;
+        w.chan_scale = chan_scale;
+        w.out = a.out;
+        w.acc_out = acc_out;
+        w.M = M;
+        w.N = N;
+        w.K = K;
+        w.group = group;
+        w.alpha_log2 = a.alpha_log2;
+        return hip_status(launch_gemm_wavek(w, wavek_plan(M, N), int_scale, true, false, static_cast<hipStream_t>(stream)));
+    }
     return hip_status(launch_gemm_w8(a, int_scale, workspace, static_cast<hipStream_t>(stream)));
 }
 

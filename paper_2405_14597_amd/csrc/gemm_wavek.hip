@@ -25,13 +25,14 @@
 //
 // Measured (GEMM on int8 codes, its preparation included, graph replay), the tiled kernel's time first: 65 x 4096 x 4096
 // 32.9 -> 12.6 us, 300 x 4096 x 4096 36.4 -> 19.5 us, 512 x 6144 x 4096 42.2 -> 28.5 us, 300 x 28672 x 4096 72.9 -> 63.0 us,
-// 128 x 4096 x 14336 46.2 -> 25.0 us; 1024 x 28672 x 4096 147 against 181 us (stays on the tiled kernel).
+// 128 x 4096 x 14336 46.2 -> 25.0 us; W8A8 300 x 4096 x 14336 126.4 -> 55.9 us, 1024 x 4096 x 14336 129 -> 103 us; W4A8 1024 x 28672 x 4096 147 against 181 us (stays on the tiled kernel).
 #include <stdio.h>
 
 #include <algorithm>
 
 #include "act_common.h"
 #include "pk_common.h"
+#include "tile_common.h"
 #include "wavek_common.h"
 
 namespace intscale {
@@ -46,7 +47,11 @@ constexpr int kXcdCount = 8;          // workgroup i is dispatched to XCD i % 8
 constexpr int kGroupRows = 8;         // tile rows of the block of tiles an XCD works on at a time
 constexpr int kPitch = kTN + 8;       // halves per row of the output tile in LDS
 
-constexpr size_t lds_bytes(int MS, int W) { return (size_t)W * MS * kNS * 1024 + (size_t)MS * 16 * kPitch * 2; }
+constexpr int kStage8 = kTN * 128;    // int8 weights of one K step
+constexpr size_t lds_bytes(int MS, int W, bool W8) {
+    const size_t sums = (size_t)W * MS * kNS * 1024 + (size_t)MS * 16 * kPitch * 2, stages = W8 ? (size_t)W * 2 * kStage8 : 0;
+    return sums > stages ? sums : stages;
+}
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* base, size_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes > 0x7FFFFFFFull ? 0x7FFFFFFFu : (unsigned)bytes,
@@ -82,7 +87,7 @@ __device__ __forceinline__ void wavek_tile(const WavekArgs& a, unsigned char* sm
     // never stored.
     const int m16 = (a.M + 15) >> 4;
     const auto xres = buffer_of(a.xp, (size_t)m16 * steps * 2048);
-    const auto wres = W8 ? buffer_of(a.w, (size_t)a.N * a.K) : buffer_of(a.w, (size_t)n16 * steps * kPkBlockBytes);
+    const auto wres = W8 ? xres : buffer_of(a.w, (size_t)n16 * steps * kPkBlockBytes);
     const auto sres = W8 ? buffer_of(a.scale, (size_t)a.N * NG * 4) : buffer_of(a.scale, (size_t)n16 * NG * 64);
     int x_off[MS], w_off[kNS], s_off[kNS];
 #pragma unroll
@@ -90,9 +95,7 @@ __device__ __forceinline__ void wavek_tile(const WavekArgs& a, unsigned char* sm
 #pragma unroll
     for (int j = 0; j < kNS; ++j) {
         if constexpr (W8) {
-            const int n = min(n0 + 16 * j + li, a.N - 1);
-            w_off[j] = n * a.K + kb * 16;
-            s_off[j] = n * NG * 4;
+            s_off[j] = min(n0 + 16 * j + li, a.N - 1) * NG * 4;
         } else {
             const int nt = min((n0 >> 4) + j, n16 - 1);
             w_off[j] = nt * steps * kPkBlockBytes + lane * 16;
@@ -100,9 +103,7 @@ __device__ __forceinline__ void wavek_tile(const WavekArgs& a, unsigned char* sm
         }
     }
     static_assert(!(W8 && WIDE), "int8 weights find wide scales themselves");
-    constexpr int kWRegs = W8 ? 2 : 1;
-    constexpr int kGroupBytes = W8 ? 4 : 64;
-    v4i_t xa[MS][2], wr[kNS][kWRegs];
+    v4i_t xa[MS][2], wr[kNS];
     int sc[kNS];
     auto load_x = [&](int i, int s) {
 #pragma unroll
@@ -112,11 +113,40 @@ __device__ __forceinline__ void wavek_tile(const WavekArgs& a, unsigned char* sm
     auto load_w = [&](int s, int g) {
 #pragma unroll
         for (int j = 0; j < kNS; ++j) {
-#pragma unroll
-            for (int h = 0; h < kWRegs; ++h)
-                wr[j][h] = __builtin_amdgcn_raw_buffer_load_b128(wres, w_off[j] + h * 64, s * (W8 ? 128 : kPkBlockBytes), 0);
-            sc[j] = __builtin_amdgcn_raw_buffer_load_b32(sres, s_off[j], g * kGroupBytes, 0);
+            wr[j] = __builtin_amdgcn_raw_buffer_load_b128(wres, w_off[j], s * kPkBlockBytes, 0);
+            sc[j] = __builtin_amdgcn_raw_buffer_load_b32(sres, s_off[j], g * 64, 0);
         }
+    };
+    // int8 weights are row-major: a load takes 8 whole 128-byte lines (one K step of 8 rows) straight to a stage of LDS that
+    // belongs to the wave alone, and the operands are read from there (fetched to registers in 64-byte pieces every line
+    // travelled twice: 300 x 4096 x 14336 131 us).  Two stages of 8 KB in the place of the wave's partial tile.  The 16-byte
+    // chunks of a row are permuted by (row >> 1) & 7, so that the operand reads of 16 rows fall on different banks.
+    const unsigned lds_stage = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem + wave * 2 * kStage8;
+    v4i w8desc;
+    int w8_off[8], w8_read[2];
+    if constexpr (W8) {
+        w8desc = make_desc(a.w, (size_t)a.N * a.K);
+#pragma unroll
+        for (int b = 0; b < 8; ++b) {
+            const int r = 8 * b + (lane >> 3);
+            // (the load's own offset of 1024 (b & 3), which is meant for LDS, is taken off again here: where that is
+            // negative, in a matrix of few short rows, the row is a repeated one, and reads as zero)
+            w8_off[b] = min(n0 + r, a.N - 1) * a.K + (((lane & 7) ^ ((r >> 1) & 7)) << 4) - (b & 3) * 1024;
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) w8_read[h] = wave * 2 * kStage8 + li * 128 + (((4 * h + kb) ^ ((li >> 1) & 7)) << 4);
+    }
+    auto request_w8 = [&](int s) {
+        const unsigned base = lds_stage + (s & 1) * kStage8;
+        load_to_lds_rows_4x1k(w8desc, base, w8_off[0], w8_off[1], w8_off[2], w8_off[3], s * 128);
+        load_to_lds_rows_4x1k(w8desc, base + 4096, w8_off[4], w8_off[5], w8_off[6], w8_off[7], s * 128);
+    };
+    // The scales of a weight row are contiguous along K: lane (li, kb) asks for that of K step s + kb, four steps at once.
+    auto load_sc8 = [&](int s) {
+        const int st = min(s + kb, steps - 1);
+        const int g = spg == 1 ? st : st / spg;
+#pragma unroll
+        for (int j = 0; j < kNS; ++j) sc[j] = __builtin_amdgcn_raw_buffer_load_b32(sres, s_off[j] + g * 4, 0, 0);
     };
 
     using acc4 = typename std::conditional<INT_SCALE, v4i_t, v4f_t>::type;
@@ -155,7 +185,13 @@ __device__ __forceinline__ void wavek_tile(const WavekArgs& a, unsigned char* sm
             }
         };
         int g = s_begin / spg, sub = s_begin - g * spg;
-        load_w(s_begin, g);
+        int sc4[kNS];
+        if constexpr (W8) {
+            load_sc8(s_begin);
+            request_w8(s_begin);
+        } else {
+            load_w(s_begin, g);
+        }
 #pragma unroll
         for (int i = 0; i < MS; ++i) load_x(i, s_begin);
         for (int s = s_begin; s < s_end; ++s) {
@@ -166,16 +202,30 @@ __device__ __forceinline__ void wavek_tile(const WavekArgs& a, unsigned char* sm
             }
             v4i_t bu[kNS][2];
             int scl[kNS];
+            if constexpr (W8) {
+                const int t = (s - s_begin) & 3;
+                if (t == 0) {
 #pragma unroll
-            for (int j = 0; j < kNS; ++j) {
-                scl[j] = sc[j];
-                if constexpr (W8) {
-                    bu[j][0] = wr[j][0];
-                    bu[j][1] = wr[j][kWRegs - 1];
-                } else {
+                    for (int j = 0; j < kNS; ++j) sc4[j] = sc[j];
+                    load_sc8(s + 4);
+                }
+                // This step's lines are in LDS once at most the requests behind them are outstanding: the activations', and the
+                // scales' just above.
+                asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * MS) : "memory");
+#pragma unroll
+                for (int j = 0; j < kNS; ++j) {
+                    scl[j] = __builtin_amdgcn_ds_bpermute((t * 16 + li) * 4, sc4[j]);
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+                        bu[j][h] = *reinterpret_cast<const v4i_t*>(smem + w8_read[h] + (s & 1) * kStage8 + j * 2048);
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < kNS; ++j) {
+                    scl[j] = sc[j];
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
-                        const uint32_t pw = (uint32_t)wr[j][0][q];
+                        const uint32_t pw = (uint32_t)wr[j][q];
                         bu[j][0][q] = (int)((pw ^ 0x08080808u) & 0x0F0F0F0Fu);         // k 0..63 of the step: low nibbles
                         bu[j][1][q] = (int)(((pw >> 4) ^ 0x08080808u) & 0x0F0F0F0Fu);  // k 64..127: high nibbles
                     }
@@ -187,7 +237,8 @@ __device__ __forceinline__ void wavek_tile(const WavekArgs& a, unsigned char* sm
                 sc_min = min(min(min(min(sc_min, scl[0]), scl[1]), scl[2]), scl[3]);
             }
             __builtin_amdgcn_sched_barrier(0);
-            load_w(next, g);
+            if constexpr (W8) request_w8(next);
+            else load_w(next, g);
             __builtin_amdgcn_sched_barrier(0);
             v4i_t part[2][kNS];
             v4i_t ci = correction(0);
@@ -218,6 +269,10 @@ __device__ __forceinline__ void wavek_tile(const WavekArgs& a, unsigned char* sm
         if (__any(sc_max >= (1 << 23) || sc_min < -(1 << 23))) k_loop(std::true_type{});
     }
 
+    if constexpr (W8) {  // every wave is done with its stages, and nothing is on its way to them any more
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+    }
     // ---- the waves' partial tiles meet in LDS: [wave][sub-tile i][j][lane][4 rows], 16 bytes a lane, no bank conflicts.
     // Units of one token sub-tile and two weight sub-tiles are dealt to the waves, which add them in wave order.
     v4i_t* parts = reinterpret_cast<v4i_t*>(smem);
@@ -331,10 +386,10 @@ template <bool INT_SCALE, bool W8, int MS, int W, bool SILU>
 hipError_t launch_instance(const WavekArgs& a, hipStream_t stream) {
     static LdsLimit limit;  // per instantiation
     auto kernel = gemm_wavek_kernel<INT_SCALE, W8, MS, W, SILU>;
-    const hipError_t r = limit.raise(reinterpret_cast<const void*>(kernel), (int)lds_bytes(MS, W));
+    const hipError_t r = limit.raise(reinterpret_cast<const void*>(kernel), (int)lds_bytes(MS, W, W8));
     if (r != hipSuccess) return r;
     const long long tiles = (long long)((a.N + kTN - 1) / kTN) * ((a.M + MS * 16 - 1) / (MS * 16));
-    hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(W * kWave), lds_bytes(MS, W), stream, a);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(W * kWave), lds_bytes(MS, W, W8), stream, a);
     return hipGetLastError();
 }
 
@@ -363,10 +418,14 @@ WavekPlan wavek_plan(int M, int N) {
 // This kernel: 10 us of launches, preparation, start and end, and 0.76 us per K step of a wave on every SIMD (for 12 KB of
 // operands; 10 KB with 48 rows).  The tiled kernel: 6 us, 2.3 us per K step for a round of two tiles per unit (1.56 when a
 // unit has one), and 14 us more to pass the partial tiles of a cut K range through memory.
-bool wavek_is_faster(int M, int N, int K) {
+bool wavek_is_faster(int M, int N, int K, bool w8) {
     const int steps = K >> 7, cus = cu_count();
     const WavekPlan p = wavek_plan(M, N);
-    const double here = 10.0 + 0.76 * 0.25 * (double)((p.tiles + cus - 1) / cus) * steps * (2 * p.ms + 4) / 12.0;
+    const double here = 10.0 + 0.76 * 0.25 * (double)((p.tiles + cus - 1) / cus) * steps * (2 * p.ms + (w8 ? 8 : 4)) / 12.0;
+    if (w8) {  // the W8A8 tiled kernel: one tile per unit at a time, 1.05 us per K step, 14 us of launches and scale transposition
+        const long long rounds = ((long long)((N + 255) / 256) * ((M + 127) / 128) + cus - 1) / cus;
+        return here < 14.0 + 1.05 * steps * (double)rounds;
+    }
     const long long tiles = (long long)((N + 255) / 256) * ((M + 127) / 128);
     const int left = (int)(tiles % (2 * cus));
     double tiled = 6.0 + 2.3 * steps * (double)(tiles / (2 * cus));

@@ -46,6 +46,17 @@ __device__ __forceinline__ void load_to_lds_4x1k(v4i d0, v4i d1, v4i d2, v4i d3,
                  : "s"(lds_base), "s"(lds_offset), "v"(voffset), "s"(d0), "s"(d1), "s"(d2), "s"(d3), "s"(soffset)
                  : "memory", "scc");
 }
+// The same with a vector offset per load and one descriptor.
+__device__ __forceinline__ void load_to_lds_rows_4x1k(v4i desc, unsigned lds_base, int v0, int v1, int v2, int v3, int soffset) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+                 "buffer_load_dwordx4 %1, %5, %6 offen lds\n\t"
+                 "buffer_load_dwordx4 %2, %5, %6 offen offset:1024 lds\n\t"
+                 "buffer_load_dwordx4 %3, %5, %6 offen offset:2048 lds\n\t"
+                 "buffer_load_dwordx4 %4, %5, %6 offen offset:3072 lds"
+                 :
+                 : "s"(lds_base), "v"(v0), "v"(v1), "v"(v2), "v"(v3), "s"(desc), "s"(soffset)
+                 : "memory");
+}
 __device__ __forceinline__ void load_to_lds_2x1k(v4i d0, unsigned lds_base, unsigned lds_offset, int voffset, int soffset) {
     asm volatile("s_add_u32 m0, %0, %1\n\ts_nop 0\n\t"
                  "buffer_load_dwordx4 %2, %3, %4 offen lds\n\t"

@@ -64,3 +64,34 @@ def test_wavek_is_the_tiled_kernel_bit_for_bit(P):
         got[route] = (out, P.is_linear_w4a8_intscale_prepacked(x, pk, dev(c), 10)[0])
         P.is_set_kernel_route(before)
     assert torch.equal(got["auto"][0], got["tiled64"][0]) and torch.equal(got["auto"][1], got["tiled64"][1])
+
+
+# int8 weights: a matrix of few short rows (repeated rows behind the last one), 3 and 9 K steps (waves without work, quads of
+# scales that end in mid-run), row tiles of 48 and 64 rows, workgroups of four and eight waves, wide groups
+@pytest.mark.parametrize("M,N,K,group", [(70, 10, 128, 128), (97, 1, 384, 128), (130, 300, 1152, 128), (250, 4100, 1280, 256),
+                                         (70, 9001, 640, 128)])
+def test_wavek_w8(P, M, N, K, group):
+    rng = np.random.default_rng(6800 + M + N + K)
+    xq = rng.integers(-128, 128, size=(M, K)).astype(np.int8)
+    q = rng.integers(-128, 128, size=(N, K)).astype(np.int8)
+    xq[0], q[0], xq[M - 1] = -128, -128, 127
+    sa = (rng.random(M) + 0.01).astype(np.float32)
+    IS = rng.integers(-2 ** 22, 2 ** 22, size=(N, K // group)).astype(np.int32)
+    wide = IS.copy()
+    wide[N // 2, -1] = 2 ** 23  # one scale beyond 24 signed bits
+    before = P.is_set_kernel_route("tiled")
+    tiled_bytes = P.is_gemm_w8a8_workspace_bytes(M, N, K, group)
+    P.is_set_kernel_route(before)
+    assert P.is_gemm_w8a8_workspace_bytes(M, N, K, group) >= tiled_bytes
+    for scales in (IS, wide):
+        ref = O.gemm_w8a8_intscale(xq, sa, q, scales, None, group, 12)
+        outs = []
+        for nbytes in (tiled_bytes, max(tiled_bytes, P.is_gemm_w8a8_workspace_bytes(M, N, K, group))):  # tiled kernel, this one
+            ws = torch.full((nbytes,), 0x5A, dtype=torch.uint8, device="cuda:0")
+            out, acc = P.is_gemm_w8a8_intscale(dev(xq), dev(sa), dev(q), dev(scales), None, group, 12, want_acc=True, workspace=ws)
+            assert np.array_equal(host(acc), ref.acc), "int32 accumulators differ"
+            outs.append(out)
+        assert torch.equal(outs[0], outs[1])
+    s = (rng.random((N, K // group)) * 1e-4).astype(np.float32)
+    fs = O.gemm_w8a8_floatscale(xq, sa, q, s, group)
+    check_fs(host(P.is_gemm_w8a8_floatscale(dev(xq), dev(sa), dev(q), dev(s), group)), fs, f"M{M} N{N} K{K}")
