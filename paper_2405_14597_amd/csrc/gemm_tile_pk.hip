@@ -138,6 +138,16 @@ __global__ __launch_bounds__(256) void prepare_activations_pk_kernel(const int8_
         if (s0 + j < steps) store_block((size_t)mt * steps + s0 + j, lane, v[j][0], v[j][1], xp, c0);
 }
 
+// Sum of v over the lanes up to and including this one.
+__device__ __forceinline__ int lanes_up_to(int v, int lane) {
+#pragma unroll
+    for (int d = 1; d < kWave; d *= 2) {
+        const int below = __shfl_up(v, d, kWave);
+        if (lane >= d) v += below;
+    }
+    return v;
+}
+
 // Mixture-of-experts form of the kernel above: block x is a 16-row tile of the padded row space (the 16-row tiles of
 // expert 0, then those of expert 1, ...); the first workgroup also lists the 128-row tiles.
 __global__ __launch_bounds__(256) void prepare_activations_grouped_pk_kernel(const int8_t* __restrict__ xq, int K,
@@ -147,53 +157,82 @@ __global__ __launch_bounds__(256) void prepare_activations_grouped_pk_kernel(con
                                                                              int ncounters) {
     if (blockIdx.x == 0 && blockIdx.y == 0)  // the tiled kernel's arrival counters start at zero
         for (int i = threadIdx.x; i < ncounters; i += 256) counters[i] = 0;
-    // (every workgroup fetches the row offsets into LDS in one round trip: the search for its expert below, and the
-    // table, which one thread builds in four passes, would otherwise wait for global memory expert by expert)
+    // (every workgroup fetches the row offsets into LDS in one round trip, for the search for its expert and the table)
     __shared__ int32_t offs[kPkMaxExperts + 1];
     for (int i = threadIdx.x; i <= tg.num_experts; i += 256) offs[i] = tg.row_offsets[i];
     __syncthreads();
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < kWave) {
         // Entries with the most rows first (the tiled kernel's cost grows with an entry's rows and workgroups start in
         // grid order: the short ones then fill the gaps the long ones leave).  Only an expert's last entry can be
-        // short: the first pass lists every entry of more than 64 rows, the others the last entries of 33..64,
-        // 17..32 and 1..16 rows.
-        constexpr int tr = kTM;
-        int used = 0;
-        for (int pass = 0; pass < 4; ++pass) {
-            const int above = pass == 0 ? 64 : pass == 1 ? 32 : pass == 2 ? 16 : 0;
-            const int upto = pass == 0 ? tr : pass == 1 ? 64 : pass == 2 ? 32 : 16;
-            int base16 = 0;
-            for (int e = 0; e < tg.num_experts; ++e) {
-                const int lo = offs[e], rows = offs[e + 1] - lo;
-                const int nt = (rows + tr - 1) / tr;
-                for (int t = tr > upto ? max(nt - 1, 0) : 0; t < nt && used < tg.slots; ++t) {  // (full entries: tr rows)
-                    const int have = min(tr, rows - t * tr);
-                    if (have <= above || have > upto) continue;
-                    int32_t* entry = tg.table + 4 + 4 * used++;
-                    entry[0] = e;
-                    entry[1] = base16 + t * (tr / 16);
-                    entry[2] = lo + t * tr;
-                    entry[3] = have;
-                }
-                base16 += (rows + 15) >> 4;
-            }
+        // short: class 0 are the entries of more than 64 rows, classes 1 to 3 the last entries of 33..64, 17..32 and
+        // 1..16 rows, by expert within a class.  One wave, a lane per expert: its places are sums over the lanes before it
+        // (one thread that walked the experts four times took 3 us of a decode step's two calls each).
+        const int me = threadIdx.x;
+        auto classes = [&](int e, int (&n)[4], int& rows, int& lo) {
+            lo = e < tg.num_experts ? offs[e] : 0;
+            rows = e < tg.num_experts ? offs[e + 1] - lo : 0;
+            const int full = max(rows, 0) / kTM, rest = max(rows, 0) - full * kTM;
+            n[0] = full + (rest > 64 ? 1 : 0);
+            n[1] = rest > 32 && rest <= 64 ? 1 : 0;
+            n[2] = rest > 16 && rest <= 32 ? 1 : 0;
+            n[3] = rest > 0 && rest <= 16 ? 1 : 0;
+        };
+        int start[4] = {0, 0, 0, 0};  // where each class begins, then where the next 64 experts' part of it does
+        int n[4], rows, lo, used = 0;
+        for (int e0 = 0; e0 < tg.num_experts; e0 += kWave) {
+            classes(e0 + me, n, rows, lo);
+            const int c0n = __shfl(lanes_up_to(n[0], me), kWave - 1, kWave);
+            const int c1n = __popcll(__ballot(n[1])), c2n = __popcll(__ballot(n[2])), c3n = __popcll(__ballot(n[3]));
+            start[1] += c0n;
+            start[2] += c0n + c1n;
+            start[3] += c0n + c1n + c2n;
+            used += c0n + c1n + c2n + c3n;
         }
-        tg.table[0] = used;
+        if (me == 0) tg.table[0] = min(used, tg.slots);
+        int base16 = 0;
+        for (int e0 = 0; e0 < tg.num_experts; e0 += kWave) {
+            classes(e0 + me, n, rows, lo);
+            const int n16 = e0 + me < tg.num_experts ? (rows + 15) >> 4 : 0;
+            const int upto0 = lanes_up_to(n[0], me), upto16 = lanes_up_to(n16, me);
+            const unsigned long long before = (1ull << me) - 1;
+            auto put = [&](int at, int t) {
+                if (at >= tg.slots) return;
+                int32_t* entry = tg.table + 4 + 4 * at;
+                entry[0] = e0 + me;
+                entry[1] = base16 + upto16 - n16 + t * (kTM / 16);
+                entry[2] = lo + t * kTM;
+                entry[3] = min(kTM, rows - t * kTM);
+            };
+            for (int t = 0; t < n[0]; ++t) put(start[0] + upto0 - n[0] + t, t);
+#pragma unroll
+            for (int c = 1; c < 4; ++c) {
+                const unsigned long long has = __ballot(n[c]);
+                if (n[c]) put(start[c] + __popcll(has & before), n[0]);
+                start[c] += __popcll(has);
+            }
+            start[0] += __shfl(upto0, kWave - 1, kWave);
+            base16 += __shfl(upto16, kWave - 1, kWave);
+        }
     }
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     const int r = lane & 15, kb = lane >> 4;
     // which expert's rows this 16-row tile holds (uniform over the workgroup)
     const int pt = blockIdx.x;
     int row0 = 0, rows = 0;
-    for (int e = 0, base16 = 0; e < tg.num_experts; ++e) {
-        const int lo = offs[e], me = offs[e + 1] - lo;
+    for (int e0 = 0, base16 = 0; e0 < tg.num_experts; e0 += kWave) {  // 64 experts at a time, a lane each
+        const int e = e0 + lane;
+        const int lo = e < tg.num_experts ? offs[e] : 0, me = e < tg.num_experts ? offs[e + 1] - lo : 0;
         const int n16 = (me + 15) >> 4;
-        if (pt < base16 + n16) {
-            row0 = lo + 16 * (pt - base16);
-            rows = min(16, me - 16 * (pt - base16));
+        const int end = base16 + lanes_up_to(n16, lane);
+        const unsigned long long past = __ballot(e < tg.num_experts && pt < end);
+        if (past != 0) {  // the first of them
+            const int who = __builtin_ctzll(past);
+            const int at = pt - (__shfl(end, who, kWave) - __shfl(n16, who, kWave));
+            row0 = __shfl(lo, who, kWave) + 16 * at;
+            rows = min(16, __shfl(me, who, kWave) - 16 * at);
             break;
         }
-        base16 += n16;
+        base16 = __shfl(end, kWave - 1, kWave);
     }
     if (rows == 0) return;  // past the last expert's tiles
     const int steps = K >> 7;
