@@ -259,66 +259,72 @@ __global__ __launch_bounds__(256) void prepare_activations_grouped_pk_kernel(con
 // pieces.  256 workgroups for 2048 rows: the chip is full, and the activations cross the memory interface once.
 // Lane (h, kb, r): row r of the eight, the 16 codes k = 64 h + 16 kb .. + 15 of a K step; wave w takes the K steps
 // w, w + 16, ...
-constexpr int kRowsPerWg = 8, kRowWaves = 16, kResidentSteps = 8;
+// Few rows make few workgroups of eight: up to kFewRows of them a workgroup takes ROWS = 2 and a wave four K steps side by side
+// (lane (sub, h, kb, r)), which gives four times the workgroups and a quarter of the steps each (linear 93 x 5003 x 4224:
+// 14.9 -> 12.8 us, of which this kernel had been 6.6; an 8B block at 300 rows 180 -> 175 us).  From 2048 rows on eight
+// rows fill the chip, with longer stores.
+constexpr int kRowWaves = 16, kResidentSteps = 8, kFewRows = 512;
 
+template <int ROWS>
 __global__ __launch_bounds__(kRowWaves* kWave) void quantize_prepare_rows_pk_kernel(const __half* __restrict__ x, int M, int K,
                                                                                    float* __restrict__ a_scale,
                                                                                    int8_t* __restrict__ xp,
                                                                                    int32_t* __restrict__ c0,
                                                                                    int32_t* __restrict__ counters,
                                                                                    int ncounters) {
-    __shared__ float red[kRowWaves][kRowsPerWg];
+    __shared__ float red[kRowWaves][ROWS];
     if (blockIdx.x == 0)  // the tiled kernel's arrival counters start at zero
         for (int i = threadIdx.x; i < ncounters; i += kRowWaves * kWave) counters[i] = 0;
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-    const int r = lane & 7, kb = (lane >> 3) & 3, h = lane >> 5;
-    const int mt = blockIdx.x >> 1, half = blockIdx.x & 1;
-    const int m = 16 * mt + 8 * half + r;
+    constexpr int kLanes = 8 * ROWS, kSide = kWave / kLanes;  // lanes per K step; K steps side by side in a wave
+    constexpr int kResident = kResidentSteps / kSide;
+    const int r = lane % ROWS, kb = (lane / ROWS) & 3, h = (lane / (4 * ROWS)) & 1, sub = lane / kLanes;
+    const int mt = blockIdx.x / (16 / ROWS), row16 = (blockIdx.x % (16 / ROWS)) * ROWS + r;
+    const int m = 16 * mt + row16;
+    const int first = wave * kSide + sub, stride = kRowWaves * kSide;  // the lane's K steps
     const int steps = K >> 7;
     const uint4* src = reinterpret_cast<const uint4*>(x + (size_t)min(m, M - 1) * K + h * 64 + kb * 16);  // + 16 uint4 per step
-    uint4 v[kResidentSteps][2];
+    uint4 v[kResident][2];
     float amax = 0.0f;
 #pragma unroll
-    for (int j = 0; j < kResidentSteps; ++j) {
-        const int st = wave + j * kRowWaves;
+    for (int j = 0; j < kResident; ++j) {
+        const int st = first + j * stride;
         v[j][0] = v[j][1] = make_uint4(0u, 0u, 0u, 0u);
-        if (st < steps) {  // (uniform over the wave)
+        if (st < steps) {
             v[j][0] = src[st * 16];
             v[j][1] = src[st * 16 + 1];
         }
     }
 #pragma unroll
-    for (int j = 0; j < kResidentSteps; ++j) amax = fmaxf(amax, fmaxf(absmax8(v[j][0]), absmax8(v[j][1])));
-    for (int st = wave + kResidentSteps * kRowWaves; st < steps; st += kRowWaves)
+    for (int j = 0; j < kResident; ++j) amax = fmaxf(amax, fmaxf(absmax8(v[j][0]), absmax8(v[j][1])));
+    for (int st = first + kResident * stride; st < steps; st += stride)
         amax = fmaxf(amax, fmaxf(absmax8(src[st * 16]), absmax8(src[st * 16 + 1])));
-    // the row's maximum: over the lanes (h, kb) of the row, then over the waves
-    amax = fmaxf(amax, __shfl_xor(amax, 8, kWave));
-    amax = fmaxf(amax, __shfl_xor(amax, 16, kWave));
-    amax = fmaxf(amax, __shfl_xor(amax, 32, kWave));
-    if (lane < kRowsPerWg) red[wave][lane] = amax;
+    // the row's maximum: over the lanes of the row, then over the waves
+#pragma unroll
+    for (int d = ROWS; d < kWave; d *= 2) amax = fmaxf(amax, __shfl_xor(amax, d, kWave));
+    if (lane < ROWS) red[wave][lane] = amax;
     __syncthreads();
     amax = red[0][r];
 #pragma unroll
     for (int w = 1; w < kRowWaves; ++w) amax = fmaxf(amax, red[w][r]);
     const float s = amax / 127.0f;  // Appendix A.1, n = 8
-    if (threadIdx.x < kRowsPerWg && m < M) a_scale[m] = s;
+    if (threadIdx.x < ROWS && m < M) a_scale[m] = s;
     auto emit = [&](int st, uint4 lo8, uint4 hi8) {
         const uint2 lo = quantize8(lo8, s), hi = quantize8(hi8, s);  // the canonical 16 codes
         const uint4 codes = m < M ? make_uint4(lo.x, lo.y, hi.x, hi.y) : make_uint4(0u, 0u, 0u, 0u);
         const size_t blk = (size_t)mt * steps + st;
-        reinterpret_cast<uint4*>(xp + blk * 2048)[h * 64 + kb * 16 + 8 * half + r] = codes;
+        reinterpret_cast<uint4*>(xp + blk * 2048)[h * 64 + kb * 16 + row16] = codes;
         int sum = sum16(codes);
-        sum += __shfl_xor(sum, 8, kWave);
-        sum += __shfl_xor(sum, 16, kWave);
-        sum += __shfl_xor(sum, 32, kWave);
-        if (lane < kRowsPerWg) c0[blk * 16 + 8 * half + lane] = -8 * sum;
+#pragma unroll
+        for (int d = ROWS; d < kLanes; d *= 2) sum += __shfl_xor(sum, d, kWave);
+        if (lane % kLanes < ROWS) c0[blk * 16 + row16] = -8 * sum;
     };
 #pragma unroll
-    for (int j = 0; j < kResidentSteps; ++j) {
-        const int st = wave + j * kRowWaves;
-        if (st < steps) emit(st, v[j][0], v[j][1]);  // (uniform over the wave)
+    for (int j = 0; j < kResident; ++j) {
+        const int st = first + j * stride;
+        if (st < steps) emit(st, v[j][0], v[j][1]);  // (uniform over the lanes of a K step)
     }
-    for (int st = wave + kResidentSteps * kRowWaves; st < steps; st += kRowWaves) emit(st, src[st * 16], src[st * 16 + 1]);
+    for (int st = first + kResident * stride; st < steps; st += stride) emit(st, src[st * 16], src[st * 16 + 1]);
 }
 
 typedef float v4f_t __attribute__((ext_vector_type(4)));
@@ -874,8 +880,12 @@ hipError_t launch_gemm_tile_pk(const PkArgs& a, bool int_scale, void* workspace,
     if (prepared) {
         // nothing to prepare
     } else if (a.x_fp16) {  // fp16 activations: quantised on the way, the token scales go to a.a_scale_out (= a.a_scale)
-        hipLaunchKernelGGL(quantize_prepare_rows_pk_kernel, dim3(2 * mtiles), dim3(kRowWaves * kWave), 0, stream, a.x_fp16,
-                           a.M, a.K, a.a_scale_out, xp, c0, sp.counters, sp.rem);
+        if (a.M <= kFewRows)
+            hipLaunchKernelGGL(quantize_prepare_rows_pk_kernel<2>, dim3(8 * mtiles), dim3(kRowWaves * kWave), 0, stream, a.x_fp16,
+                               a.M, a.K, a.a_scale_out, xp, c0, sp.counters, sp.rem);
+        else
+            hipLaunchKernelGGL(quantize_prepare_rows_pk_kernel<8>, dim3(2 * mtiles), dim3(kRowWaves * kWave), 0, stream, a.x_fp16,
+                               a.M, a.K, a.a_scale_out, xp, c0, sp.counters, sp.rem);
     } else {
         hipLaunchKernelGGL(prepare_activations_pk_kernel, blocks, dim3(256), 0, stream, a.xq, a.M, a.K, xp, c0,
                            sp.counters, sp.rem);
