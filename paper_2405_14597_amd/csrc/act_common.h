@@ -23,15 +23,20 @@ __device__ __forceinline__ float wave_max(float v) {
 
 // Largest magnitude of eight fp16 values, 0 if none of them is a number.  Taken in fp16, two values an instruction (the maximum
 // of fp16 values is one of them, so nothing is rounded; a NaN loses against a number, as in fmaxf): 12 instructions where
-// converting first takes 18.
+// converting first takes 18.  Magnitudes are taken as max(x, -x), not by clearing the sign: that also turns a signalling NaN into
+// a quiet one.  Met by a number, a signalling NaN comes out as a quiet one in the number's place, and the number is lost.
 __device__ __forceinline__ float absmax8(uint4 v) {
+    auto magnitude = [](uint32_t a) {
+        uint32_t r;
+        asm("v_pk_max_f16 %0, %1, %1 neg_lo:[0,1] neg_hi:[0,1]" : "=v"(r) : "v"(a));
+        return r;
+    };
     auto larger = [](uint32_t a, uint32_t b) {
         uint32_t r;
         asm("v_pk_max_f16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
         return r;
     };
-    constexpr uint32_t kAbs = 0x7FFF7FFFu;
-    const uint32_t m = larger(larger(v.x & kAbs, v.y & kAbs), larger(v.z & kAbs, v.w & kAbs));
+    const uint32_t m = larger(larger(magnitude(v.x), magnitude(v.y)), larger(magnitude(v.z), magnitude(v.w)));
     const float2 f = __half22float2(*reinterpret_cast<const __half2*>(&m));
     return fmaxf(fmaxf(f.x, f.y), 0.0f);  // (callers compare bit patterns: a NaN would be the largest)
 }

@@ -1,4 +1,5 @@
-"""Values that are no numbers in the quantisers' inputs: what the definition of Appendix A.1 gives for the numbers beside them."""
+"""Values that are no numbers (NaN of both kinds) in the quantisers' inputs: what the definition of Appendix A.1 gives for the
+numbers beside them."""
 import numpy as np
 import pytest
 
@@ -8,7 +9,7 @@ from test_gpu_parity import dev, host
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
-QUIET = 0x7E00
+QUIET, SIGNALLING = 0x7E00, 0x7C01
 
 
 @pytest.fixture(scope="module")
@@ -48,3 +49,25 @@ def test_weight_groups_with_sixteen_bytes_of_nan(P, bits, group, alpha):
     codes_ref = O.unpack_int4(ref[0]) if bits == 4 else ref[0]
     assert np.array_equal(codes[~hole], codes_ref[~hole])
     assert (codes[hole] == (-8 if bits == 4 else -128)).all()
+
+
+@pytest.mark.parametrize("K", [64, 4096, 40960])
+def test_signalling_nan_beside_the_largest_value(P, K):
+    """A signalling NaN takes no part in the row's maximum, and no neighbour with it: in every place of an 8-value chunk, next to
+    the row's largest value in every other place."""
+    rng = np.random.default_rng(K)
+    places = [(i, j) for i in range(8) for j in range(8) if i != j]
+    x = rng.uniform(-1.0, 1.0, size=(len(places), K)).astype(np.float16)
+    hole = np.zeros(x.shape, bool)
+    for m, (i, j) in enumerate(places):
+        chunk = 8 * int(rng.integers(0, K // 8))
+        x[m, chunk + i] = 100.0
+        hole[m, chunk + j] = True
+    xq_ref, sa_ref = O.quantize_act_int8_token(np.where(hole, np.float16(0), x))
+    xq, sa = P.is_quantize_act_int8_token(dev(with_nan(x, hole, SIGNALLING)))
+    assert np.array_equal(host(sa), sa_ref)
+    assert np.array_equal(host(xq)[~hole], xq_ref[~hole]) and (host(xq)[hole] == -128).all()
+    w = with_nan(x[:, :64], hole[:, :64], SIGNALLING)
+    ref = O.quantize_weights_int4_group(np.where(hole[:, :64], np.float16(0), x[:, :64]), 32, 10, O.SCALE_NORM)
+    got = P.is_quantize_weights_int4_group(dev(w), 32, 10, P.IS_SCALE_NORM)
+    assert np.array_equal(host(got.scale_f32), ref.scale_f32)
