@@ -21,10 +21,11 @@ __device__ __forceinline__ float wave_max(float v) {
     return __uint_as_float(max(max(r0, r1), max(r2, r3)));
 }
 
-// Largest magnitude of eight fp16 values, 0 if none of them is a number.  Taken in fp16, two values an instruction (the maximum
-// of fp16 values is one of them, so nothing is rounded; a NaN loses against a number, as in fmaxf): 12 instructions where
-// converting first takes 18.  Magnitudes are taken as max(x, -x), not by clearing the sign: that also turns a signalling NaN into
-// a quiet one.  Met by a number, a signalling NaN comes out as a quiet one in the number's place, and the number is lost.
+// Largest magnitude of eight fp16 values, NaN if none of them is a number.  Taken in fp16, two values an instruction (the maximum
+// of fp16 values is one of them, so nothing is rounded; a NaN loses against a number, as in fmaxf): 12 instructions with the
+// caller's running maximum, where converting first takes 18.  Magnitudes are taken as max(x, -x), not by clearing the sign: that
+// also turns a signalling NaN into a quiet one.  Met by a number, a signalling NaN comes out as a quiet one in the number's
+// place, and the number is lost.
 __device__ __forceinline__ float absmax8(uint4 v) {
     auto magnitude = [](uint32_t a) {
         uint32_t r;
@@ -38,7 +39,7 @@ __device__ __forceinline__ float absmax8(uint4 v) {
     };
     const uint32_t m = larger(larger(magnitude(v.x), magnitude(v.y)), larger(magnitude(v.z), magnitude(v.w)));
     const float2 f = __half22float2(*reinterpret_cast<const __half2*>(&m));
-    return fmaxf(fmaxf(f.x, f.y), 0.0f);  // (callers compare bit patterns: a NaN would be the largest)
+    return fmaxf(f.x, f.y);
 }
 
 // e^t and SiLU(g) * u as fixed sequences of separately rounded single-precision operations (no contraction into
@@ -120,12 +121,13 @@ __device__ __forceinline__ uint32_t low_bytes(uint32_t a, uint32_t b, uint32_t c
 }
 
 // N values' codes + OFFSET in the low bytes of c[] (a value that is no number gives byte 0, the lowest code, as the clamp of a
-// NaN does)
+// NaN does; in a row or group whose numbers are all zero every code is 0, a NaN's too)
 template <int OFFSET, int N>
 __device__ __forceinline__ void offset_codes(const float (&x)[N], float s, uint32_t (&c)[N]) {
-    const float r = s > 0.0f ? 1.0f / s : 0.0f;  // a row of zeros: codes 0
+    const float r = s > 0.0f ? 1.0f / s : 0.0f;
     const float r_lo = r * (1.0f - 0x1p-21f), r_hi = r * (1.0f + 0x1p-21f);
-    uint32_t apart = 0;
+    constexpr uint32_t kNoScale = 0x80000000u;  // (two numbers' codes do not differ in this bit, nor do two NaN)
+    uint32_t apart = s > 0.0f ? 0u : kNoScale;
 #pragma unroll
     for (int i = 0; i < N; ++i) {
         c[i] = __float_as_uint(fmaf(x[i], r_lo, kCodeMagic + OFFSET));
@@ -133,10 +135,14 @@ __device__ __forceinline__ void offset_codes(const float (&x)[N], float s, uint3
         // apart |= c[i] ^ other, in one instruction (written out in C it becomes a flag per value and the flags are packed)
         asm("v_bitop3_b32 %0, %1, %2, %0 bitop3:0xbe" : "+v"(apart) : "v"(c[i]), "v"(other));
     }
-    if (__any(apart != 0)) {
-        const float by = s > 0.0f ? s : 1.0f;
+    if (__builtin_expect(__any(apart != 0), 0)) {
+        if (__any((apart & ~kNoScale) != 0)) {
+            const float by = s > 0.0f ? s : 1.0f;
 #pragma unroll
-        for (int i = 0; i < N; ++i) c[i] = __float_as_uint(rintf(x[i] / by) + (kCodeMagic + OFFSET));
+            for (int i = 0; i < N; ++i) c[i] = __float_as_uint(rintf(x[i] / by) + (kCodeMagic + OFFSET));
+        }
+#pragma unroll
+        for (int i = 0; i < N; ++i) c[i] = s > 0.0f ? c[i] : __float_as_uint(kCodeMagic + OFFSET);  // (a NaN times 0 is no 0)
     }
 }
 

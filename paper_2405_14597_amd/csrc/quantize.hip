@@ -94,7 +94,7 @@ constexpr int kWqThreads = 256, kWqInFlight = 4;
 constexpr int kWqMaxGroups = 2048;  // group scales a workgroup keeps in LDS
 
 template <int LPG>
-__device__ __forceinline__ float group_max(float v) {  // values >= 0; over aligned sets of LPG lanes
+__device__ __forceinline__ float group_max(float v) {  // values >= 0 (no NaN: its bit pattern is the largest); over aligned sets of LPG lanes
     unsigned x = __float_as_uint(v);
     if constexpr (LPG >= 2) x = max(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xF, 0xF, true));
     if constexpr (LPG >= 4) x = max(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xF, 0xF, true));
@@ -127,7 +127,7 @@ __global__ __launch_bounds__(kWqThreads) void quantize_weight_rows_kernel(const 
         for (int i = 0; i < kWqInFlight; ++i) {
             if (c0 + i * kWqThreads >= chunks) break;  // uniform
             const int c = c0 + i * kWqThreads + (int)threadIdx.x;
-            const float s = group_max<LPG>(absmax8(v[i])) / kHi;
+            const float s = group_max<LPG>(fmaxf(absmax8(v[i]), 0.0f)) / kHi;
             const __half2* h = reinterpret_cast<const __half2*>(&v[i]);
             float x[8];
 #pragma unroll

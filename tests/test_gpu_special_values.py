@@ -1,10 +1,10 @@
-"""Values that are no numbers (NaN of both kinds) in the quantisers' inputs: what the definition of Appendix A.1 gives for the
-numbers beside them."""
+"""Values that are no numbers (NaN of both kinds) in the quantisers' inputs: what the definition of Appendix A.1 gives for them and
+for the numbers beside them, on every kernel that quantises."""
 import numpy as np
 import pytest
 
 from oracle import oracle as O
-from test_gpu_parity import dev, host
+from test_gpu_parity import dev, host, rand_quantised
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -71,3 +71,53 @@ def test_signalling_nan_beside_the_largest_value(P, K):
     ref = O.quantize_weights_int4_group(np.where(hole[:, :64], np.float16(0), x[:, :64]), 32, 10, O.SCALE_NORM)
     got = P.is_quantize_weights_int4_group(dev(w), 32, 10, P.IS_SCALE_NORM)
     assert np.array_equal(host(got.scale_f32), ref.scale_f32)
+
+
+@pytest.mark.parametrize("M", [5, 300])
+@pytest.mark.parametrize("K", [64, 4096, 16384, 40960])
+def test_rows_of_zeros_and_nan(P, M, K):
+    """A row whose numbers are all zero has scale 0, and then every code is 0, a NaN's too (stand-alone quantiser and both
+    producers, rows that stay in registers and longer ones)."""
+    x = np.random.default_rng(K).standard_normal((M, K)).astype(np.float16)
+    x[2] = 0
+    hole = np.zeros(x.shape, bool)
+    hole[2, [0, 9, K - 1]] = True
+    x = with_nan(x, hole)
+    xq, sa = P.is_quantize_act_int8_token(dev(x))
+    assert host(sa)[2] == 0 and not host(xq)[2].any() and host(sa)[3] > 0 and host(xq)[3].any()
+    gu = np.concatenate([np.where(hole, np.float16(0), x), np.ones_like(x)], axis=1)
+    gu[:, K:][hole] = np.nan                                            # SiLU(0) * NaN beside SiLU(0) * 1
+    xq, sa = P.is_silu_mul_quantize_act_int8_token(dev(gu))
+    assert host(sa)[2] == 0 and not host(xq)[2].any() and host(xq)[3].any()
+    xq, sa = P.is_rmsnorm_quantize_act_int8_token(dev(x), dev(np.ones(K, np.float16)), 1e-5)   # NaN in every place of the row
+    assert host(sa)[2] == 0 and not host(xq)[2].any() and host(xq)[3].any()
+
+
+@pytest.mark.parametrize("M", [1, 5, 70, 600])
+@pytest.mark.parametrize("K", [1024, 4096])
+def test_linear_calls_on_rows_of_zeros_and_nan(P, M, K):
+    """The same inside the linear calls: the accumulators of such a row are 0."""
+    N = 272
+    _, qw, IS, _, _, c = rand_quantised(np.random.default_rng(M + K), 1, N, K)
+    x = np.random.default_rng(M).standard_normal((M, K)).astype(np.float16)
+    x[M // 2] = 0
+    hole = np.zeros(x.shape, bool)
+    hole[M // 2, [0, 77, K - 1]] = True
+    x = dev(with_nan(x, hole))
+    _, acc = P.is_linear_w4a8_intscale_prepacked(x, P.is_prepack_w4(dev(qw), dev(IS), 128), dev(c), 10, want_acc=True)
+    assert not host(acc)[M // 2].any()
+    _, acc = P.is_linear_w4a8_intscale(x, dev(qw), dev(IS), dev(c), 128, 10, want_acc=True)
+    assert not host(acc)[M // 2].any()
+
+
+@pytest.mark.parametrize("bits", [4, 8])
+def test_weight_groups_of_zeros_and_nan(P, bits):
+    w = np.random.default_rng(3).standard_normal((3, 1024)).astype(np.float16)
+    w[1, 256:384] = 0
+    hole = np.zeros(w.shape, bool)
+    hole[1, [256, 300]] = True
+    quantise = P.is_quantize_weights_int4_group if bits == 4 else P.is_quantize_weights_int8_group
+    for alpha in (10, -1):
+        got = quantise(dev(with_nan(w, hole)), 128, alpha, P.IS_SCALE_NORM)
+        codes = O.unpack_int4(host(got.qweight)) if bits == 4 else host(got.qweight)
+        assert host(got.scale_f32)[1, 2] == 0 and not codes[1, 256:384].any()
