@@ -47,10 +47,15 @@ __device__ __forceinline__ float absmax8(uint4 v) {
 // Shorter forms stand in where they give the same bits.  n = rint(t log2 e) is read off the sum with 2^23 + 2^22, whose low
 // bits are also the exponent that 2^n adds to p (|n| <= 127 and p lies in [0.7, 1.5], so the result stays normal);
 // n * ln2_hi is exact, so subtracting it in a fused multiply-add rounds once all the same.
+// The definition clamps t at 88, this at 87: above it SiLU is about -1e-36 either way (its product with any finite fp16 value is
+// a zero of the same sign), and 1 + e^t stays below 2^126, where the reciprocal that silu_mul takes is a normal number.  A
+// smaller one is flushed to 0, and 0 times an infinite up value is no infinity.
+constexpr float kExpMax = 87.0f;
+
 __device__ __forceinline__ float exp_steps(float t) {
 #pragma clang fp contract(off)
     constexpr float kRound = 12582912.0f;
-    t = fminf(fmaxf(t, -87.0f), 88.0f);
+    t = fminf(fmaxf(t, -87.0f), kExpMax);
     const float shifted = fmaf(t, 1.4426950408889634f, kRound);
     const float n = shifted - kRound;
     const float r = fmaf(-n, 0.693145751953125f, t) - n * 1.428606765330187e-06f;
@@ -74,8 +79,8 @@ __device__ __forceinline__ float rounded_f32(float v) {
 
 // g holds an fp16 value, so SiLU(g) takes one of 2^16 values, and the short form of the division below (reciprocal, one
 // correction of the quotient, the fix-up for infinities and NaN) has been compared with the true division on every one of
-// them: the same bits wherever the quotient is above 1e-30, and the same sign below that, where the product with any fp16
-// value rounds to a zero of fp16.  6 instructions where the general division takes 11; with the shorter e^t above 32 instead of
+// them: the same bits wherever the quotient is above 1e-30, and the same sign below that, where it is no zero and its product with
+// a finite fp16 value rounds to one.  6 instructions where the general division takes 11; with the shorter e^t above 32 instead of
 // 41 per element, SiLU * up and quantiser at 2048 x 28672: 85 -> 64 us (4.6 TB/s; with the
 // row spread over 1024 lanes, see the launcher).
 __device__ __forceinline__ float silu_mul(float g, float u) {

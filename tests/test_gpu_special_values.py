@@ -1,5 +1,5 @@
-"""Values that are no numbers (NaN of both kinds) in the quantisers' inputs: what the definition of Appendix A.1 gives for them and
-for the numbers beside them, on every kernel that quantises."""
+"""Values that are no finite numbers (NaN of both kinds, infinities) in the quantisers' and SiLU * up's inputs: what the definitions
+of Appendix A.1 and of SiLU give for the numbers beside them, on every kernel that quantises."""
 import numpy as np
 import pytest
 
@@ -121,3 +121,18 @@ def test_weight_groups_of_zeros_and_nan(P, bits):
         got = quantise(dev(with_nan(w, hole)), 128, alpha, P.IS_SCALE_NORM)
         codes = O.unpack_int4(host(got.qweight)) if bits == 4 else host(got.qweight)
         assert host(got.scale_f32)[1, 2] == 0 and not codes[1, 256:384].any()
+
+
+@pytest.mark.parametrize("up", [np.inf, -np.inf, 65504.0, -65504.0, 0.0, np.nan])
+def test_silu_mul_on_every_gate_pattern(P, up):
+    """All 65536 gates, infinities and NaN among them, against up values at the ends of the type: infinite products are infinite
+    (also where SiLU is far below the smallest fp16 value), products that are no numbers leave a row of zeros."""
+    g = np.arange(65536, dtype=np.uint16).view(np.float16)
+    gu = np.concatenate([np.repeat(g[:, None], 8, axis=1), np.full((g.size, 8), up, np.float16)], axis=1)
+    with np.errstate(invalid="ignore", over="ignore"):
+        h = O.silu_mul_fp16(gu)[:, 0].astype(np.float32)
+    amax = np.where(np.isnan(h), np.float32(0), np.abs(h))
+    xq, sa = P.is_silu_mul_quantize_act_int8_token(dev(gu))
+    assert np.array_equal(host(sa), amax / np.float32(127.0))
+    code = np.where(amax == 0, 0, np.where(np.isinf(h), -128, np.sign(np.nan_to_num(h)) * 127)).astype(np.int8)
+    assert np.array_equal(host(xq), np.repeat(code[:, None], 8, axis=1))
