@@ -293,6 +293,16 @@ hipError_t launch_quantize_act(const __half* x, int M, int K, int8_t* xq, float*
     return hipGetLastError();
 }
 
+// Both forms' times in microseconds, fits to 1019 calls (1 to 3000 rows, K 1024 to 262144, groups 32 to 512; the wrong choice costs
+// an eighth at most).  A workgroup that walks a whole row takes 1.8 us for every 8192 of its values, which many rows share and
+// few do not; the kernels in steps pay for two launches, by the group and by the value.  16 x 65536, groups of 128: 15.3 us in
+// whole rows, 9.3 us in steps; 96 x 65536: 15.7 and 17.5 us.
+static bool whole_rows_are_faster(int N, int K, int NG) {
+    const double rows = 2.4 + 1.8 * ((K + 8191) / 8192);
+    const double steps = 4.6 + 1.8e-4 * N * (double)NG + 4e-7 * N * (double)K + 5.1e-3 * NG + 1.3e-5 * K;
+    return rows < steps;
+}
+
 hipError_t launch_quantize_weights(const __half* w, int N, int K, int group, int alpha_log2, int scale_mode,
                                    uint8_t* qweight, float* scale_f32, int32_t* scale_i32, float* chan_scale,
                                    int* alpha_log2_dev, hipStream_t stream, int bits) {
@@ -300,7 +310,8 @@ hipError_t launch_quantize_weights(const __half* w, int N, int K, int group, int
     const int lpg = group >> 3;
     // (a search needs the largest amplifier of all rows first; rows of more scales than fit LDS, and groups that are not 8
     // times a power of two up to 64 values, have lanes to spare in the kernels below)
-    if (alpha_log2 >= 0 && NG <= kWqMaxGroups && (group & 7) == 0 && lpg >= 4 && lpg <= 64 && (lpg & (lpg - 1)) == 0) {
+    if (alpha_log2 >= 0 && NG <= kWqMaxGroups && (group & 7) == 0 && lpg >= 4 && lpg <= 64 && (lpg & (lpg - 1)) == 0 &&
+        whole_rows_are_faster(N, K, NG)) {
         // whole rows of up to one round of loads in flight; at least one
         const int chunks = K >> 3;
         const int rows = std::max(1, std::min(kWqThreads * kWqInFlight / chunks, kWqMaxGroups / NG));
