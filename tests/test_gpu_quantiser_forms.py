@@ -67,11 +67,11 @@ def test_silu_mul_on_every_gate_value(P):
 
 @pytest.mark.parametrize("N,K,group", [(3, 128, 128), (130, 1024, 128), (5, 33792, 128), (9, 4096, 32), (70, 192, 64), (17, 2048, 256),
                                        (6, 3584, 512), (2, 131072, 64), (2, 1 << 18, 64), (11, 960, 24), (5, 1024, 1024),
-                                       (100, 33792, 128), (96, 20480, 32)])
+                                       (100, 33792, 128), (96, 20480, 32), (5001, 128, 64), (2100, 384, 128)])
 @pytest.mark.parametrize("bits", [4, 8])
 def test_weight_codes_and_scales(P, N, K, group, bits):
-    """One pass over whole rows (the last two: several rounds of loads a row), and the shapes it leaves to the kernels in steps (few
-    long rows, rows of more scales than LDS holds, groups that are no power of two, groups beyond 512)."""
+    """One pass over whole rows (the last four: several rounds of loads a row, several rows a workgroup), and the shapes it leaves to
+    the kernels in steps (few long rows, rows of more scales than LDS holds, groups that are no power of two, groups beyond 512)."""
     rng = np.random.default_rng(N + K + group)
     w = (rng.standard_normal((N, K)) * 0.02).astype(np.float16)
     w[0, :group] = 0                                                 # a group of zeros
