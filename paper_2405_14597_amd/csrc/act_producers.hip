@@ -247,12 +247,14 @@ hipError_t launch_rmsnorm_quantize_act(const __half* x, const __half* gamma, flo
         else RMS_LAUNCH(4, kWideThreads);
         return hipGetLastError();
     }
-    // Two chunks a lane: the row and gamma then take few enough registers for eight waves per SIMD (a lane with eight chunks
-    // left room for four).  2048 x 8192: 20.3 us at 8 chunks and 256 lanes, 15.1 us at 2 and 512; 4096 x 4096, where the
-    // lanes stay as they were, 17.5 -> 14.8 us from the order of the loads and the shorter sums.
+    // Up to 1024 chunks two a lane: the row and gamma then take few enough registers for eight waves per SIMD (a lane with eight
+    // chunks leaves room for four).  2048 x 8192: 20.3 us at 8 chunks and 256 lanes, 15.1 us at 2 and 512; 4096 x 4096, where the
+    // lanes stay as they were, 17.5 -> 14.8 us from the order of the loads and the shorter sums.  Beyond that two a lane would
+    // mean 1024 lanes, two workgroups per unit whose barriers nothing else covers: 4096 x 8704 35.0 us, 4096 x 16384 42.5 us,
+    // against 25.3 and 36.3 us at 8 and 256.
     if (nchunk <= 2 * 256) RMS_LAUNCH(2, 256);
     else if (nchunk <= 2 * 512) RMS_LAUNCH(2, 512);
-    else if (nchunk <= 2 * 1024) RMS_LAUNCH(2, 1024);
+    else if (nchunk <= 8 * 256) RMS_LAUNCH(8, 256);
     else if (nchunk <= 4 * 1024) RMS_LAUNCH(4, 1024);
     else
         hipLaunchKernelGGL(rmsnorm_quantize_kernel, grid, dim3(kActThreads), 0, stream, x, gamma, eps, M, K, xq, a_scale);

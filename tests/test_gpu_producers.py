@@ -33,11 +33,12 @@ def _gamma(K, seed):
     return (1.0 + 0.25 * np.random.default_rng(seed).standard_normal(K)).astype(np.float16)
 
 
-# few rows (1024 lanes per row, 1 / 2 / 4 chunks per lane), many rows (256 lanes, 2 / 8 / 16 chunks), the three-pass
-# kernel (K = 40000), one chunk, ragged last chunk slots
+# few rows (1024 lanes per row, 1 / 2 / 4 chunks per lane), many rows (2 or 8 chunks on 256 lanes, 2 on 512, 4 on 1024, and the
+# rows at which one takes over from the other), the three-pass kernel (K = 40000), one chunk, ragged last chunk slots
 @pytest.mark.parametrize("M,K,eps", [(1, 4096, 1e-5), (7, 4096, 1e-6), (33, 5120, 1e-5), (5, 8192, 1e-5),
                                      (3, 14336, 1e-5), (2, 28672, 1e-6), (2, 40000, 1e-5), (64, 128, 1e-5),
-                                     (3, 8, 1e-5), (130, 11008, 1e-2), (260, 11008, 1e-5), (257, 28672, 1e-5), (300, 2048, 1e-5)])
+                                     (3, 8, 1e-5), (130, 11008, 1e-2), (260, 11008, 1e-5), (257, 28672, 1e-5), (300, 2048, 1e-5),
+                                     (257, 4104, 1e-5), (258, 8192, 1e-5), (259, 8200, 1e-5), (257, 16384, 1e-5), (257, 16392, 1e-5)])
 def test_rmsnorm_quantize_bit_exact(P, M, K, eps):
     x = S.activations_outlier(M, K, 100 + K % 97).astype(np.float16)
     if M > 2:
