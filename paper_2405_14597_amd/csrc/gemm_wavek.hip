@@ -413,28 +413,28 @@ WavekPlan wavek_plan(int M, int N) {
     return p;
 }
 
-// Both kernels' times from what bounds them, in microseconds; the constants are fits to 33 calls (65 to 2048 rows, 4096 to
-// 28672 columns, K 4096 and 14336; each within a fifth, and the wrong choice on one of them, by 3 %).
+// Both kernels' times from what bounds them, in microseconds; the constants are fits, checked on 1482 calls with int4 weights (65 to
+// 8192 rows, 200 to 65536 columns, K 128 to 28672, integer and float scales), on which the wrong choice of this kernel costs 6 %
+// at most.
 // This kernel: 10 us of launches, preparation, start and end, and 0.76 us per K step of a wave on every SIMD (for 12 KB of
 // operands; 10 KB with 48 rows).  The tiled kernel: 6 us, 2.3 us per K step for a round of two tiles per unit (1.56 when a
-// unit has one), and 14 us more to pass the partial tiles of a cut K range through memory.
+// unit has one, 1.31 of a long K range: 1024 x 8192 x 28672 286 us there, 313 us here), and 14 us more to pass the partial tiles
+// of a cut K range through memory.  With one full round of the tiled kernel or more there are sixteen rounds of tiles here, and
+// their starts and ends, which these times leave out, add up (540 x 53283 x 1536 97 us there, 108 us here; 4096 x 4608 x 2304 73
+// and 79 us; the best of such calls here is 3 % ahead).
 bool wavek_is_faster(int M, int N, int K, bool w8) {
     const int steps = K >> 7, cus = cu_count();
     const WavekPlan p = wavek_plan(M, N);
     const double here = 10.0 + 0.76 * 0.25 * (double)((p.tiles + cus - 1) / cus) * steps * (2 * p.ms + (w8 ? 8 : 4)) / 12.0;
+    const long long tiles = (long long)((N + 255) / 256) * ((M + 127) / 128);
     if (w8) {  // the W8A8 tiled kernel: one tile per unit at a time, 1.05 us per K step, 14 us of launches and scale transposition
-        const long long rounds = ((long long)((N + 255) / 256) * ((M + 127) / 128) + cus - 1) / cus;
+        const long long rounds = (tiles + cus - 1) / cus;
         return here < 14.0 + 1.05 * steps * (double)rounds;
     }
-    const long long tiles = (long long)((N + 255) / 256) * ((M + 127) / 128);
-    const int left = (int)(tiles % (2 * cus));
-    double tiled = 6.0 + 2.3 * steps * (double)(tiles / (2 * cus));
-    if (left > cus) tiled += 2.3 * steps;
-    else if (left > 0) {
-        const int parts = std::min(std::min(cus / left, 8), std::max(steps / 8, 1));
-        tiled += 1.56 * steps / parts + (parts > 1 ? 14.0 : 0.0);
-    }
-    return here < tiled;
+    if (tiles >= 2 * cus) return false;
+    if (tiles > cus) return here < 6.0 + 2.3 * steps;
+    const int parts = std::min(std::min(cus / (int)tiles, 8), std::max(steps / 8, 1));
+    return here < 6.0 + (parts > 1 ? 1.56 * steps / parts + 14.0 : std::min(1.56 * steps, 25.0 + 1.31 * steps));
 }
 
 void wavek_kernel_name(const WavekPlan& p, bool int_scale, bool w8, bool silu, char* buf, size_t len) {
