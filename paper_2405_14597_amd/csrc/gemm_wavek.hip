@@ -422,15 +422,20 @@ WavekPlan wavek_plan(int M, int N) {
 // of a cut K range through memory.  With one full round of the tiled kernel or more there are sixteen rounds of tiles here, and
 // their starts and ends, which these times leave out, add up (540 x 53283 x 1536 97 us there, 108 us here; 4096 x 4608 x 2304 73
 // and 79 us; the best of such calls here is 3 % ahead).
+// With int8 weights: 16 KB of operands (14 KB) here; the tiled kernel of that recipe works on one tile per unit at a time, 1.03 us
+// per K step, behind 9.5 us of launches and scale transposition.  There the ends decide short K ranges, 2 us a round here and
+// 10 us a tile there: 4096 x 4096 x 128 38 us here and 30 us there, 1109 x 719 x 384 11 and 20 us.  Checked on 864 calls: the
+// wrong choice costs 8 % at most, the choice without the ends up to 54 %.
 bool wavek_is_faster(int M, int N, int K, bool w8) {
     const int steps = K >> 7, cus = cu_count();
     const WavekPlan p = wavek_plan(M, N);
-    const double here = 10.0 + 0.76 * 0.25 * (double)((p.tiles + cus - 1) / cus) * steps * (2 * p.ms + (w8 ? 8 : 4)) / 12.0;
-    const long long tiles = (long long)((N + 255) / 256) * ((M + 127) / 128);
-    if (w8) {  // the W8A8 tiled kernel: one tile per unit at a time, 1.05 us per K step, 14 us of launches and scale transposition
-        const long long rounds = (tiles + cus - 1) / cus;
-        return here < 14.0 + 1.05 * steps * (double)rounds;
+    const long long tiles = (long long)((N + 255) / 256) * ((M + 127) / 128), here_rounds = (p.tiles + cus - 1) / cus;
+    if (w8) {
+        const double filled = std::max(1.0, 0.5 * ((double)here_rounds + (double)p.tiles / cus));
+        const double here = 8.0 + filled * (2.0 + 0.72 * 0.25 * steps * (2 * p.ms + 8) / 12.0);
+        return here < 9.5 + (double)((tiles + cus - 1) / cus) * (10.0 + 1.03 * steps);
     }
+    const double here = 10.0 + 0.76 * 0.25 * (double)here_rounds * steps * (2 * p.ms + 4) / 12.0;
     if (tiles >= 2 * cus) return false;
     if (tiles > cus) return here < 6.0 + 2.3 * steps;
     const int parts = std::min(std::min(cus / (int)tiles, 8), std::max(steps / 8, 1));

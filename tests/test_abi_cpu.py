@@ -304,6 +304,20 @@ def test_which_kernel_prepacked_calls_of_moderate_rows_take(M, N, K, wavek):
         assert P.is_describe_prepacked(M, N, K, 128, int_scale)[1].startswith("gemm_wavek_kernel<" if wavek else "gemm_tile_pk_kernel<")
 
 
+# the same for int8 weights (short K ranges, whose tiles' starts and ends decide), told by the workspace: the kernel whose waves
+# split K wants room for the activations' blocks
+@pytest.mark.parametrize("M,N,K,wavek", [(2048, 4096, 128, False), (4096, 4096, 128, False), (1579, 9442, 128, False),
+                                         (3870, 1813, 384, False), (1885, 5931, 256, False), (300, 4096, 14336, True),
+                                         (1024, 4096, 14336, True), (300, 4096, 4096, True), (2048, 300, 128, True)])
+def test_which_kernel_w8a8_calls_of_moderate_rows_take(M, N, K, wavek):
+    before = P.is_set_kernel_route("tiled")
+    tiled = P.is_gemm_w8a8_workspace_bytes(M, N, K, 128)
+    P.is_set_kernel_route("auto")
+    got = P.is_gemm_w8a8_workspace_bytes(M, N, K, 128)
+    P.is_set_kernel_route(before)
+    assert got > tiled if wavek else got == tiled
+
+
 def test_kernel_route_override_is_a_host_setting():
     """The routing override of the tests is a call, not an environment read on the launch path: it returns the setting
     in force before, rejects unknown routes and leaves the setting alone when it does."""
