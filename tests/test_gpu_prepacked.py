@@ -208,14 +208,32 @@ def test_prepacked_linear_token_scale_and_zero_token(P):
     assert not host(acc).any() and not host(out).any()
 
 
+@pytest.fixture(params=["tiled kernel", "library's choice"])
+def route(P, request):
+    """More than 64 token rows: on the tiled kernel whatever the shape, and on the kernel the library picks (for most of the
+    shapes here the one whose waves split K).  Returns a check of the kernel that a shape's calls run."""
+    tiled = request.param == "tiled kernel"
+    before = P.is_set_kernel_route("tiled64" if tiled else "auto")
+
+    def check(M, N, K, group=G, fp16_in=False):
+        if tiled:
+            for int_scale in (True, False):
+                name = P.is_describe_prepacked(M, N, K, group, int_scale, fp16_in)[-1]
+                assert name == f"gemm_tile_pk_kernel<{str(int_scale).lower()}>"
+    yield check
+    P.is_set_kernel_route(before)
+
+
 # more than 64 token rows: the tiled kernel on the prepacked layout (ragged row and column tiles, one and many K steps,
-# N not a multiple of 8: element-wise epilogue; several tiles per XCD)
+# N not a multiple of 8: element-wise epilogue; several tiles per XCD; the last two: K cut into two and three parts, ragged
+# on both sides)
 TILE_PK_SHAPES = [(65, 256, 128), (129, 300, 1024), (256, 512, 2048), (300, 700, 1152), (513, 257, 512), (128, 256, 4096),
-                  (1000, 1040, 256), (70, 16, 384)]
+                  (1000, 1040, 256), (70, 16, 384), (333, 1028, 2304), (201, 776, 3200)]
 
 
 @pytest.mark.parametrize("M,N,K", TILE_PK_SHAPES)
-def test_prepacked_tiled_gemm(P, M, N, K):
+def test_prepacked_tiled_gemm(P, route, M, N, K):
+    route(M, N, K)
     rng = np.random.default_rng(3500 + M + N + K)
     xq, qw, IS, s, sa, c = rand_quantised(rng, M, N, K)
     xq[0], xq[1] = -128, 127                 # extreme codes on both sides
@@ -275,10 +293,10 @@ def test_prepacked_33_to_64_rows_on_the_tiled_kernel(P, tiled64, M, N, K):
 
 
 @pytest.mark.parametrize("M,K", [(130, 1024), (2048, 2048), (65, 128), (300, 4096)])
-def test_prepacked_gemms_on_shared_prepared_activations(P, M, K):
+def test_prepacked_gemms_on_shared_prepared_activations(P, route, M, K):
     """One preparation of the activations, then GEMMs with several weight sets of different widths on the prepared
-    workspace (last rounds with and without a K split, so the arrival counters are used and left zero in turn): the
-    accumulators and outputs of the ordinary prepacked call, bit for bit, and the oracle's accumulators."""
+    workspace (on the tiled kernel last rounds with and without a K split, so the arrival counters are used and left zero in
+    turn): the accumulators and outputs of the ordinary prepacked call, bit for bit, and the oracle's accumulators."""
     rng = np.random.default_rng(4100 + M + K)
     widths = [520, 16, 4104, 256, 520]
     xq = rng.integers(-128, 128, size=(M, K)).astype(np.int8)
@@ -287,6 +305,7 @@ def test_prepacked_gemms_on_shared_prepared_activations(P, M, K):
     ws.random_(0, 256)
     P.is_prepare_activations_prepacked(dev(xq), ws)
     for i, N in enumerate(widths):
+        route(M, N, K)
         _, qw, IS, s, _, c = rand_quantised(np.random.default_rng(4200 + N + i), 1, N, K)
         pk = P.is_prepack_w4(dev(qw), dev(IS), G)
         out, acc = P.is_gemm_w4a8_intscale_prepacked_prepared(dev(sa), pk, dev(c), 10, ws, want_acc=i % 2 == 0)
@@ -345,9 +364,10 @@ def test_prepacked_33_to_64_rows_on_large_weights_take_the_tiled_kernel(P, M, N,
 
 @pytest.mark.parametrize("M,N,K,group", [(200, 300, 1024, 128), (129, 520, 2048, 256), (130, 80, 1536, 1536),
                                          (129, 300, 6144, 384)])
-def test_prepacked_tiled_wide_scales_and_groups(P, M, N, K, group):
+def test_prepacked_tiled_wide_scales_and_groups(P, route, M, N, K, group):
     """Scales beyond 24 bits (the 32-bit multiply instance, bit-exact modulo 2^32), groups of several K steps (the last:
-    K parts of the last round's tiles that begin inside a group)."""
+    on the tiled kernel K parts of the last round's tiles that begin inside a group)."""
+    route(M, N, K, group)
     rng = np.random.default_rng(77 + M)
     xq = rng.integers(-128, 128, size=(M, K)).astype(np.int8)
     q = rng.integers(-8, 8, size=(N, K)).astype(np.int8)
@@ -363,10 +383,11 @@ def test_prepacked_tiled_wide_scales_and_groups(P, M, N, K, group):
         check_out(host(out), ref.out)
 
 
-def test_prepacked_tiled_workspace_contents_do_not_matter(P):
-    """The tiled route writes what it reads of its workspace (its preparation kernel also clears the arrival counters
-    of the K split of the last round): a workspace full of ones, used twice, gives the same bits."""
+def test_prepacked_tiled_workspace_contents_do_not_matter(P, route):
+    """The route for more than 64 rows writes what it reads of its workspace (the preparation kernel also clears the tiled
+    kernel's arrival counters of the K split of the last round): a workspace full of ones, used twice, gives the same bits."""
     M, N, K = 300, 520, 4096
+    route(M, N, K)
     assert P.is_gemm_prepacked_workspace_bytes(M, N, K, G) > (M + 15) // 16 * 16 * K + 2 ** 20   # partial tiles in it
     rng = np.random.default_rng(4100)
     xq, qw, IS, s, sa, c = rand_quantised(rng, M, N, K)
@@ -380,16 +401,18 @@ def test_prepacked_tiled_workspace_contents_do_not_matter(P):
     pkf = P.is_prepack_w4(dev(qw), dev(s), G)
     a = P.is_gemm_w4a8_floatscale_prepacked(dev(xq), dev(sa), pkf, workspace=ws)
     b = P.is_gemm_w4a8_floatscale_prepacked(dev(xq), dev(sa), pkf, workspace=ws)
-    assert torch.equal(a, b)          # float partial sums are added in part order, whoever arrives last
+    assert torch.equal(a, b)          # float partial sums are added in part (or wave) order, whoever arrives last
     check_fs(host(a), O.gemm_w4a8_floatscale(xq, sa, qw, s, G))
 
 
 @pytest.mark.parametrize("M,N,K", [(130, 512, 4096), (70, 272, 8192), (200, 256, 14336), (66, 128, 28672), (257, 40, 2048),
-                                   (70, 48, 40960), (72, 32, 256), (89, 16, 128), (300, 48, 1152)])
-def test_prepacked_tiled_linear_fp16(P, M, N, K):
-    """More than 64 fp16 tokens: the tiled kernel's preparation quantises on the way (a workgroup per 8 token rows: row
-    maxima, then the rounding into the kernel layout; rows longer than the registers hold are read twice).  Fewer K
-    steps than waves, 8-row halves past M, an all-zero row."""
+                                   (70, 48, 40960), (72, 32, 256), (89, 16, 128), (300, 48, 1152), (512, 24, 640),
+                                   (513, 40, 1152), (603, 56, 20480), (617, 16, 128)])
+def test_prepacked_tiled_linear_fp16(P, route, M, N, K):
+    """More than 64 fp16 tokens: the preparation of both kernels quantises on the way (a workgroup per 2 token rows, from 513
+    rows on per 8: row maxima, then the rounding into the kernel layout; rows longer than the registers hold are read twice).
+    Fewer K steps than waves or than they hold side by side, 8-row halves past M, an all-zero row."""
+    route(M, N, K, fp16_in=True)
     rng = np.random.default_rng(7600 + M + N + K)
     _, qw, IS, s, _, c = rand_quantised(rng, 1, N, K)
     x = S.activations_student_t(M, K, 78 + K % 13)
