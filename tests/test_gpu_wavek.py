@@ -1,6 +1,7 @@
-"""GPU parity of the kernel whose waves split K (prepacked calls of a moderate number of token rows) against the CPU oracle:
-row tiles of 48 and 64 rows with remainders, fewer K steps than waves, workgroups of four and eight waves, ragged widths,
-wide groups, wide scales, the float-scale twin, the SiLU * up epilogue, prepared activations and captured calls."""
+"""GPU parity of the kernel whose waves split K (prepacked and W8A8 calls of a moderate number of token rows) against the CPU
+oracle: row tiles of 48 and 64 rows with remainders, fewer K steps than waves, workgroups of four and eight waves, ragged
+widths, wide groups, wide scales, the float-scale twin, prepared activations and captured calls.  (Its SiLU * up epilogue is in
+test_gpu_gate_up.py.)"""
 import numpy as np
 import pytest
 
@@ -79,19 +80,85 @@ def test_wavek_w8(P, M, N, K, group):
     IS = rng.integers(-2 ** 22, 2 ** 22, size=(N, K // group)).astype(np.int32)
     wide = IS.copy()
     wide[N // 2, -1] = 2 ** 23  # one scale beyond 24 signed bits
+    nbytes = P.is_gemm_w8a8_workspace_bytes(M, N, K, group)
+    blocks = torch.zeros((max(nbytes, P.is_gemm_prepacked_workspace_bytes(M, N, K, group)),), dtype=torch.uint8, device="cuda:0")
+    P.is_prepare_activations_prepacked(dev(xq), blocks)
+    blocks = blocks[:(M + 15) // 16 * 16 * K]   # what only the kernel whose waves split K leaves in the workspace
     before = P.is_set_kernel_route("tiled")
     tiled_bytes = P.is_gemm_w8a8_workspace_bytes(M, N, K, group)
     P.is_set_kernel_route(before)
-    assert P.is_gemm_w8a8_workspace_bytes(M, N, K, group) >= tiled_bytes
+    assert nbytes >= tiled_bytes
     for scales in (IS, wide):
         ref = O.gemm_w8a8_intscale(xq, sa, q, scales, None, group, 12)
         outs = []
-        for nbytes in (tiled_bytes, max(tiled_bytes, P.is_gemm_w8a8_workspace_bytes(M, N, K, group))):  # tiled kernel, this one
-            ws = torch.full((nbytes,), 0x5A, dtype=torch.uint8, device="cuda:0")
+        for route, ws_bytes in (("auto", nbytes), ("tiled", tiled_bytes)):
+            P.is_set_kernel_route(route)
+            ws = torch.full((ws_bytes,), 0x5A, dtype=torch.uint8, device="cuda:0")
             out, acc = P.is_gemm_w8a8_intscale(dev(xq), dev(sa), dev(q), dev(scales), None, group, 12, want_acc=True, workspace=ws)
+            P.is_set_kernel_route(before)
+            assert (ws.numel() >= blocks.numel() and torch.equal(ws[:blocks.numel()], blocks)) == (route == "auto")
             assert np.array_equal(host(acc), ref.acc), "int32 accumulators differ"
             outs.append(out)
         assert torch.equal(outs[0], outs[1])
     s = (rng.random((N, K // group)) * 1e-4).astype(np.float32)
     fs = O.gemm_w8a8_floatscale(xq, sa, q, s, group)
     check_fs(host(P.is_gemm_w8a8_floatscale(dev(xq), dev(sa), dev(q), dev(s), group)), fs, f"M{M} N{N} K{K}")
+
+
+def test_w8_workspace_of_the_tiled_kernel_is_enough(P):
+    """A workspace of the size that the tiled kernel alone needs keeps the call there, with the same integer results."""
+    M, N, K, group = 97, 33, 1152, 128
+    rng = np.random.default_rng(6900)
+    xq = rng.integers(-128, 128, size=(M, K)).astype(np.int8)
+    q = rng.integers(-128, 128, size=(N, K)).astype(np.int8)
+    sa = (rng.random(M) + 0.01).astype(np.float32)
+    IS = rng.integers(-2 ** 22, 2 ** 22, size=(N, K // group)).astype(np.int32)
+    before = P.is_set_kernel_route("tiled")
+    tiled_bytes = P.is_gemm_w8a8_workspace_bytes(M, N, K, group)
+    P.is_set_kernel_route(before)
+    assert P.is_gemm_w8a8_workspace_bytes(M, N, K, group) > tiled_bytes
+    ws = torch.full((tiled_bytes,), 0x5A, dtype=torch.uint8, device="cuda:0")
+    small, acc = P.is_gemm_w8a8_intscale(dev(xq), dev(sa), dev(q), dev(IS), None, group, 12, want_acc=True, workspace=ws)
+    full, _ = P.is_gemm_w8a8_intscale(dev(xq), dev(sa), dev(q), dev(IS), None, group, 12)
+    assert torch.equal(small, full)
+    assert np.array_equal(host(acc), O.gemm_w8a8_intscale(xq, sa, q, IS, None, group, 12).acc)
+
+
+def test_captured_calls(P):
+    """A linear call on fp16 rows, a GEMM on codes and a W8A8 GEMM on this kernel in one graph, replayed with new inputs in the
+    same buffers and with the program's own work between the replays: the results of the ordinary calls each time."""
+    M, N, K = 130, 328, 1152
+    assert P.is_describe_prepacked(M, N, K, 128)[-1].startswith("gemm_wavek_kernel<true, ")
+    rng = np.random.default_rng(7100)
+    _, qw, IS, _, sa, c = rand_quantised(rng, M, N, K)
+    pk = P.is_prepack_w4(dev(qw), dev(IS), 128)
+    q8, IS8 = dev(rng.integers(-128, 128, size=(N, K)).astype(np.int8)), dev(rng.integers(0, 1025, size=(N, K // 128)).astype(np.int32))
+    c, sa = dev(c), dev(sa)
+    x, xq = torch.zeros((M, K), dtype=torch.float16, device="cuda:0"), torch.zeros((M, K), dtype=torch.int8, device="cuda:0")
+    outs = [torch.zeros((M, N), dtype=torch.float16, device="cuda:0") for _ in range(3)]
+    ws = [torch.zeros((n,), dtype=torch.uint8, device="cuda:0") for n in (P.is_linear_prepacked_workspace_bytes(M, N, K, 128),
+          P.is_gemm_prepacked_workspace_bytes(M, N, K, 128), P.is_gemm_w8a8_workspace_bytes(M, N, K, 128))]
+
+    def calls(outs, ws):
+        P.is_linear_w4a8_intscale_prepacked(x, pk, c, 10, out=outs[0], workspace=ws[0])
+        P.is_gemm_w4a8_intscale_prepacked(xq, sa, pk, c, 10, out=outs[1], workspace=ws[1])
+        P.is_gemm_w8a8_intscale(xq, sa, q8, IS8, c, 128, 10, out=outs[2], workspace=ws[2])
+
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        calls(outs, ws)
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        calls(outs, ws)
+    for i in range(4):
+        x.copy_(torch.randn((M, K), device="cuda:0").half())
+        xq.copy_(torch.randint(-128, 128, (M, K), dtype=torch.int8, device="cuda:0"))
+        graph.replay()
+        torch.cuda.synchronize()
+        want = [torch.empty_like(o) for o in outs]
+        calls(want, [torch.full_like(w, 0x5A) for w in ws])
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(outs, want)), f"replay {i}"
