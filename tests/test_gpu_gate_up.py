@@ -107,6 +107,29 @@ def test_gate_up_silu_33_to_64_rows_on_the_tiled_kernel(P, M, inter, K, wide):
         P.is_set_kernel_route(before)
 
 
+# (the last: K cut into two parts)
+@pytest.mark.parametrize("M,inter,K,wide", [(65, 48, 1024, False), (130, 272, 512, True), (300, 144, 256, False),
+                                             (256, 1040, 1024, False), (129, 272, 2304, True)])
+def test_gate_up_silu_more_than_64_rows_on_the_tiled_kernel(P, M, inter, K, wide):
+    """The route of large calls at small sizes: the tiled kernel's 128-row instance with the fused epilogue."""
+    before = P.is_set_kernel_route("tiled64")
+    try:
+        assert P.is_describe_prepacked(M, 2 * inter, K, G)[-1] == "gemm_tile_pk_kernel<true>"
+        test_gate_up_silu_intscale(P, M, inter, K, wide)
+        test_gate_up_silu_floatscale(P, M, inter, K)
+    finally:
+        P.is_set_kernel_route(before)
+
+
+# the fused epilogue of the kernel whose waves split K: row tiles of 48 and 64 rows, workgroups of four and eight waves
+@pytest.mark.parametrize("M,inter,K,wide,shape", [(65, 48, 1024, True, "3, 8"), (128, 48, 1024, False, "4, 8"),
+                                                   (65, 4160, 640, False, "3, 4"), (250, 2064, 768, True, "4, 4")])
+def test_gate_up_silu_on_the_kernel_whose_waves_split_k(P, M, inter, K, wide, shape):
+    assert P.is_describe_prepacked(M, 2 * inter, K, G)[-1] == f"gemm_wavek_kernel<true, false, {shape}, false>"
+    test_gate_up_silu_intscale(P, M, inter, K, wide)
+    test_gate_up_silu_floatscale(P, M, inter, K)
+
+
 @pytest.mark.parametrize("M,inter,K", [(8, 48, 256), (200, 272, 1024)])
 def test_gate_up_silu_floatscale(P, M, inter, K):
     rng = np.random.default_rng(9100 + M + inter)
