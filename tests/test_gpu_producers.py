@@ -84,10 +84,11 @@ def test_rmsnorm_quantize_empty_and_bad_arguments(P):
             P.is_rmsnorm_quantize_act_int8_token(x1, g, eps)
 
 
-# few rows (1024 lanes per row), many rows (256 lanes, 2 / 8 / 16 chunks per lane), the two-pass kernel
-# (inter = 40960), one chunk, a ragged tail
+# few rows (1024 lanes per row), many rows (2 or 4 chunks on 256 lanes, 4 on 512 and on 1024, and the rows at which one takes over
+# from the other), the two-pass kernel (inter = 40960), one chunk, a ragged tail
 @pytest.mark.parametrize("M,inter", [(1, 11008), (8, 11008), (33, 14336), (3, 28672), (2, 40960), (64, 136),
-                                     (5, 8), (130, 4096), (260, 11008), (257, 28672), (300, 2048)])
+                                     (5, 8), (130, 4096), (260, 11008), (257, 28672), (300, 2048), (257, 4104), (258, 8192), (259, 8200),
+                                     (257, 16384), (257, 16392)])
 def test_silu_mul_quantize_bit_exact(P, M, inter):
     rng = np.random.default_rng(200 + inter % 89)
     gate = (3.0 * rng.standard_normal((M, inter))).astype(np.float16)
