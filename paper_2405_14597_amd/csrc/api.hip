@@ -756,14 +756,13 @@ int is_describe_prepacked(int M, int N, int K, int group, int int_scale, int fp1
     const int shape = check_pk_shape(N, K, group);
     if (shape != IS_OK) return shape;
     if (pk_takes_tile(M, N, K) && takes_wavek(M, N, K)) {
-        const bool quantises = fp16_in != 0 && gemm_tile_pk_takes_fp16(K);
         char name[64];
         wavek_kernel_name(wavek_plan(M, N), int_scale != 0, false, false, name, sizeof name);
-        snprintf(names, names_len, "%s\n%s", quantises ? "quantize_prepare_rows_pk_kernel" : "prepare_activations_pk_kernel", name);
+        snprintf(names, names_len, "%s\n%s", prepare_pk_kernel_name(M, fp16_in != 0 && gemm_tile_pk_takes_fp16(K)), name);
         return IS_OK;
     }
     if (pk_takes_tile(M, N, K)) {
-        gemm_tile_pk_kernel_names(K, int_scale != 0, fp16_in != 0 && M > 64 && gemm_tile_pk_takes_fp16(K), names, names_len);
+        gemm_tile_pk_kernel_names(M, int_scale != 0, fp16_in != 0 && M > 64 && gemm_tile_pk_takes_fp16(K), names, names_len);
         return IS_OK;
     }
     PkPlan plan;

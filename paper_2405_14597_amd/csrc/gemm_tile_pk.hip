@@ -266,12 +266,9 @@ __global__ __launch_bounds__(256) void prepare_activations_grouped_pk_kernel(con
 constexpr int kRowWaves = 16, kResidentSteps = 8, kFewRows = 512;
 
 template <int ROWS>
-__global__ __launch_bounds__(kRowWaves* kWave) void quantize_prepare_rows_pk_kernel(const __half* __restrict__ x, int M, int K,
-                                                                                   float* __restrict__ a_scale,
-                                                                                   int8_t* __restrict__ xp,
-                                                                                   int32_t* __restrict__ c0,
-                                                                                   int32_t* __restrict__ counters,
-                                                                                   int ncounters) {
+__device__ __forceinline__ void quantize_prepare_rows(const __half* __restrict__ x, int M, int K, float* __restrict__ a_scale,
+                                                      int8_t* __restrict__ xp, int32_t* __restrict__ c0,
+                                                      int32_t* __restrict__ counters, int ncounters) {
     __shared__ float red[kRowWaves][ROWS];
     if (blockIdx.x == 0)  // the tiled kernel's arrival counters start at zero
         for (int i = threadIdx.x; i < ncounters; i += kRowWaves * kWave) counters[i] = 0;
@@ -325,6 +322,24 @@ __global__ __launch_bounds__(kRowWaves* kWave) void quantize_prepare_rows_pk_ker
         if (st < steps) emit(st, v[j][0], v[j][1]);  // (uniform over the lanes of a K step)
     }
     for (int st = first + kResident * stride; st < steps; st += stride) emit(st, src[st * 16], src[st * 16 + 1]);
+}
+
+__global__ __launch_bounds__(kRowWaves* kWave) void quantize_prepare_rows_pk_kernel(const __half* __restrict__ x, int M, int K,
+                                                                                   float* __restrict__ a_scale,
+                                                                                   int8_t* __restrict__ xp,
+                                                                                   int32_t* __restrict__ c0,
+                                                                                   int32_t* __restrict__ counters,
+                                                                                   int ncounters) {
+    quantize_prepare_rows<8>(x, M, K, a_scale, xp, c0, counters, ncounters);
+}
+
+__global__ __launch_bounds__(kRowWaves* kWave) void quantize_prepare_few_rows_pk_kernel(const __half* __restrict__ x, int M, int K,
+                                                                                       float* __restrict__ a_scale,
+                                                                                       int8_t* __restrict__ xp,
+                                                                                       int32_t* __restrict__ c0,
+                                                                                       int32_t* __restrict__ counters,
+                                                                                       int ncounters) {
+    quantize_prepare_rows<2>(x, M, K, a_scale, xp, c0, counters, ncounters);
 }
 
 typedef float v4f_t __attribute__((ext_vector_type(4)));
@@ -840,11 +855,12 @@ size_t gemm_tile_pk_workspace_bytes(int M, int N, int K) {
 
 bool gemm_tile_pk_takes_fp16(int K) { return (K & 127) == 0; }
 
-void gemm_tile_pk_kernel_names(int K, bool int_scale, bool fp16_in, char* buf, size_t len, bool silu) {
-    char prep[96];
-    if (fp16_in) snprintf(prep, sizeof prep, "quantize_prepare_rows_pk_kernel");
-    else snprintf(prep, sizeof prep, "prepare_activations_pk_kernel");
-    snprintf(buf, len, "%s\ngemm_tile%s_pk_kernel<%s>", prep, silu ? "_silu" : "", int_scale ? "true" : "false");
+const char* prepare_pk_kernel_name(int M, bool fp16_in) {
+    return !fp16_in ? "prepare_activations_pk_kernel" : M <= kFewRows ? "quantize_prepare_few_rows_pk_kernel" : "quantize_prepare_rows_pk_kernel";
+}
+
+void gemm_tile_pk_kernel_names(int M, bool int_scale, bool fp16_in, char* buf, size_t len, bool silu) {
+    snprintf(buf, len, "%s\ngemm_tile%s_pk_kernel<%s>", prepare_pk_kernel_name(M, fp16_in), silu ? "_silu" : "", int_scale ? "true" : "false");
 }
 
 // The preparation of quantised activations on its own (for activations that several GEMMs share): fills the fixed part
@@ -881,10 +897,10 @@ hipError_t launch_gemm_tile_pk(const PkArgs& a, bool int_scale, void* workspace,
         // nothing to prepare
     } else if (a.x_fp16) {  // fp16 activations: quantised on the way, the token scales go to a.a_scale_out (= a.a_scale)
         if (a.M <= kFewRows)
-            hipLaunchKernelGGL(quantize_prepare_rows_pk_kernel<2>, dim3(8 * mtiles), dim3(kRowWaves * kWave), 0, stream, a.x_fp16,
+            hipLaunchKernelGGL(quantize_prepare_few_rows_pk_kernel, dim3(8 * mtiles), dim3(kRowWaves * kWave), 0, stream, a.x_fp16,
                                a.M, a.K, a.a_scale_out, xp, c0, sp.counters, sp.rem);
         else
-            hipLaunchKernelGGL(quantize_prepare_rows_pk_kernel<8>, dim3(2 * mtiles), dim3(kRowWaves * kWave), 0, stream, a.x_fp16,
+            hipLaunchKernelGGL(quantize_prepare_rows_pk_kernel, dim3(2 * mtiles), dim3(kRowWaves * kWave), 0, stream, a.x_fp16,
                                a.M, a.K, a.a_scale_out, xp, c0, sp.counters, sp.rem);
     } else {
         hipLaunchKernelGGL(prepare_activations_pk_kernel, blocks, dim3(256), 0, stream, a.xq, a.M, a.K, xp, c0,

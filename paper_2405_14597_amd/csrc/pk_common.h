@@ -92,7 +92,8 @@ size_t gemm_tile_grouped_pk_workspace_bytes(int E, int M, int N, int K);
 hipError_t launch_gemm_tile_grouped_pk(const PkArgs& a, const int32_t* row_offsets, int E, size_t wstride,
                                        size_t sstride, bool int_scale, void* workspace, hipStream_t stream);
 // The kernels launch_gemm_tile_pk runs, in order, as a kernel trace names them, separated by '\n'.
-void gemm_tile_pk_kernel_names(int K, bool int_scale, bool fp16_in, char* buf, size_t len, bool silu = false);
+void gemm_tile_pk_kernel_names(int M, bool int_scale, bool fp16_in, char* buf, size_t len, bool silu = false);
+const char* prepare_pk_kernel_name(int M, bool fp16_in);  // its first one
 void gemm_tile_grouped_pk_kernel_names(int E, int M, bool int_scale, char* buf, size_t len);
 
 }  // namespace intscale

@@ -294,6 +294,19 @@ def test_describe_prepacked_names_the_kernels():
     assert lib.is_describe_grouped_prepacked(2, 16, 256, 128, 64, 1, buf, 8) == P.IS_ERR_UNSUPPORTED
 
 
+def test_described_kernels_are_the_sources_kernels():
+    """A described name is the one a kernel trace shows: template arguments where the kernel is a template, none where it is not."""
+    import re
+    from paper_2405_14597_amd import build
+    text = "".join(open(p).read() for p in build.sources())
+    found = {m[2]: m[1] is not None for m in re.finditer(r"(template <[^>]*>\s*)?__global__[^;{]*?\bvoid\s+(\w+)\(", text)}
+    names = [n for M in (1, 17, 40, 65, 300, 512, 513, 4096) for N, K in ((4096, 4096), (8192, 28672), (28672, 4096))
+             for fp16_in in (False, True) for n in P.is_describe_prepacked(M, N, K, 128, True, fp16_in)]
+    names += P.is_describe_grouped_prepacked(8, 1024, 14336, 4096, 128, True)
+    for name in names:
+        assert found[name.split("<")[0]] == ("<" in name), name
+
+
 # measured: the tiled kernel is 5 to 15 % ahead on the first five (every unit has one tile and a long K range, or more than a full
 # round of tiles), the kernel whose waves split K 1.2 to 2.8 times on the others
 @pytest.mark.parametrize("M,N,K,wavek", [(1024, 8192, 28672, False), (2048, 4096, 20480, False), (512, 16384, 14336, False),
