@@ -178,16 +178,19 @@ int is_prepack_w4(const void* qweight, const int32_t* scale_i32, const float* sc
  * is_gemm_w4a8_floatscale (accumulators bit for bit; the float-scale sums in a different but fixed order).
  *   qweight_packed, scales_packed   from is_prepack_w4 (integer scales for the first, float scales for the second)
  *   workspace   at least is_gemm_prepacked_workspace_bytes(M,N,K,group) bytes.
- *               (Which kernel: the tiled one for M > 64, and for 33 <= M <= 64 when N * K >= 2^27; else the
- *               weight-streaming one.  Ask is_gemm_prepacked_workspace_bytes / is_describe_prepacked, do not guess.)
+ *               (Which kernel: for M > 64 the one whose waves split K where a fitted time says that it is faster,
+ *               roughly up to a few hundred rows, else the tiled one, which 33 <= M <= 64 takes too when N * K >= 2^27;
+ *               else the weight-streaming one.  Ask is_gemm_prepacked_workspace_bytes / is_describe_prepacked, do not
+ *               guess.)
  *               M <= 64 (the weight-streaming kernel): 0 for most shapes; when it is not 0 the K dimension is split
  *               across workgroups and the first 64 KB of the workspace are arrival counters: they must be ZERO when a
  *               call starts and every call leaves them zero, so zero the workspace once after allocating it.
- *               M > 64 (the MFMA-bound tiled kernel): the activations re-ordered into MFMA operand blocks
- *               (ceil(M/16) * 16 * K bytes) and one zero-point correction per token row and K step, written by a
- *               preparation kernel of the call; when the last round of output tiles would leave most of the chip idle,
- *               also partial tiles (up to 64 MB) of a K split of that round, reduced exactly in int32 (the float-scale
- *               form adds its float partial sums in a fixed order).  No requirement on the contents.
+ *               M > 64: the activations re-ordered into MFMA operand blocks (ceil(M/16) * 16 * K bytes) and one
+ *               zero-point correction per token row and K step, written by a preparation kernel of the call; when the
+ *               last round of the tiled kernel's output tiles would leave most of the chip idle, also partial tiles (up
+ *               to 64 MB) of a K split of that round, reduced exactly in int32 (the float-scale form adds its float
+ *               partial sums in a fixed order).  The size is the same whichever kernel the call takes (the one whose
+ *               waves split K reads the operand blocks alone).  No requirement on the contents.
  *               Calls sharing one workspace must not overlap.
  * Covered: M >= 1, N up to 16 * 256 * (compute units) rows when M <= 64, ceil(M/16) * 16 * K below 2^31 beyond
  * (IS_ERR_UNSUPPORTED otherwise).  M = 0 is a no-op.
@@ -202,16 +205,16 @@ int is_gemm_w4a8_floatscale_prepacked(const int8_t* xq, const float* a_scale, co
                                       void* workspace, size_t workspace_bytes, void* stream);
 
 /*
- * Activations that several GEMMs share (the q / k / v or the gate / up projections of one layer input): the tiled
- * route's preparation of the quantised activations, done once, and the prepacked GEMMs on the prepared workspace,
- * which then launch the tiled kernel alone.  Same arithmetic and results as the calls above (Eq. (2) / Eq. (1)), bit
- * for bit.
+ * Activations that several GEMMs share (the q / k / v or the gate / up projections of one layer input): the
+ * preparation of the quantised activations that calls of more than 64 rows do, done once, and the prepacked GEMMs on the
+ * prepared workspace, which then launch their GEMM kernel alone.  Same arithmetic and results as the calls above (Eq. (2) /
+ * Eq. (1)), bit for bit.
  *   is_prepare_activations_prepacked   xq int8 [M,K] -> the front part of `workspace`, whose size depends on M and K
  *       only (MFMA operand blocks, zero-point corrections, zeroed arrival counters).  M > 32, K a multiple of
  *       128, ceil(M/16) * 16 * K below 2^31 (IS_ERR_UNSUPPORTED otherwise).
  *   is_gemm_w4a8_*_prepacked_prepared  as is_gemm_w4a8_*_prepacked without xq, on a workspace prepared for the same
  *       M and K; any number of calls, with any N and weights, may follow one preparation, one after the other on the
- *       same stream (each leaves the workspace prepared).  Only shapes that take the tiled kernel (M > 64, or
+ *       same stream (each leaves the workspace prepared).  Only shapes whose calls prepare (M > 64, or
  *       33 <= M <= 64 with N * K >= 2^27): IS_ERR_UNSUPPORTED otherwise, use the ordinary call.
  *   workspace   the same buffer for all of them, at least is_gemm_prepacked_workspace_bytes(M, N, K, group) bytes of the
  *       widest N (less is accepted down to the size for N = 1: the last round's K split then uses what there is).
@@ -232,8 +235,8 @@ int is_gemm_w4a8_floatscale_prepacked_prepared(const float* a_scale, const void*
  * call uses a fixed scratch array inside the library (IS_NOALLOC_SCRATCH_BYTES of device memory per GPU, held until
  * the process ends) and allocates nothing, on the device or through any library.
  *   - Shapes whose is_gemm_prepacked_workspace_bytes(M,N,K,group) exceeds IS_NOALLOC_SCRATCH_BYTES return
- *     IS_ERR_WORKSPACE before anything is enqueued (covered: every M <= 64 shape, and tiled shapes up to about
- *     ceil(M/16) * 16 * K = 31 MiB; the tiled route splits its last round only as far as the rest of the scratch allows).
+ *     IS_ERR_WORKSPACE before anything is enqueued (covered: every M <= 64 shape, and larger ones up to about
+ *     ceil(M/16) * 16 * K = 31 MiB; the tiled kernel splits its last round only as far as the rest of the scratch allows).
  *   - All calls on one GPU share that GPU's array: calls that overlap in time on one GPU (two streams, two threads)
  *     race on it; serialise them or give the overlapping ones the workspace form.
  *   - The first call on a device resolves the array's address (hipGetSymbolAddress); make that call outside a graph
@@ -247,8 +250,8 @@ int is_gemm_w4a8_intscale_prepacked_noalloc(const int8_t* xq, const float* a_sca
 /*
  * The linear layer on fp16 activations and prepacked weights: Appendix A.1 per token, then Eq. (2) / Eq. (1), with the
  * results of is_quantize_act_int8_token followed by the prepacked GEMM, to the bit.  One token (M = 1, K <= 32768) is
- * quantised inside the GEMM kernel (one launch); more than 64 tokens are quantised by the tiled kernel's preparation
- * pass; otherwise the quantiser runs first.
+ * quantised inside the GEMM kernel (one launch); more than 64 tokens are quantised by the preparation pass; otherwise
+ * the quantiser runs first.
  *   workspace   at least is_linear_prepacked_workspace_bytes(M,N,K,group) bytes: quantised activations [M,K], token
  *               scales [M] (each padded to 256 bytes), then the GEMM's workspace, whose zero-counter rule applies.
  */
@@ -295,8 +298,8 @@ int is_gemm_w4a8_floatscale_grouped_prepacked(const int8_t* xq, const float* a_s
  *   is_gemm_w4a8_*_gate_up_silu_prepacked: out [M, inter] fp16, out[m, n] = fp16(SiLU(g) * u) with g, u the fp16
  *     results of the integer-scale (float-scale) GEMM of Eq. (2) (Eq. (1)) for gate row n and up row n: the value of
  *     the unfused sequence GEMM -> fp16 tensor -> SiLU * up, bit for bit, without the [M, 2 inter] tensor's trip
- *     through memory when M > 64 (the epilogue of the tiled kernel; for M <= 64 the weight-streaming kernel writes
- *     that tensor into the workspace and a second kernel reads it).  SiLU(g) = g / (1 + e^-g) in single precision,
+ *     through memory when M > 64 (the epilogue of either kernel that takes such calls; for M <= 64 the weight-streaming
+ *     kernel writes that tensor into the workspace and a second kernel reads it).  SiLU(g) = g / (1 + e^-g) in single precision,
  *     e^-g by the operation sequence stated in the oracle.  acc_out (may be NULL): [M, 2 inter] int32 accumulators
  *     in the packed row order.  workspace >= is_gemm_gate_up_silu_prepacked_workspace_bytes(M, inter, K, group),
  *     zero-filled once (same rules as the prepacked GEMM's).
@@ -351,7 +354,10 @@ size_t is_gemm_grouped_workspace_bytes(int num_experts, int M_total, int N, int 
  * is_quantize_weights_int8_group takes the arguments and requirements of is_quantize_weights_int4_group.
  * The GEMMs compute Eq. (2) resp. Eq. (1) exactly as their W4A8 counterparts (a group's partial sum is at most 2^21
  * in magnitude, so the same integer scale step applies); group and K multiples of 128, any M >= 0, any N >= 1;
- * `workspace` of at least is_gemm_w8a8_workspace_bytes(M,N,K,group) bytes is always needed (transposed scales).
+ * `workspace` of at least is_gemm_w8a8_workspace_bytes(M,N,K,group) bytes is always needed (transposed scales, or, where
+ * more than 64 token rows take the kernel whose waves split K, the activations re-ordered into operand blocks).  Such a
+ * call accepts a workspace of the transposed scales' size as well and then runs the tiled kernel: the same accumulators
+ * and integer-scale results, float-scale sums in that kernel's order.
  */
 int is_quantize_weights_int8_group(const void* w_fp16, int N, int K, int group, int alpha_log2, int scale_mode,
                                    int8_t* qweight8, float* scale_f32, int32_t* scale_i32, float* chan_scale,
@@ -405,13 +411,16 @@ int is_probe_mfma_i8(int iters, int* sink, double* ops_out, void* stream);
 int is_probe_mfma_i8_random(int iters, int* sink, double* ops_out, void* stream);
 
 /*
- * For tests and experiments (not part of the method): which kernel the calls on the canonical layouts take.
+ * For tests and experiments (not part of the method): which kernel the calls take.
  *   0  the library chooses by shape (the default);
  *   1  every call goes to the general kernel where it covers the shape;
- *   2  the W8A8 GEMMs go to the tiled kernel whatever M is;
- *   3  the prepacked calls of 33..64 token rows go to the tiled kernel whatever the size of the weights.
+ *   2  the W8A8 GEMMs go to their tiled kernel whatever M is, and the prepacked calls of more than 64 token rows to
+ *      theirs;
+ *   3  the prepacked calls of more than 32 token rows and the W8A8 GEMMs of more than 64 go to their tiled kernels
+ *      whatever the shape.
  * The setting is process-wide and starts from INTSCALE_FORCE_KERNEL=general|tiled (read once).  Returns the setting
- * that was in force before, or IS_ERR_INVALID_ARG.  Results do not depend on it (every route computes the same bits).
+ * that was in force before, or IS_ERR_INVALID_ARG.  Every route computes the same accumulators, codes and, with integer
+ * scales, the same bits; float-scale results differ in the order of their sums, as the kernels do.
  */
 int is_set_kernel_route(int route);
 

@@ -45,10 +45,10 @@ int check_gemm_shape(int M, int N, int K, int group) {
 }
 
 // Regime selection by the number of token rows.  More than 64 rows (per expert on average, for the grouped form)
-// go to the MFMA-bound tiled kernel, which needs workspace for its zero-point corrections.
+// go to the MFMA-bound tiled kernel, which needs workspace for its zero-point corrections (takes_wavek below has the exceptions).
 // Routing override (tests and experiments): 0 automatic, 1 everything the general kernel covers goes to it, 2 the
 // W8A8 GEMMs go to the tiled kernel whatever M is, 3 the prepacked calls of 33..64 rows go to the tiled kernel (with 2 and 3 the
-// prepacked calls of more rows stay there, too).  Starts from INTSCALE_FORCE_KERNEL=general|tiled, read once;
+// prepacked and the W8A8 calls of more rows stay there, too).  Starts from INTSCALE_FORCE_KERNEL=general|tiled, read once;
 // is_set_kernel_route changes it afterwards.  Nothing on the launch path reads the environment.
 std::atomic<int> g_route{-1};
 int kernel_route() {
@@ -64,7 +64,8 @@ int kernel_route() {
 bool general_forced() { return kernel_route() == 1; }
 bool general_forced_off() { return kernel_route() == 2; }
 
-// Which of the two kernels on the prepacked layout a call takes.  More than 64 token rows: the tiled one.  33..64 rows:
+// Which calls on the prepacked layout prepare their activations, for the tiled kernel or the one whose waves split K (takes_wavek):
+// those of more than 64 token rows.  The others take the weight-streaming kernel.  33..64 rows:
 // the weight-streaming kernel cannot keep a long K slab of 64 rows in LDS, so it splits K many times and moves partial
 // tiles and activation slabs of about the weights' own size; from 2^27 weights on (measured: LLaMA-2-70B gate 50 -> 47 us,
 // down 62 -> 53 us at 64 rows; every smaller shape of the LLaMA-2-7B / LLaMA-3-8B / LLaMA-2-70B layers is slower there)
@@ -115,7 +116,10 @@ int static_scratch(void** ptr_out) {
 
 namespace intscale {
 // The calls of the tiled kernel that the kernel takes whose waves split K (more than 64 rows, where it is faster; routes 2
-// and 3 keep them on the tiled kernel).
+// and 3 keep them on the tiled kernel).  The line at 64 rows is the weight-streaming kernel's, which prepares nothing; at 64
+// rows it takes 11.9 / 17.1 / 19.5 us for 4096 x 4096 / 4096 x 11008 / 4096 x 14336 (N x K) where this kernel with its
+// preparation takes 13.3 / 20.7 / 23.9 us.  For wide matrices the line could lie lower: 12288 x 4096 17.0 against 15.1 us here,
+// 28672 x 4096 26.3 against 22.5, 10240 x 8192 22.7 against 19.0.
 bool takes_wavek(int M, int N, int K, bool w8) {
     return M > 64 && kernel_route() < 2 && (!w8 || (long long)((M + 15) / 16) * 16 * K < (1LL << 31)) && wavek_is_faster(M, N, K, w8);
 }

@@ -261,8 +261,10 @@ __global__ __launch_bounds__(256) void prepare_activations_grouped_pk_kernel(con
 // w, w + 16, ...
 // Few rows make few workgroups of eight: up to kFewRows of them a workgroup takes ROWS = 2 and a wave four K steps side by side
 // (lane (sub, h, kb, r)), which gives four times the workgroups and a quarter of the steps each (linear 93 x 5003 x 4224:
-// 14.9 -> 12.8 us, of which this kernel had been 6.6; an 8B block at 300 rows 180 -> 175 us).  From 2048 rows on eight
-// rows fill the chip, with longer stores.
+// 14.9 -> 12.8 us, of which this kernel had been 6.6; an 8B block at 300 rows 180 -> 175 us).  Up to 512 rows that is one
+// workgroup per compute unit: 512 x 4096 4.8 us against 9.4 us at eight rows, 512 x 14336 11 against 24 us.  Above, two rows
+// stay ahead up to about 1024 (1024 x 4096 7.3 against 10.0 us), and the two forms meet at 2048 (2048 x 2048 9.1 against 7.3 us,
+// x 4096 10.9 against 11.6, x 8192 20.4 against 18.5), where eight rows fill the chip, with longer stores.
 constexpr int kRowWaves = 16, kResidentSteps = 8, kFewRows = 512;
 
 template <int ROWS>

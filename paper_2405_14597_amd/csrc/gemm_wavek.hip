@@ -11,12 +11,17 @@
 //
 // Operands go straight from global memory to the registers of the wave that multiplies them (no two waves of a workgroup
 // read the same bytes, so LDS would only pass them on): weights in the 1 KB blocks of the kernel layout, activations in the
-// 2 KB blocks that the tiled kernel's preparation writes, every load one contiguous kilobyte.  (Row-major activations, which
+// 2 KB blocks that the preparation kernels write, every load one contiguous kilobyte.  (Row-major activations, which
 // need no preparation, cost 71 cycles per load and compute unit in 16 pieces of 64 bytes against about 30: 2048 x 28672 x 4096
 // 519 against 344 us, and no gain at 65 rows.)  Each register is asked for again as soon as its last use has been
-// issued, a K step ahead; two waves per SIMD cover the rest of the latency.  12 KB of operands per 32 MFMAs of a wave leave
-// the kernel bound by the L2 (32 bytes per cycle and compute unit), not by the matrix pipe: large calls stay on the
-// tiled kernel, which shares its operands through LDS (takes_wavek says where the line lies).
+// issued, a K step ahead; two waves per SIMD cover the rest of the latency.  What bounds it, from counters: with int4 weights
+// (300 x 28672 x 4096, 58 us) a wave issues 44 % of its time, waits for an issue slot 37 % and for loads 19 %, so that the two
+// waves of a SIMD leave it little room, and the L2 delivers 35 bytes per cycle and compute unit (12 KB of operands per 32 MFMAs
+// of a wave; tile loads alone sustain 40 to 55): large calls stay on the tiled kernel, which shares its operands through LDS
+// (takes_wavek says where the line lies).  With int8 weights (300 x 4096 x 14336, 48 us) it waits for loads: 46 % of a wave's
+// time, 27 % issuing, 24 bytes per cycle.  There the weight lines are requested by assembly, which the compiler does not
+// count, so that its waits for the activations (7 and 6 outstanding) hold up until the lines just requested have come too: they
+// are less than a K step ahead; and the copy of the scales every fourth step waits for everything.
 //
 // int4 -> int8 with a zero point, as in the tiled kernel: (word ^ 0x08..) & 0x0F.. is q + 8, and the MFMA chain starts from
 // -8 * sum_k x[m,k].  That sum comes from the matrix pipe as well (a multiplication by a constant operand of -8s gives it in every
@@ -25,7 +30,8 @@
 //
 // Measured (GEMM on int8 codes, its preparation included, graph replay), the tiled kernel's time first: 65 x 4096 x 4096
 // 32.9 -> 12.6 us, 300 x 4096 x 4096 36.4 -> 19.5 us, 512 x 6144 x 4096 42.2 -> 28.5 us, 300 x 28672 x 4096 72.9 -> 63.0 us,
-// 128 x 4096 x 14336 46.2 -> 25.0 us; W8A8 300 x 4096 x 14336 126.4 -> 55.9 us, 1024 x 4096 x 14336 129 -> 103 us; W4A8 1024 x 28672 x 4096 147 against 181 us (stays on the tiled kernel).
+// 128 x 4096 x 14336 46.2 -> 25.0 us; W8A8 300 x 4096 x 14336 126.4 -> 55.9 us, 1024 x 4096 x 14336 129 -> 103 us;
+// W4A8 1024 x 28672 x 4096 147 against 181 us (stays on the tiled kernel).
 #include <stdio.h>
 
 #include <algorithm>
