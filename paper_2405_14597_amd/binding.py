@@ -937,7 +937,7 @@ def is_gemm_w4a8_intscale_prepacked_noalloc(xq, a_scale, packed: PackedWeights, 
 
 
 def is_prepare_activations_prepacked(xq, workspace, stream=None):
-    """The tiled route's preparation of quantised activations [M,K] into `workspace` (a uint8 tensor the caller keeps
+    """The preparation of quantised activations [M,K] that calls of more than 64 rows do, into `workspace` (a uint8 tensor the caller keeps
     for the *_prepared GEMMs that follow; size it with is_gemm_prepacked_workspace_bytes of the widest N)."""
     torch = _torch()
     M, K = xq.shape
@@ -950,7 +950,7 @@ def is_prepare_activations_prepacked(xq, workspace, stream=None):
 
 def is_gemm_w4a8_intscale_prepacked_prepared(a_scale, packed: PackedWeights, chan_scale, alpha_log2: int, workspace,
                                              out=None, acc_out=None, want_acc=False, stream=None):
-    """The prepacked integer-scale GEMM on a workspace is_prepare_activations_prepacked has filled (tiled kernel only)."""
+    """The prepacked integer-scale GEMM on a workspace is_prepare_activations_prepacked has filled (its GEMM kernel only)."""
     torch = _torch()
     M = a_scale.shape[0]
     N, K, group = packed.N, packed.K, packed.group

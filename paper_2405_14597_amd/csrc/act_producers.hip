@@ -96,9 +96,9 @@ __device__ __forceinline__ uint4 silu_mul8(uint4 g, uint4 u) {
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// RMSNorm + quantiser.  Rows of up to 2048 * CH elements stay in registers (CH 16-byte chunks per lane): read
-// once, normalised in place, written once as codes.  Few rows (a decode step) take 1024 lanes per row instead of 256:
-// the chip is far from full then, and a row's arithmetic is spread over four times as many lanes.
+// RMSNorm + quantiser.  Rows of up to 8 * CH * THREADS elements stay in registers (CH 16-byte chunks per lane): read
+// once, normalised in place, written once as codes.  Few rows (a decode step) take 1024 lanes per row instead of 256 or 512:
+// the chip is far from full then, and a row's arithmetic is spread over more lanes.
 // ---------------------------------------------------------------------------------------------------------
 template <int CH, int THREADS>
 __global__ __launch_bounds__(THREADS) void rmsnorm_quantize_resident_kernel(const __half* __restrict__ x,

@@ -400,7 +400,7 @@ __device__ __forceinline__ void tile_pk(const PkArgs& a, const int8_t* __restric
     const int mt0 = GROUPED ? entry[1] : tile_m * MS;
     const int m0 = GROUPED ? entry[2] : tile_m * TM;
     const int m_rows = GROUPED ? entry[3] : min(TM, a.M - m0);
-    const int mt_end = mt0 + ((m_rows + 15) >> 4);  // 16-row tiles from here on are not this tile's (they read as zero)
+    const int mt_end = mt0 + ((m_rows + 15) >> 4);  // 16-row tiles from here on are not this tile's (what is read in their place is never stored)
     const uint8_t* wpack = a.wpack + (GROUPED ? (size_t)expert * tg.wstride : 0);
     const uint8_t* spack = a.spack + (GROUPED ? (size_t)expert * tg.sstride : 0);
     const float* chan_scale = a.chan_scale ? a.chan_scale + (GROUPED ? (size_t)expert * a.N : 0) : nullptr;

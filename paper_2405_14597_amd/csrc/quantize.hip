@@ -17,7 +17,7 @@ __device__ __forceinline__ float wave_min(float v) {
     return v;
 }
 
-// Rows of up to 2048 * CH elements: the row is read once and stays in registers (CH 16-byte chunks per lane) between
+// Rows of up to 8 * CH * THREADS elements: the row is read once and stays in registers (CH 16-byte chunks per lane) between
 // the absmax reduction and the rounding, so a token row costs one trip to memory, not two.  With few rows (a decode
 // step) a row is spread over up to 1024 lanes: the chip is far from full and the row's latency is what counts.
 template <int CH, int THREADS>
