@@ -21,25 +21,30 @@ __device__ __forceinline__ float wave_max(float v) {
     return __uint_as_float(max(max(r0, r1), max(r2, r3)));
 }
 
-// Largest magnitude of eight fp16 values, NaN if none of them is a number.  Taken in fp16, two values an instruction (the maximum
-// of fp16 values is one of them, so nothing is rounded; a NaN loses against a number, as in fmaxf): 12 instructions with the
-// caller's running maximum, where converting first takes 18.  Magnitudes are taken as max(x, -x), not by clearing the sign: that
-// also turns a signalling NaN into a quiet one.  Met by a number, a signalling NaN comes out as a quiet one in the number's
-// place, and the number is lost.
+// Largest magnitude of eight fp16 values, 0 if none of them is a number.  Magnitudes order like unsigned integers, so the maxima
+// are taken on their bits, two values an instruction (11 instructions with the test below and the caller's running maximum, where
+// converting first takes 18).  A NaN, signalling ones among them, is then the largest: where a wave meets one, its maxima are taken again in
+// floating point, where a NaN loses against a number.
 __device__ __forceinline__ float absmax8(uint4 v) {
-    auto magnitude = [](uint32_t a) {
-        uint32_t r;
-        asm("v_pk_max_f16 %0, %1, %1 neg_lo:[0,1] neg_hi:[0,1]" : "=v"(r) : "v"(a));
-        return r;
-    };
     auto larger = [](uint32_t a, uint32_t b) {
         uint32_t r;
-        asm("v_pk_max_f16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+        asm("v_pk_max_u16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
         return r;
     };
-    const uint32_t m = larger(larger(magnitude(v.x), magnitude(v.y)), larger(magnitude(v.z), magnitude(v.w)));
-    const float2 f = __half22float2(*reinterpret_cast<const __half2*>(&m));
-    return fmaxf(f.x, f.y);
+    constexpr uint32_t kAbs = 0x7FFF7FFFu, kInf = 0x7C00u;
+    const uint32_t m2 = larger(larger(v.x & kAbs, v.y & kAbs), larger(v.z & kAbs, v.w & kAbs));
+    const uint32_t m = max(m2 & 0xFFFFu, m2 >> 16);
+    float r = __half2float(__ushort_as_half((unsigned short)m));
+    if (__builtin_expect(__any(m > kInf), 0)) {
+        const __half2* h = reinterpret_cast<const __half2*>(&v);
+        r = 0.0f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float2 f = __half22float2(h[i]);
+            r = fmaxf(r, fmaxf(fabsf(f.x), fabsf(f.y)));
+        }
+    }
+    return r;
 }
 
 // e^t and SiLU(g) * u as fixed sequences of separately rounded single-precision operations (no contraction into
@@ -125,14 +130,20 @@ __device__ __forceinline__ uint32_t low_bytes(uint32_t a, uint32_t b, uint32_t c
     return __builtin_amdgcn_perm(cd, ab, 0x05040100u);
 }
 
-// N values' codes + OFFSET in the low bytes of c[] (a value that is no number gives byte 0, the lowest code, as the clamp of a
-// NaN does; in a row or group whose numbers are all zero every code is 0, a NaN's too)
+// Values as offset_codes wants them: all zero where there is no scale, i.e. where every number of the row or group is zero (a
+// NaN among them has code 0 as well, but times a reciprocal of 0 it is no 0).
+__device__ __forceinline__ uint4 zero_without_scale(uint4 v, float s) {
+    if (__builtin_expect(__any(!(s > 0.0f)), 0)) v = s > 0.0f ? v : make_uint4(0u, 0u, 0u, 0u);
+    return v;
+}
+
+// N values' codes + OFFSET in the low bytes of c[] (beside a scale a value that is no number gives byte 0, the lowest code, as the
+// clamp of a NaN does)
 template <int OFFSET, int N>
 __device__ __forceinline__ void offset_codes(const float (&x)[N], float s, uint32_t (&c)[N]) {
     const float r = s > 0.0f ? 1.0f / s : 0.0f;
     const float r_lo = r * (1.0f - 0x1p-21f), r_hi = r * (1.0f + 0x1p-21f);
-    constexpr uint32_t kNoScale = 0x80000000u;  // (two numbers' codes do not differ in this bit, nor do two NaN)
-    uint32_t apart = s > 0.0f ? 0u : kNoScale;
+    uint32_t apart = 0;
 #pragma unroll
     for (int i = 0; i < N; ++i) {
         c[i] = __float_as_uint(fmaf(x[i], r_lo, kCodeMagic + OFFSET));
@@ -141,17 +152,14 @@ __device__ __forceinline__ void offset_codes(const float (&x)[N], float s, uint3
         asm("v_bitop3_b32 %0, %1, %2, %0 bitop3:0xbe" : "+v"(apart) : "v"(c[i]), "v"(other));
     }
     if (__builtin_expect(__any(apart != 0), 0)) {
-        if (__any((apart & ~kNoScale) != 0)) {
-            const float by = s > 0.0f ? s : 1.0f;
+        const float by = s > 0.0f ? s : 1.0f;
 #pragma unroll
-            for (int i = 0; i < N; ++i) c[i] = __float_as_uint(rintf(x[i] / by) + (kCodeMagic + OFFSET));
-        }
-#pragma unroll
-        for (int i = 0; i < N; ++i) c[i] = s > 0.0f ? c[i] : __float_as_uint(kCodeMagic + OFFSET);  // (a NaN times 0 is no 0)
+        for (int i = 0; i < N; ++i) c[i] = __float_as_uint(rintf(x[i] / by) + (kCodeMagic + OFFSET));
     }
 }
 
 __device__ __forceinline__ uint2 quantize8(uint4 v, float s) {
+    v = zero_without_scale(v, s);
     const __half2* h = reinterpret_cast<const __half2*>(&v);
     float x[8];
 #pragma unroll

@@ -367,8 +367,8 @@ __global__ __launch_bounds__(WAVES * kWave) void gemm_decode_kernel(GemmArgs a, 
             uint32_t code[2 * XS];
 #pragma unroll
             for (int i = 0; i < XS; ++i) {
-                xv[2 * i] = xf0[i];
-                xv[2 * i + 1] = xf1[i];
+                xv[2 * i] = s_a > 0.0f ? xf0[i] : 0.0f;  // (a NaN in a row of zeros has code 0)
+                xv[2 * i + 1] = s_a > 0.0f ? xf1[i] : 0.0f;
             }
             offset_codes<128>(xv, s_a, code);
 #pragma unroll

@@ -127,7 +127,8 @@ __global__ __launch_bounds__(kWqThreads) void quantize_weight_rows_kernel(const 
         for (int i = 0; i < kWqInFlight; ++i) {
             if (c0 + i * kWqThreads >= chunks) break;  // uniform
             const int c = c0 + i * kWqThreads + (int)threadIdx.x;
-            const float s = group_max<LPG>(fmaxf(absmax8(v[i]), 0.0f)) / kHi;
+            const float s = group_max<LPG>(absmax8(v[i])) / kHi;
+            v[i] = zero_without_scale(v[i], s);
             const __half2* h = reinterpret_cast<const __half2*>(&v[i]);
             float x[8];
 #pragma unroll
