@@ -5,6 +5,7 @@
 #include <algorithm>
 #include <mutex>
 
+#include "few_common.h"
 #include "is_common.h"
 #include "pk_common.h"
 #include "wavek_common.h"
@@ -73,6 +74,11 @@ bool general_forced_off() { return kernel_route() == 2; }
 bool pk_takes_tile(int M, int N, int K) {
     return M > 64 || (M > 32 && (kernel_route() == 3 || (long long)N * K >= (1LL << 27)));
 }
+
+// Which of the others the kernel takes whose waves split K over the canonical activations (gemm_few_pk.hip): those of 2 to 64
+// rows.  One row stays on the weight-streaming kernel, whose scale step works on the one result register that carries it and which
+// quantises an fp16 token itself (on 60 calls of one row the two are within -10 and +6 % of each other, 3 % on average).
+bool takes_few(int M) { return M >= 2 && M <= 64; }
 
 bool wants_prefill(int M, int num_experts, int group) {
     return !general_forced() && !gemm_small_group_covers(group) && M > 64 * num_experts;
@@ -484,6 +490,22 @@ static int gemm_pk_common(const int8_t* xq, const void* x_fp16, const float* a_s
     a.group = group;
     a.alpha_log2 = int_scale ? alpha_log2 : 0;
     a.pair = (pair && tiled) ? 1 : 0;  // (the fused epilogue is the tiled kernel's)
+    if (!tiled && takes_few(M)) {
+        FewArgs f;
+        f.xq = xq;
+        f.a_scale = a_scale;
+        f.wpack = a.wpack;
+        f.spack = a.spack;
+        f.chan_scale = chan_scale;
+        f.out = a.out;
+        f.acc_out = acc_out;
+        f.M = M;
+        f.N = N;
+        f.K = K;
+        f.group = group;
+        f.alpha_log2 = a.alpha_log2;
+        return hip_status(launch_gemm_few_pk(f, few_plan(M, N, K, pair), int_scale, pair, static_cast<hipStream_t>(stream)));
+    }
     if (tiled)
         return hip_status(launch_gemm_tile_pk(a, int_scale, workspace, workspace_bytes, static_cast<hipStream_t>(stream),
                                               prepared));
@@ -557,6 +579,9 @@ static int gate_up_silu_common(const int8_t* xq, const float* a_scale, const voi
     if (!ok_ptr(out_fp16)) return IS_ERR_INVALID_ARG;
     const size_t gemm = pad_256(is_gemm_prepacked_workspace_bytes(M, N, K, group));
     __half* gu = reinterpret_cast<__half*>(static_cast<unsigned char*>(workspace) + gemm);
+    if (takes_few(M))  // SiLU * up as that kernel's epilogue: the [M, 2 inter] tensor's place stays unused
+        return gemm_pk_common(xq, nullptr, a_scale, nullptr, wpack, spack, chan_scale_packed, M, N, K, group, alpha_log2, out_fp16,
+                              acc_out, workspace, gemm, stream, int_scale, false, true);
     const int st = gemm_pk_common(xq, nullptr, a_scale, nullptr, wpack, spack, chan_scale_packed, M, N, K, group,
                                   alpha_log2, gu, acc_out, workspace, gemm, stream, int_scale);
     if (st != IS_OK) return st;
@@ -770,6 +795,11 @@ int is_describe_prepacked(int M, int N, int K, int group, int int_scale, int fp1
         return IS_OK;
     }
     PkPlan plan;
+    if (takes_few(M)) {
+        if (!pk_decode_plan(M, N, K, group, false, &plan)) return IS_ERR_UNSUPPORTED;
+        few_kernel_name(few_plan(M, N, K, false), int_scale != 0, false, names, names_len);
+        return IS_OK;
+    }
     const bool fused = fp16_in != 0 && M == 1 && pk_decode_plan(1, N, K, group, true, &plan);
     if (!fused && !pk_decode_plan(M, N, K, group, false, &plan)) return IS_ERR_UNSUPPORTED;
     pk_decode_kernel_name(plan, int_scale != 0, fused, names, names_len);

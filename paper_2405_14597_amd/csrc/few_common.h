@@ -1,0 +1,31 @@
+// Interface of the kernel for 2 to 64 token rows whose waves split K (gemm_few_pk.hip).
+#pragma once
+#include "is_common.h"
+
+namespace intscale {
+
+struct FewArgs {
+    const int8_t* xq;         // [M,K]
+    const float* a_scale;     // [M]
+    const uint8_t* wpack;     // kernel layout
+    const uint8_t* spack;     // kernel layout (header included)
+    const float* chan_scale;  // [N] or nullptr
+    __half* out;              // [M,N], or [M,N/2] with the SiLU * up epilogue
+    int32_t* acc_out;         // [M,N] or nullptr
+    int M, N, K, group;
+    int alpha_log2;
+    int num_groups = 0, phase_mask = 0;  // set by the launcher
+};
+
+struct FewPlan {
+    int ms;     // 16-row token tiles
+    int ns;     // 16-row weight tiles of a workgroup
+    int waves;  // waves of a workgroup (the K split)
+    int depth;  // K steps whose weights a wave has on their way
+};
+
+FewPlan few_plan(int M, int N, int K, bool silu);
+void few_kernel_name(const FewPlan& p, bool int_scale, bool silu, char* buf, size_t len);
+hipError_t launch_gemm_few_pk(const FewArgs& a, const FewPlan& p, bool int_scale, bool silu, hipStream_t stream);
+
+}  // namespace intscale

@@ -715,26 +715,19 @@ constexpr int ring_depth(int mt) { return mt == 4 ? 6 : INTSCALE_PK_RING; }
 // Waves per workgroup the instantiations exist for (dispatch_waves and pk_decode_kernel_name both round with this).
 constexpr int waves_instance(int mt, int waves) { return waves <= 4 ? 4 : (waves <= 8 || mt == 4) ? 8 : 16; }
 
-template <bool INT_SCALE, bool FUSEQ, int MT, int NR>
+template <bool INT_SCALE, bool FUSEQ>
 hipError_t dispatch_waves(const PkArgs& a, const PkKernelPlan& kp, const PkPlan& plan, hipStream_t stream) {
-    constexpr int DT = ring_depth(MT);
-    constexpr bool FQ = MT == 1 && FUSEQ;
-    switch (waves_instance(MT, plan.waves)) {
-        case 4: return launch_pk<MT, DT, 4, NR, INT_SCALE, FQ>(a, kp, plan, stream);
-        case 8: return launch_pk<MT, DT, 8, NR, INT_SCALE, FQ>(a, kp, plan, stream);
-        default:
-            if constexpr (MT != 4) return launch_pk<MT, DT, 16, NR, INT_SCALE, FQ>(a, kp, plan, stream);
-            return hipErrorInvalidValue;
+    constexpr int DT = ring_depth(1);
+    switch (waves_instance(1, plan.waves)) {
+        case 4: return launch_pk<1, DT, 4, 1, INT_SCALE, FUSEQ>(a, kp, plan, stream);
+        case 8: return launch_pk<1, DT, 8, 1, INT_SCALE, FUSEQ>(a, kp, plan, stream);
+        default: return launch_pk<1, DT, 16, 1, INT_SCALE, FUSEQ>(a, kp, plan, stream);
     }
 }
 
 template <bool INT_SCALE>
 hipError_t dispatch_pk(const PkArgs& a, const PkKernelPlan& kp, const PkPlan& plan, hipStream_t stream) {
-    if (a.x_fp16) return dispatch_waves<INT_SCALE, true, 1, 1>(a, kp, plan, stream);
-    if (a.M == 1) return dispatch_waves<INT_SCALE, false, 1, 1>(a, kp, plan, stream);
-    if (plan.mt == 1) return dispatch_waves<INT_SCALE, false, 1, 4>(a, kp, plan, stream);
-    if (plan.mt == 2) return dispatch_waves<INT_SCALE, false, 2, 4>(a, kp, plan, stream);
-    return dispatch_waves<INT_SCALE, false, 4, 4>(a, kp, plan, stream);
+    return a.x_fp16 ? dispatch_waves<INT_SCALE, true>(a, kp, plan, stream) : dispatch_waves<INT_SCALE, false>(a, kp, plan, stream);
 }
 
 constexpr size_t kActBudget = 128 * 1024;  // LDS bytes for the slab's activations (the fused quantiser's scratch follows)
@@ -837,7 +830,7 @@ size_t pk_decode_workspace_bytes(int M, int N, int K, int group) {
 
 hipError_t launch_gemm_decode_pk(const PkArgs& a, bool int_scale, hipStream_t stream) {
     PkPlan plan;
-    if (!pk_decode_plan(a.M, a.N, a.K, a.group, a.x_fp16 != nullptr, &plan)) return hipErrorInvalidValue;
+    if (a.M != 1 || !pk_decode_plan(a.M, a.N, a.K, a.group, a.x_fp16 != nullptr, &plan)) return hipErrorInvalidValue;
     PkKernelPlan kp;
     kp.n16 = (a.N + 15) / 16;
     kp.steps = a.K / 128;

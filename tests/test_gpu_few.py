@@ -1,0 +1,107 @@
+"""The kernel for 2 to 64 token rows whose waves split K: one small call per instance that the library can pick, ragged rows and
+columns, short and uneven runs of K steps, groups of several steps, scales beyond 24 bits, the fused SiLU * up epilogue.  The reference
+is the same sums in plain PyTorch (exact in float64: a group's partial sum is below 2^22, its product with a scale below 2^53)."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+G = 128
+
+
+@pytest.fixture(scope="module")
+def P():
+    import paper_2405_14597_amd as P
+    P.load_library()
+    return P
+
+
+def smallest_shape_per_instance():
+    import paper_2405_14597_amd as P
+    best = {}
+    for M in (2, 16, 17, 32, 33, 48, 49, 64):
+        for N in (20, 1000, 4100, 8184, 12280, 16376, 20472, 22000, 24568, 28664):
+            for K in (128, 256, 640, 1024, 3072, 4224, 8192, 12288, 14336, 16384):
+                name = P.is_describe_prepacked(M, N, K, G)[-1]
+                if name.startswith("gemm_decode_pk_kernel<") and N * K < best.get(name, (0, 1 << 60))[1]:
+                    best[name] = ((M, N, K), N * K)
+    return [(name, *shape) for name, (shape, _) in sorted(best.items())]
+
+
+def reference(xq, q, scale, group):
+    """Sum over the groups of (integer partial sum) * scale, in float64."""
+    acc = torch.zeros((xq.shape[0], q.shape[0]), dtype=torch.float64, device=xq.device)
+    for g in range(xq.shape[1] // group):
+        cut = slice(g * group, (g + 1) * group)
+        acc += (xq[:, cut].double() @ q[:, cut].double().t().contiguous()) * scale[:, g].double()
+    return acc
+
+
+def case(M, N, K, group=G, wide=False, seed=0):
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(1000 * seed + M + N + K)
+    xq = torch.randint(-128, 128, (M, K), generator=gen, device="cuda:0", dtype=torch.int8)
+    q = torch.randint(-8, 8, (N, K), generator=gen, device="cuda:0", dtype=torch.int32)
+    qw = ((q[:, 0::2] & 15) | ((q[:, 1::2] & 15) << 4)).to(torch.uint8).contiguous()
+    scale = torch.randint(0, 1025, (N, K // group), generator=gen, device="cuda:0", dtype=torch.int32)
+    if wide:
+        scale[N // 2, -1] = 2 ** 25
+        scale[0, 0] = -(2 ** 23) - 1
+    sa = torch.rand((M,), generator=gen, device="cuda:0") + 0.1
+    c = torch.rand((N,), generator=gen, device="cuda:0") + 0.5
+    return xq, q, qw, scale, sa, c
+
+
+def wrapped(acc):
+    return ((acc.long() + 2 ** 31) % 2 ** 32 - 2 ** 31).to(torch.int32)
+
+
+def check_call(P, M, N, K, group=G, wide=False, chan=True):
+    xq, q, qw, scale, sa, c = case(M, N, K, group, wide)
+    acc = wrapped(reference(xq, q, scale, group))
+    cc = c if chan else None
+    out, got = P.is_gemm_w4a8_intscale_prepacked(xq, sa, P.is_prepack_w4(qw, scale, group), cc, 10, want_acc=True)
+    assert torch.equal(got, acc), "int32 accumulators"
+    want = acc.double() * sa.double()[:, None] * (c.double()[None, :] if chan else 1.0) / 1024.0
+    ok = want.abs() < 65000.0
+    # two fp32 products and one rounding to fp16: 2^-11 of the value and a little more, and half a step of the smallest numbers
+    assert bool(((out.double() - want).abs() <= 5e-4 * want.abs() + 2.0 ** -25)[ok].all())
+    again, _ = P.is_gemm_w4a8_intscale_prepacked(xq, sa, P.is_prepack_w4(qw, scale, group), cc, 10)
+    assert torch.equal(again, out)
+    s32 = scale.float() * (2.0 ** -17 if not wide else 2.0 ** -32)
+    fout = P.is_gemm_w4a8_floatscale_prepacked(xq, sa, P.is_prepack_w4(qw, s32, group))
+    fs = reference(xq, q, s32, group) * sa.double()[:, None]
+    size = reference(xq.abs().clamp(max=127), q.abs(), s32.abs(), group) * sa.double()[:, None]
+    # (the sum of K / group products in fp32: their sizes times 2^-24 each and per addition)
+    bound = 5e-4 * fs.abs() + 2.0 ** -25 + size * (K // group + 2) * 2.0 ** -24
+    assert bool(((fout.double() - fs).abs() <= bound)[fs.abs() < 65000.0].all())
+
+
+@pytest.mark.parametrize("name,M,N,K", smallest_shape_per_instance())
+def test_every_instance(P, name, M, N, K):
+    assert P.is_describe_prepacked(M, N, K, G)[-1] == name
+    check_call(P, M, N, K)
+
+
+@pytest.mark.parametrize("M,N,K,group", [(2, 16, 128, 128), (3, 17, 384, 384), (31, 300, 1536, 512), (64, 1003, 1152, 384), (50, 97, 1152, 1152),
+                                         (16, 2050, 12288, 256), (33, 40, 14336, 256)])
+@pytest.mark.parametrize("wide", [False, True])
+def test_groups_ragged_sizes_and_wide_scales(P, M, N, K, group, wide):
+    check_call(P, M, N, K, group, wide, chan=not wide)
+
+
+@pytest.mark.parametrize("M,inter,K", [(2, 16, 128), (16, 48, 1024), (17, 1200, 512), (40, 5504, 256), (64, 2064, 4096), (9, 14336, 256)])
+def test_fused_gate_up(P, M, inter, K):
+    """The epilogue gives the bits of the GEMM's fp16 outputs taken through SiLU * up (the quantiser of that product, on either)."""
+    xq, q, qw, scale, sa, c = case(M, 2 * inter, K, seed=3)
+    sa = sa * 1e-3
+    gu, _ = P.is_gemm_w4a8_intscale_prepacked(xq, sa, P.is_prepack_w4(qw, scale, G), c, 10)
+    codes, s = P.is_silu_mul_quantize_act_int8_token(gu)
+    packed = P.is_prepack_w4_gate_up(qw, scale, c, G)
+    fused = P.is_gemm_w4a8_intscale_gate_up_silu_prepacked(xq, sa, packed, 10)
+    fused = fused[0] if isinstance(fused, tuple) else fused
+    codes_f, s_f = P.is_quantize_act_int8_token(fused)
+    assert torch.equal(codes, codes_f) and torch.equal(s, s_f)
+    g, u = gu[:, :inter].double(), gu[:, inter:].double()
+    want = g / (1.0 + torch.exp(-g)) * u
+    assert bool(((fused.double() - want).abs() <= 1e-3 * want.abs() + 2.0 ** -24)[want.abs() < 65000.0].all())
