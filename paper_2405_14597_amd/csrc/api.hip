@@ -49,7 +49,7 @@ int check_gemm_shape(int M, int N, int K, int group) {
 // go to the MFMA-bound tiled kernel, which needs workspace for its zero-point corrections (takes_wavek below has the exceptions).
 // Routing override (tests and experiments): 0 automatic, 1 everything the general kernel covers goes to it, 2 the
 // W8A8 GEMMs go to the tiled kernel whatever M is, 3 the prepacked calls of 33..64 rows go to the tiled kernel (with 2 and 3 the
-// prepacked and the W8A8 calls of more rows stay there, too).  Starts from INTSCALE_FORCE_KERNEL=general|tiled, read once;
+// prepacked and the W8A8 calls of more rows stay there, too, and so does the mixture-of-experts form).  Starts from INTSCALE_FORCE_KERNEL=general|tiled, read once;
 // is_set_kernel_route changes it afterwards.  Nothing on the launch path reads the environment.
 std::atomic<int> g_route{-1};
 int kernel_route() {
@@ -697,6 +697,24 @@ static int gemm_grouped_pk_common(const int8_t* xq, const float* a_scale, const 
     a.K = K;
     a.group = group;
     a.alpha_log2 = int_scale ? alpha_log2 : 0;
+    const FewPlan plan = kernel_route() < 2 ? few_grouped_plan(E, M, N, K) : FewPlan{};  // (routes 2 and 3: the tiled kernel)
+    if (plan.ns > 0) {
+        FewArgs f;
+        f.xq = xq;
+        f.a_scale = a_scale;
+        f.wpack = a.wpack;
+        f.spack = a.spack;
+        f.chan_scale = chan_scale;
+        f.out = a.out;
+        f.acc_out = acc_out;
+        f.M = M;
+        f.N = N;
+        f.K = K;
+        f.group = group;
+        f.alpha_log2 = a.alpha_log2;
+        const FewGroups fg{row_offsets, E, pk_weight_bytes(N, K), pk_scale_bytes(N, K, group)};
+        return hip_status(launch_gemm_few_grouped_pk(f, fg, plan, int_scale, static_cast<hipStream_t>(stream)));
+    }
     return hip_status(launch_gemm_tile_grouped_pk(a, row_offsets, E, pk_weight_bytes(N, K), pk_scale_bytes(N, K, group),
                                                   int_scale, workspace, static_cast<hipStream_t>(stream)));
 }
@@ -813,7 +831,9 @@ int is_describe_grouped_prepacked(int num_experts, int M_total, int N, int K, in
     if (M_total < 1) return IS_ERR_INVALID_ARG;
     const int shape = check_grouped_pk(num_experts, M_total, N, K, group);
     if (shape != IS_OK) return shape;
-    gemm_tile_grouped_pk_kernel_names(num_experts, M_total, int_scale != 0, names, names_len);
+    const FewPlan plan = kernel_route() < 2 ? few_grouped_plan(num_experts, M_total, N, K) : FewPlan{};
+    if (plan.ns > 0) few_grouped_kernel_name(plan, int_scale != 0, names, names_len);
+    else gemm_tile_grouped_pk_kernel_names(num_experts, M_total, int_scale != 0, names, names_len);
     return IS_OK;
 }
 

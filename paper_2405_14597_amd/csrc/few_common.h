@@ -24,8 +24,20 @@ struct FewPlan {
     int depth;  // K steps whose weights a wave has on their way
 };
 
+// Mixture-of-experts form: xq / a_scale / out hold all experts' rows sorted by expert, expert e owning rows
+// [row_offsets[e], row_offsets[e+1]); wpack, spack and chan_scale of FewArgs are expert 0's.
+struct FewGroups {
+    const int32_t* row_offsets;  // device, [num_experts + 1]
+    int num_experts;
+    size_t wstride, sstride;     // bytes from one expert's packed weights / scales to the next
+};
+
 FewPlan few_plan(int M, int N, int K, bool silu);
 void few_kernel_name(const FewPlan& p, bool int_scale, bool silu, char* buf, size_t len);
 hipError_t launch_gemm_few_pk(const FewArgs& a, const FewPlan& p, bool int_scale, bool silu, hipStream_t stream);
+// (ms: 16-row token tiles a workgroup takes at a time; ns = 0: the call is not for this kernel)
+FewPlan few_grouped_plan(int E, int M, int N, int K);
+void few_grouped_kernel_name(const FewPlan& p, bool int_scale, char* buf, size_t len);
+hipError_t launch_gemm_few_grouped_pk(const FewArgs& a, const FewGroups& g, const FewPlan& p, bool int_scale, hipStream_t stream);
 
 }  // namespace intscale

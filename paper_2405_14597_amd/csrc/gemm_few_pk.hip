@@ -21,6 +21,7 @@
 // workgroups first): 16 rows: 4096 x 4096 6.5 -> 5.0 us, 12288 x 4096 8.2 -> 7.3, 4096 x 11008 10.1 -> 7.5, 57344 x 8192 49.5 -> 45.6;
 // 32 rows: 4096 x 4096 9.0 -> 5.7, 22016 x 4096 14.9 -> 13.0, 57344 x 8192 63 -> 51, 8192 x 28672 32.8 -> 33.5; 64 rows: 4096 x 4096
 // 11.1 -> 7.3, 12288 x 4096 15.9 -> 10.3, 22016 x 4096 24.3 -> 18.7, 10240 x 8192 22.8 -> 17.2; on 359 calls 0.77 of its time.
+#include <math.h>
 #include <stdio.h>
 
 #include <algorithm>
@@ -425,6 +426,15 @@ __global__ __launch_bounds__(W* kWave) __attribute__((amdgpu_waves_per_eu(2, 2))
     few_tile<INT_SCALE, MS, NS, W, D, SILU>(a, t, smem_few);
 }
 
+// The launch's own arguments: groups along K, and the largest 2^n - 1 below the shortest wave's number of steps
+FewArgs with_launch_arguments(const FewArgs& a, int waves) {
+    FewArgs b = a;
+    b.num_groups = a.K / a.group;
+    b.phase_mask = 0;
+    while (2 * b.phase_mask + 2 <= (a.K >> 7) / waves) b.phase_mask = 2 * b.phase_mask + 1;
+    return b;
+}
+
 template <bool INT_SCALE, int MS, int NS, int W, int D, bool SILU>
 hipError_t launch_instance(const FewArgs& a, hipStream_t stream) {
     static LdsLimit limit;  // per instantiation
@@ -434,13 +444,55 @@ hipError_t launch_instance(const FewArgs& a, hipStream_t stream) {
     const hipError_t r = limit.raise(reinterpret_cast<const void*>(kernel), (int)lds);
     if (r != hipSuccess) return r;
     const int n16 = (a.N + 15) / 16;
-    FewArgs b = a;
-    b.num_groups = a.K / a.group;
-    const int run = (a.K >> 7) / W;  // steps of the shortest run
-    b.phase_mask = 0;  // 2^n - 1 below it
-    while (2 * b.phase_mask + 2 <= run) b.phase_mask = 2 * b.phase_mask + 1;
-    
-    hipLaunchKernelGGL(kernel, dim3((n16 + NS - 1) / NS), dim3(W * kWave), lds, stream, b);
+    hipLaunchKernelGGL(kernel, dim3((n16 + NS - 1) / NS), dim3(W * kWave), lds, stream, with_launch_arguments(a, W));
+    return hipGetLastError();
+}
+
+// Mixture-of-experts form: workgroup (x, e) takes NS weight tiles of expert e and the expert's rows, 16 MT of them at a time; an expert
+// without rows costs a workgroup's start.
+template <int MT, int NS, int W, int D, bool INT_SCALE>
+__global__ __launch_bounds__(W* kWave) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_decode_grouped_pk_kernel(FewArgs a, FewGroups g) {
+    extern __shared__ __align__(16) unsigned char smem_few[];
+    const int e = blockIdx.y;
+    const int lo = max(g.row_offsets[e], 0), hi = min(g.row_offsets[e + 1], a.M);
+    FewTile t;
+    t.wpack = a.wpack + e * g.wstride;
+    t.spack = a.spack + e * g.sstride;
+    t.chan_scale = a.chan_scale ? a.chan_scale + (size_t)e * a.N : nullptr;
+    t.t0 = blockIdx.x * NS;
+    t.phase = blockIdx.x / 16;
+    for (int m = lo; m < hi; m += 16 * MT) {
+        if (m > lo) __syncthreads();  // the output tile of the rows before has been read
+        t.x = a.xq + (size_t)m * a.K;
+        t.a_scale = a.a_scale + m;
+        t.out = a.out + (size_t)m * a.N;
+        t.acc_out = a.acc_out ? a.acc_out + (size_t)m * a.N : nullptr;
+        t.m_rows = min(hi - m, 16 * MT);
+        if constexpr (MT >= 4) {
+            if (t.m_rows > 32) {
+                few_tile<INT_SCALE, 4, NS, W, D, false>(a, t, smem_few);
+                continue;
+            }
+        }
+        if constexpr (MT >= 2) {
+            if (t.m_rows > 16) {
+                few_tile<INT_SCALE, 2, NS, W, D, false>(a, t, smem_few);
+                continue;
+            }
+        }
+        few_tile<INT_SCALE, 1, NS, W, D, false>(a, t, smem_few);
+    }
+}
+
+template <int MT, int NS, int W, int D, bool INT_SCALE>
+hipError_t launch_grouped_instance(const FewArgs& a, const FewGroups& g, hipStream_t stream) {
+    static LdsLimit limit;  // per instantiation
+    auto kernel = gemm_decode_grouped_pk_kernel<MT, NS, W, D, INT_SCALE>;
+    constexpr size_t lds = few_lds_bytes(MT, NS, W);
+    const hipError_t r = limit.raise(reinterpret_cast<const void*>(kernel), (int)lds);
+    if (r != hipSuccess) return r;
+    const int n16 = (a.N + 15) / 16;
+    hipLaunchKernelGGL(kernel, dim3((n16 + NS - 1) / NS, g.num_experts), dim3(W * kWave), lds, stream, with_launch_arguments(a, W), g);
     return hipGetLastError();
 }
 
@@ -490,6 +542,21 @@ hipError_t launch_ms(const FewArgs& a, const FewPlan& p, hipStream_t stream) {
     }
 }
 
+template <bool INT_SCALE>
+hipError_t launch_grouped(const FewArgs& a, const FewGroups& g, const FewPlan& p, hipStream_t stream) {
+    if (p.ms == 4) return p.ns == 2 ? launch_grouped_instance<4, 2, 4, 2, INT_SCALE>(a, g, stream) : launch_grouped_instance<4, 3, 4, 2, INT_SCALE>(a, g, stream);
+    switch (p.ns) {
+        case 2: return launch_grouped_instance<2, 2, 4, 2, INT_SCALE>(a, g, stream);
+        case 3: return launch_grouped_instance<2, 3, 4, 2, INT_SCALE>(a, g, stream);
+        case 4: return launch_grouped_instance<2, 4, 4, 2, INT_SCALE>(a, g, stream);
+        default: return launch_grouped_instance<2, 5, 4, 2, INT_SCALE>(a, g, stream);
+    }
+}
+
+// microseconds: a wave's step with its SIMD to itself, a workgroup's start and end (fitted, see few_plan)
+double step_us(int ms, int ns) { return 0.062 * ms + 0.025 * ns + 0.014 * ms * ns; }
+double ends_us(int ms, int ns) { return 1.1 * (1.0 + 0.11 * ms * ns); }
+
 }  // namespace
 
 // Waves: eight where one workgroup a compute unit is all there is, so that each SIMD still has two (by rows, from the K length on
@@ -515,8 +582,7 @@ FewPlan few_plan(int M, int N, int K, bool silu) {
         int run = (steps + waves - 1) / waves;
         const int depth = has_instance(ms, ns, waves, 4, silu) && run >= (ms == 1 ? 8 : 16) ? 4 : 2;  // (K steps)
         run = (run + depth - 1) / depth * depth;
-        // microseconds: a wave's step with its SIMD to itself, a workgroup's start and end
-        const double step = 0.062 * ms + 0.025 * ns + 0.014 * ms * ns, ends = 1.1 * (1.0 + 0.11 * ms * ns);
+        const double step = step_us(ms, ns), ends = ends_us(ms, ns);
         const double us = waves == 8 ? per_cu * (ends + 2 * run * step) : (per_cu / 2) * (ends + 2 * run * step) + (per_cu % 2) * (ends + run * step);
         if (best.ns == 0 || us < best_us) {
             best = FewPlan{ms, ns, waves, depth};
@@ -534,6 +600,44 @@ void few_kernel_name(const FewPlan& p, bool int_scale, bool silu, char* buf, siz
 hipError_t launch_gemm_few_pk(const FewArgs& a, const FewPlan& p, bool int_scale, bool silu, hipStream_t stream) {
     if (silu) return int_scale ? launch_ms<true, true>(a, p, stream) : launch_ms<false, true>(a, p, stream);
     return int_scale ? launch_ms<true, false>(a, p, stream) : launch_ms<false, false>(a, p, stream);
+}
+
+hipError_t launch_gemm_few_grouped_pk(const FewArgs& a, const FewGroups& g, const FewPlan& p, bool int_scale, hipStream_t stream) {
+    return int_scale ? launch_grouped<true>(a, g, p, stream) : launch_grouped<false>(a, g, p, stream);
+}
+
+// The mixture-of-experts form takes the calls of few rows an expert: there the tiled kernel's preparation and its tiles of 256 columns,
+// which go through LDS with a barrier a step, cost more than one read of the weights (8 experts, two per token: 28672 x 4096,
+// 16 tokens, 115.7 -> 93.0 us, 64 tokens 109 -> 96.7; 4096 x 14336 61.3 -> 47.0 and 63.7 -> 47.9; 4 experts of 6144 x 2048, one per
+// token, 32 tokens 18.6 -> 8.6).  At 32 rows an expert the tiled kernel is ahead where the weights are large (28672 x 4096 115.6
+// against 123.4 us here) and behind where they are not (4096 x 14336 72.7 and 68.2, 6144 x 2048 23.7 and 10.6).
+// Rows are dealt as if the router were uniform (the offsets are on the device): workgroups of 32 rows, of 64 from 24 rows an expert on;
+// an expert with more is worked on in turns.
+FewPlan few_grouped_plan(int E, int M, int N, int K) {
+    const int tiles = (N + 15) / 16;
+    const double rows = (double)M / E;
+    if (rows > 40.0 || (rows > 24.0 && (long long)E * tiles > 2048)) return FewPlan{0, 0, 0, 0};
+    const int ms = rows <= 10.0 ? 1 : rows <= 24.0 ? 2 : 3;
+    double idle = 1.0;  // share of the experts that no row comes to
+    for (int i = 0; i < M && idle > 1e-3; ++i) idle *= 1.0 - 1.0 / E;
+    int run = ((K >> 7) + 3) / 4;
+    run += run & 1;
+    FewPlan best{rows <= 24.0 ? 2 : 4, 0, 4, 2};
+    double best_us = 0.0;
+    for (int ns = 2; ns <= (best.ms == 2 ? 5 : 3); ++ns) {
+        const double per_cu = (tiles + ns - 1) / ns * (E * (1.0 - idle)) / cu_count();
+        // rounds of two workgroups a unit, the last one as long as the others
+        const double us = per_cu <= 1.05 ? ends_us(ms, ns) + run * step_us(ms, ns) : ceil(per_cu / 2 - 0.05) * (ends_us(ms, ns) + 2 * run * step_us(ms, ns));
+        if (best.ns == 0 || us < best_us) {
+            best.ns = ns;
+            best_us = us;
+        }
+    }
+    return best;
+}
+
+void few_grouped_kernel_name(const FewPlan& p, bool int_scale, char* buf, size_t len) {
+    snprintf(buf, len, "gemm_decode_grouped_pk_kernel<%d, %d, %d, %d, %s>", p.ms, p.ns, p.waves, p.depth, int_scale ? "true" : "false");
 }
 
 }  // namespace intscale

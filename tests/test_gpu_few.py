@@ -105,3 +105,39 @@ def test_fused_gate_up(P, M, inter, K):
     g, u = gu[:, :inter].double(), gu[:, inter:].double()
     want = g / (1.0 + torch.exp(-g)) * u
     assert bool(((fused.double() - want).abs() <= 1e-3 * want.abs() + 2.0 ** -24)[want.abs() < 65000.0].all())
+
+
+# experts without rows, with one, with more than a workgroup takes at a time (32 or 64), ragged widths, groups of several steps
+GROUPED = [(1, [5], 100, 256, 128), (4, [0, 3, 16, 17], 300, 640, 128), (8, [0, 0, 40, 1, 0, 33, 0, 0], 1000, 1536, 384),
+           (4, [70, 1, 0, 25], 520, 1024, 128), (4, [40, 33, 64, 15], 264, 2048, 256), (16, [2] * 15 + [0], 4104, 384, 128),
+           (3, [0, 31, 64], 84, 1152, 1152), (2, [12, 4], 28672, 256, 128)]
+
+
+@pytest.mark.parametrize("E,rows,N,K,group", GROUPED)
+@pytest.mark.parametrize("wide", [False, True])
+def test_grouped(P, E, rows, N, K, group, wide):
+    M = sum(rows)
+    assert P.is_describe_grouped_prepacked(E, M, N, K, group)[-1].startswith("gemm_decode_grouped_pk_kernel<")
+    offsets = torch.tensor([sum(rows[:e]) for e in range(E + 1)], dtype=torch.int32, device="cuda:0")
+    sets = [case(max(r, 1), N, K, group, wide and e % 2 == 1, seed=e) for e, r in enumerate(rows)]
+    xq = torch.cat([s[0][:r] for s, r in zip(sets, rows)])
+    sa = torch.cat([s[4][:r] for s, r in zip(sets, rows)])
+    chan = torch.stack([s[5] for s in sets])
+    packed = P.is_prepack_w4_experts(torch.stack([s[2] for s in sets]), torch.stack([s[3] for s in sets]), group)
+    acc = torch.cat([wrapped(reference(s[0][:r], s[1], s[3], group)) for s, r in zip(sets, rows)])
+    out, got = P.is_gemm_w4a8_intscale_grouped_prepacked(xq, sa, packed, chan, offsets, 10, want_acc=True)
+    assert torch.equal(got, acc), "int32 accumulators"
+    # the tiled form computes the same bits
+    before = P.is_set_kernel_route("tiled64")
+    try:
+        assert P.is_describe_grouped_prepacked(E, M, N, K, group)[-1] == "gemm_tile_grouped_pk_kernel<true>"
+        tiled, tiled_acc = P.is_gemm_w4a8_intscale_grouped_prepacked(xq, sa, packed, chan, offsets, 10, want_acc=True)
+    finally:
+        P.is_set_kernel_route(before)
+    assert torch.equal(tiled_acc, got) and torch.equal(tiled, out)
+    floats = [s[3].float() * (2.0 ** -32 if wide else 2.0 ** -17) for s in sets]
+    fpacked = P.is_prepack_w4_experts(torch.stack([s[2] for s in sets]), torch.stack(floats), group)
+    fout = P.is_gemm_w4a8_floatscale_grouped_prepacked(xq, sa, fpacked, offsets)
+    fs = torch.cat([reference(s[0][:r], s[1], f, group) for s, f, r in zip(sets, floats, rows)]) * sa.double()[:, None]
+    size = torch.cat([reference(s[0][:r].abs().clamp(max=127), s[1].abs(), f.abs(), group) for s, f, r in zip(sets, floats, rows)]) * sa.double()[:, None]
+    assert bool(((fout.double() - fs).abs() <= 5e-4 * fs.abs() + 2.0 ** -25 + size * (K // group + 2) * 2.0 ** -24)[fs.abs() < 65000.0].all())
