@@ -236,23 +236,43 @@ def _check(fn: str, status: int) -> None:
 # --------------------------------------------------------------------------------------------------------------
 # torch-tensor level.  torch is imported lazily so that the symbol/ABI checks work without it.
 # --------------------------------------------------------------------------------------------------------------
+_torch_module = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
+
+
+# (device, current stream of a device as a number): what torch.cuda.current_stream().cuda_stream comes to, without the stream object,
+# whose making took 2.9 of the 9.9 us of a one-token call's host side (0.2 this way)
+_current_device = _current_raw_stream = None
 
 
 def _stream_handle(stream) -> int:
-    torch = _torch()
-    s = torch.cuda.current_stream() if stream is None else stream
-    return int(s.cuda_stream)
+    global _current_device, _current_raw_stream
+    if stream is not None:
+        return int(stream.cuda_stream)
+    if _current_raw_stream is None:
+        torch = _torch()
+        current = torch.cuda.current_stream()   # (initialises CUDA where nothing has yet)
+        _current_device = getattr(torch._C, "_cuda_getDevice", None)
+        _current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if _current_device is None or _current_raw_stream is None:
+            _current_device, _current_raw_stream = int, lambda _: int(torch.cuda.current_stream().cuda_stream)
+        return int(current.cuda_stream)
+    return _current_raw_stream(_current_device())
 
 
 def _p(t) -> Optional[int]:
-    return None if t is None else int(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _require(t, dtype, shape, name):
-    if t.dtype != dtype or tuple(t.shape) != tuple(shape) or not t.is_contiguous() or not t.is_cuda:
+    if t.dtype != dtype or t.shape != shape or not t.is_contiguous() or not t.is_cuda:
         raise ValueError(f"{name}: expected contiguous cuda tensor {dtype} {tuple(shape)}, got {t.dtype} "
                          f"{tuple(t.shape)} on {t.device}")
 
@@ -341,13 +361,14 @@ def is_gemm_grouped_workspace_bytes(E: int, M_total: int, N: int, K: int, group:
     return int(load_library().is_gemm_grouped_workspace_bytes(E, M_total, N, K, group))
 
 
-def _workspace(nbytes: int, device, workspace):
-    torch = _torch()
+def _workspace(query, sizes, device, workspace):
+    """The caller's workspace, or one of the size that `query(*sizes)` asks for (the library checks the caller's itself)."""
     if workspace is not None:
         return workspace, workspace.numel() * workspace.element_size()
+    nbytes = query(*sizes)
     if nbytes == 0:
         return None, 0
-    ws = torch.empty((nbytes,), dtype=torch.uint8, device=device)
+    ws = _torch().empty((nbytes,), dtype=_torch().uint8, device=device)
     return ws, nbytes
 
 
@@ -377,7 +398,7 @@ def is_gemm_w4a8_intscale(xq, a_scale, qweight, scale_i32, chan_scale, group: in
         acc_out = torch.empty((M, N), dtype=torch.int32, device=xq.device)
     if acc_out is not None:
         _require(acc_out, torch.int32, (M, N), "acc_out")
-    ws, ws_bytes = _workspace(is_gemm_workspace_bytes(M, N, K, group), xq.device, workspace)
+    ws, ws_bytes = _workspace(is_gemm_workspace_bytes, (M, N, K, group), xq.device, workspace)
     st = load_library().is_gemm_w4a8_intscale(_p(xq), _p(a_scale), _p(qweight), _p(scale_i32), _p(chan_scale), M, N, K,
                                              group, alpha_log2, _p(out), _p(acc_out), _p(ws), ws_bytes,
                                              _stream_handle(stream))
@@ -397,7 +418,7 @@ def is_gemm_w4a8_floatscale(xq, a_scale, qweight, scale_f32, group: int, out=Non
     if out is None:
         out = torch.empty((M, N), dtype=torch.float16, device=xq.device)
     _require(out, torch.float16, (M, N), "out")
-    ws, ws_bytes = _workspace(is_gemm_workspace_bytes(M, N, K, group), xq.device, workspace)
+    ws, ws_bytes = _workspace(is_gemm_workspace_bytes, (M, N, K, group), xq.device, workspace)
     st = load_library().is_gemm_w4a8_floatscale(_p(xq), _p(a_scale), _p(qweight), _p(scale_f32), M, N, K, group,
                                                _p(out), _p(ws), ws_bytes, _stream_handle(stream))
     _check("is_gemm_w4a8_floatscale", st)
@@ -427,7 +448,7 @@ def is_linear_w4a8_intscale(x, qweight, scale_i32, chan_scale, group: int, alpha
         acc_out = torch.empty((M, N), dtype=torch.int32, device=x.device)
     if acc_out is not None:
         _require(acc_out, torch.int32, (M, N), "acc_out")
-    ws, ws_bytes = _workspace(is_linear_workspace_bytes(M, N, K, group), x.device, workspace)
+    ws, ws_bytes = _workspace(is_linear_workspace_bytes, (M, N, K, group), x.device, workspace)
     st = load_library().is_linear_w4a8_intscale(_p(x), _p(qweight), _p(scale_i32), _p(chan_scale), M, N, K, group,
                                                alpha_log2, _p(out), _p(acc_out), _p(ws), ws_bytes,
                                                _stream_handle(stream))
@@ -446,7 +467,7 @@ def is_linear_w4a8_floatscale(x, qweight, scale_f32, group: int, out=None, works
     if out is None:
         out = torch.empty((M, N), dtype=torch.float16, device=x.device)
     _require(out, torch.float16, (M, N), "out")
-    ws, ws_bytes = _workspace(is_linear_workspace_bytes(M, N, K, group), x.device, workspace)
+    ws, ws_bytes = _workspace(is_linear_workspace_bytes, (M, N, K, group), x.device, workspace)
     st = load_library().is_linear_w4a8_floatscale(_p(x), _p(qweight), _p(scale_f32), M, N, K, group, _p(out), _p(ws),
                                                  ws_bytes, _stream_handle(stream))
     _check("is_linear_w4a8_floatscale", st)
@@ -497,7 +518,7 @@ def is_gemm_w8a8_intscale(xq, a_scale, qweight8, scale_i32, chan_scale, group: i
         acc_out = torch.empty((M, N), dtype=torch.int32, device=xq.device)
     if acc_out is not None:
         _require(acc_out, torch.int32, (M, N), "acc_out")
-    ws, ws_bytes = _workspace(is_gemm_w8a8_workspace_bytes(M, N, K, group), xq.device, workspace)
+    ws, ws_bytes = _workspace(is_gemm_w8a8_workspace_bytes, (M, N, K, group), xq.device, workspace)
     st = load_library().is_gemm_w8a8_intscale(_p(xq), _p(a_scale), _p(qweight8), _p(scale_i32), _p(chan_scale), M, N, K,
                                              group, alpha_log2, _p(out), _p(acc_out), _p(ws), ws_bytes,
                                              _stream_handle(stream))
@@ -517,7 +538,7 @@ def is_gemm_w8a8_floatscale(xq, a_scale, qweight8, scale_f32, group: int, out=No
     if out is None:
         out = torch.empty((M, N), dtype=torch.float16, device=xq.device)
     _require(out, torch.float16, (M, N), "out")
-    ws, ws_bytes = _workspace(is_gemm_w8a8_workspace_bytes(M, N, K, group), xq.device, workspace)
+    ws, ws_bytes = _workspace(is_gemm_w8a8_workspace_bytes, (M, N, K, group), xq.device, workspace)
     st = load_library().is_gemm_w8a8_floatscale(_p(xq), _p(a_scale), _p(qweight8), _p(scale_f32), M, N, K, group,
                                                _p(out), _p(ws), ws_bytes, _stream_handle(stream))
     _check("is_gemm_w8a8_floatscale", st)
@@ -543,7 +564,7 @@ def is_gemm_w4a8_intscale_safe(xq, a_scale, qweight, scale_i32, chan_scale, grou
     if out is None:
         out = torch.empty((M, N), dtype=torch.float16, device=xq.device)
     _require(out, torch.float16, (M, N), "out")
-    ws, ws_bytes = _workspace(is_gemm_safe_workspace_bytes(M, N, K, group), xq.device, workspace)
+    ws, ws_bytes = _workspace(is_gemm_safe_workspace_bytes, (M, N, K, group), xq.device, workspace)
     st = load_library().is_gemm_w4a8_intscale_safe(_p(xq), _p(a_scale), _p(qweight), _p(scale_i32), _p(chan_scale), M,
                                                   N, K, group, alpha_log2, _p(out), _p(ws), ws_bytes,
                                                   _stream_handle(stream))
@@ -583,7 +604,7 @@ def is_gemm_w4a8_intscale_grouped(xq, a_scale, qweight, scale_i32, chan_scale, r
     _require(out, torch.float16, (M, N), "out")
     if acc_out is None and want_acc:
         acc_out = torch.empty((M, N), dtype=torch.int32, device=xq.device)
-    ws, ws_bytes = _workspace(is_gemm_grouped_workspace_bytes(E, M, N, K, group), xq.device, workspace)
+    ws, ws_bytes = _workspace(is_gemm_grouped_workspace_bytes, (E, M, N, K, group), xq.device, workspace)
     st = load_library().is_gemm_w4a8_intscale_grouped(_p(xq), _p(a_scale), _p(qweight), _p(scale_i32), _p(chan_scale),
                                                      _p(row_offsets), E, M, N, K, group, alpha_log2, _p(out),
                                                      _p(acc_out), _p(ws), ws_bytes, _stream_handle(stream))
@@ -605,7 +626,7 @@ def is_gemm_w4a8_floatscale_grouped(xq, a_scale, qweight, scale_f32, row_offsets
     if out is None:
         out = torch.empty((M, N), dtype=torch.float16, device=xq.device)
     _require(out, torch.float16, (M, N), "out")
-    ws, ws_bytes = _workspace(is_gemm_grouped_workspace_bytes(E, M, N, K, group), xq.device, workspace)
+    ws, ws_bytes = _workspace(is_gemm_grouped_workspace_bytes, (E, M, N, K, group), xq.device, workspace)
     st = load_library().is_gemm_w4a8_floatscale_grouped(_p(xq), _p(a_scale), _p(qweight), _p(scale_f32),
                                                        _p(row_offsets), E, M, N, K, group, _p(out), _p(ws), ws_bytes,
                                                        _stream_handle(stream))
@@ -736,7 +757,7 @@ def is_gemm_w4a8_intscale_grouped_prepacked(xq, a_scale, packed: PackedExperts, 
         acc_out = torch.empty((M, N), dtype=torch.int32, device=xq.device)
     if acc_out is not None:
         _require(acc_out, torch.int32, (M, N), "acc_out")
-    ws, ws_bytes = _workspace(is_gemm_grouped_prepacked_workspace_bytes(E, M, N, K, group), xq.device, workspace)
+    ws, ws_bytes = _workspace(is_gemm_grouped_prepacked_workspace_bytes, (E, M, N, K, group), xq.device, workspace)
     st = load_library().is_gemm_w4a8_intscale_grouped_prepacked(
         _p(xq), _p(a_scale), _p(packed.wpack), _p(packed.spack), _p(chan_scale), _p(row_offsets), E, M, N, K, group,
         alpha_log2, _p(out), _p(acc_out), _p(ws), ws_bytes, _stream_handle(stream))
@@ -758,7 +779,7 @@ def is_gemm_w4a8_floatscale_grouped_prepacked(xq, a_scale, packed: PackedExperts
     if out is None:
         out = torch.empty((M, N), dtype=torch.float16, device=xq.device)
     _require(out, torch.float16, (M, N), "out")
-    ws, ws_bytes = _workspace(is_gemm_grouped_prepacked_workspace_bytes(E, M, N, K, group), xq.device, workspace)
+    ws, ws_bytes = _workspace(is_gemm_grouped_prepacked_workspace_bytes, (E, M, N, K, group), xq.device, workspace)
     st = load_library().is_gemm_w4a8_floatscale_grouped_prepacked(
         _p(xq), _p(a_scale), _p(packed.wpack), _p(packed.spack), _p(row_offsets), E, M, N, K, group, _p(out), _p(ws),
         ws_bytes, _stream_handle(stream))
@@ -784,14 +805,14 @@ def is_describe_grouped_prepacked(num_experts: int, M_total: int, N: int, K: int
     return buf.value.decode().split("\n")
 
 
-def _zero_workspace(nbytes: int, device, workspace):
+def _zero_workspace(query, sizes, device, workspace):
     """The prepacked GEMMs want their arrival counters zero: a fresh workspace is zero-filled."""
-    torch = _torch()
     if workspace is not None:
         return workspace, workspace.numel() * workspace.element_size()
+    nbytes = query(*sizes)
     if nbytes == 0:
         return None, 0
-    return torch.zeros((nbytes,), dtype=torch.uint8, device=device), nbytes
+    return _torch().zeros((nbytes,), dtype=_torch().uint8, device=device), nbytes
 
 
 def is_gemm_w4a8_intscale_prepacked(xq, a_scale, packed: PackedWeights, chan_scale, alpha_log2: int, out=None,
@@ -813,7 +834,7 @@ def is_gemm_w4a8_intscale_prepacked(xq, a_scale, packed: PackedWeights, chan_sca
         acc_out = torch.empty((M, N), dtype=torch.int32, device=xq.device)
     if acc_out is not None:
         _require(acc_out, torch.int32, (M, N), "acc_out")
-    ws, ws_bytes = _zero_workspace(is_gemm_prepacked_workspace_bytes(M, N, K, group), xq.device, workspace)
+    ws, ws_bytes = _zero_workspace(is_gemm_prepacked_workspace_bytes, (M, N, K, group), xq.device, workspace)
     st = load_library().is_gemm_w4a8_intscale_prepacked(_p(xq), _p(a_scale), _p(packed.wpack), _p(packed.spack),
                                                        _p(chan_scale), M, N, K, group, alpha_log2, _p(out), _p(acc_out),
                                                        _p(ws), ws_bytes, _stream_handle(stream))
@@ -877,7 +898,7 @@ def is_gemm_w4a8_intscale_gate_up_silu_prepacked(xq, a_scale, gate_up: PackedGat
         acc_out = torch.empty((M, 2 * inter), dtype=torch.int32, device=xq.device)
     if acc_out is not None:
         _require(acc_out, torch.int32, (M, 2 * inter), "acc_out")
-    ws, ws_bytes = _zero_workspace(is_gemm_gate_up_silu_prepacked_workspace_bytes(M, inter, K, packed.group), xq.device,
+    ws, ws_bytes = _zero_workspace(is_gemm_gate_up_silu_prepacked_workspace_bytes, (M, inter, K, packed.group), xq.device,
                                    workspace)
     st = load_library().is_gemm_w4a8_intscale_gate_up_silu_prepacked(
         _p(xq), _p(a_scale), _p(packed.wpack), _p(packed.spack), _p(gate_up.chan_scale), M, inter, K, packed.group,
@@ -899,7 +920,7 @@ def is_gemm_w4a8_floatscale_gate_up_silu_prepacked(xq, a_scale, gate_up: PackedG
     if out is None:
         out = torch.empty((M, inter), dtype=torch.float16, device=xq.device)
     _require(out, torch.float16, (M, inter), "out")
-    ws, ws_bytes = _zero_workspace(is_gemm_gate_up_silu_prepacked_workspace_bytes(M, inter, K, packed.group), xq.device,
+    ws, ws_bytes = _zero_workspace(is_gemm_gate_up_silu_prepacked_workspace_bytes, (M, inter, K, packed.group), xq.device,
                                    workspace)
     st = load_library().is_gemm_w4a8_floatscale_gate_up_silu_prepacked(
         _p(xq), _p(a_scale), _p(packed.wpack), _p(packed.spack), M, inter, K, packed.group, _p(out), _p(ws), ws_bytes,
@@ -1001,7 +1022,7 @@ def is_gemm_w4a8_floatscale_prepacked(xq, a_scale, packed: PackedWeights, out=No
     if out is None:
         out = torch.empty((M, N), dtype=torch.float16, device=xq.device)
     _require(out, torch.float16, (M, N), "out")
-    ws, ws_bytes = _zero_workspace(is_gemm_prepacked_workspace_bytes(M, N, K, group), xq.device, workspace)
+    ws, ws_bytes = _zero_workspace(is_gemm_prepacked_workspace_bytes, (M, N, K, group), xq.device, workspace)
     st = load_library().is_gemm_w4a8_floatscale_prepacked(_p(xq), _p(a_scale), _p(packed.wpack), _p(packed.spack), M, N,
                                                          K, group, _p(out), _p(ws), ws_bytes, _stream_handle(stream))
     _check("is_gemm_w4a8_floatscale_prepacked", st)
@@ -1027,7 +1048,7 @@ def is_linear_w4a8_intscale_prepacked(x, packed: PackedWeights, chan_scale, alph
         acc_out = torch.empty((M, N), dtype=torch.int32, device=x.device)
     if acc_out is not None:
         _require(acc_out, torch.int32, (M, N), "acc_out")
-    ws, ws_bytes = _zero_workspace(is_linear_prepacked_workspace_bytes(M, N, K, group), x.device, workspace)
+    ws, ws_bytes = _zero_workspace(is_linear_prepacked_workspace_bytes, (M, N, K, group), x.device, workspace)
     st = load_library().is_linear_w4a8_intscale_prepacked(_p(x), _p(packed.wpack), _p(packed.spack), _p(chan_scale), M, N,
                                                          K, group, alpha_log2, _p(out), _p(acc_out), _p(ws), ws_bytes,
                                                          _stream_handle(stream))
@@ -1046,7 +1067,7 @@ def is_linear_w4a8_floatscale_prepacked(x, packed: PackedWeights, out=None, work
     if out is None:
         out = torch.empty((M, N), dtype=torch.float16, device=x.device)
     _require(out, torch.float16, (M, N), "out")
-    ws, ws_bytes = _zero_workspace(is_linear_prepacked_workspace_bytes(M, N, K, group), x.device, workspace)
+    ws, ws_bytes = _zero_workspace(is_linear_prepacked_workspace_bytes, (M, N, K, group), x.device, workspace)
     st = load_library().is_linear_w4a8_floatscale_prepacked(_p(x), _p(packed.wpack), _p(packed.spack), M, N, K, group,
                                                            _p(out), _p(ws), ws_bytes, _stream_handle(stream))
     _check("is_linear_w4a8_floatscale_prepacked", st)
