@@ -804,7 +804,7 @@ int is_describe_prepacked(int M, int N, int K, int group, int int_scale, int fp1
     if (shape != IS_OK) return shape;
     if (pk_takes_tile(M, N, K) && takes_wavek(M, N, K)) {
         char name[64];
-        wavek_kernel_name(wavek_plan(M, N), int_scale != 0, false, false, name, sizeof name);
+        wavek_kernel_name(wavek_plan(M, N, K, false), int_scale != 0, false, false, name, sizeof name);
         snprintf(names, names_len, "%s\n%s", prepare_pk_kernel_name(M, fp16_in != 0 && gemm_tile_pk_takes_fp16(K)), name);
         return IS_OK;
     }
@@ -903,7 +903,7 @@ static int gemm_w8_common(const int8_t* xq, const float* a_scale, const int8_t* 
         w.K = K;
         w.group = group;
         w.alpha_log2 = a.alpha_log2;
-        return hip_status(launch_gemm_wavek(w, wavek_plan(M, N), int_scale, true, false, static_cast<hipStream_t>(stream)));
+        return hip_status(launch_gemm_wavek(w, wavek_plan(M, N, K, true), int_scale, true, false, static_cast<hipStream_t>(stream)));
     }
     return hip_status(launch_gemm_w8(a, int_scale, workspace, static_cast<hipStream_t>(stream)));
 }

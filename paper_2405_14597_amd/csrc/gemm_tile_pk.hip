@@ -925,7 +925,7 @@ hipError_t launch_gemm_tile_pk(const PkArgs& a, bool int_scale, void* workspace,
         w.K = a.K;
         w.group = a.group;
         w.alpha_log2 = a.alpha_log2;
-        return launch_gemm_wavek(w, wavek_plan(a.M, a.N), int_scale, false, a.pair != 0, stream);
+        return launch_gemm_wavek(w, wavek_plan(a.M, a.N, a.K, false), int_scale, false, a.pair != 0, stream);
     }
     const size_t smem = 2 * (size_t)stage_bytes(kMS);
     const int tiles = sp.whole + sp.rem * sp.parts;  // workgroups

@@ -32,6 +32,7 @@
 // 32.9 -> 12.6 us, 300 x 4096 x 4096 36.4 -> 19.5 us, 512 x 6144 x 4096 42.2 -> 28.5 us, 300 x 28672 x 4096 72.9 -> 63.0 us,
 // 128 x 4096 x 14336 46.2 -> 25.0 us; W8A8 300 x 4096 x 14336 126.4 -> 55.9 us, 1024 x 4096 x 14336 129 -> 103 us;
 // W4A8 1024 x 28672 x 4096 147 against 181 us (stays on the tiled kernel).
+#include <math.h>
 #include <stdio.h>
 
 #include <algorithm>
@@ -54,8 +55,12 @@ constexpr int kGroupRows = 8;         // tile rows of the block of tiles an XCD 
 constexpr int kPitch = kTN + 8;       // halves per row of the output tile in LDS
 
 constexpr int kStage8 = kTN * 128;    // int8 weights of one K step
+// Token sub-tiles whose partial sums pass through LDS at a time: all of them up to 64 rows; all five of 80 would need 160 KB with
+// eight waves, and with four leave no room for the second workgroup on the unit
+constexpr int rows_at_once(int MS, int W) { return W * MS * kNS > 16 * W ? (MS + 1) / 2 : MS; }
+constexpr size_t sums_bytes(int MS, int W) { return (size_t)W * rows_at_once(MS, W) * kNS * 1024; }
 constexpr size_t lds_bytes(int MS, int W, bool W8) {
-    const size_t sums = (size_t)W * MS * kNS * 1024 + (size_t)MS * 16 * kPitch * 2, stages = W8 ? (size_t)W * 2 * kStage8 : 0;
+    const size_t sums = sums_bytes(MS, W) + (size_t)MS * 16 * kPitch * 2, stages = W8 ? (size_t)W * 2 * kStage8 : 0;
     return sums > stages ? sums : stages;
 }
 
@@ -282,77 +287,84 @@ __device__ __forceinline__ void wavek_tile(const WavekArgs& a, unsigned char* sm
     // ---- the waves' partial tiles meet in LDS: [wave][sub-tile i][j][lane][4 rows], 16 bytes a lane, no bank conflicts.
     // Units of one token sub-tile and two weight sub-tiles are dealt to the waves, which add them in wave order.
     v4i_t* parts = reinterpret_cast<v4i_t*>(smem);
-    __half* otile = reinterpret_cast<__half*>(smem + (size_t)W * MS * kNS * 1024);
-#pragma unroll
-    for (int i = 0; i < MS; ++i)
-#pragma unroll
-        for (int j = 0; j < kNS; ++j) {
-            v4i_t o;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                if constexpr (INT_SCALE) o[r] = acc[i][j][r];
-                else o[r] = __float_as_int(acc[i][j][r]);
-            }
-            parts[((wave * MS + i) * kNS + j) * kWave + lane] = o;
-        }
-    __syncthreads();
+    __half* otile = reinterpret_cast<__half*>(smem + sums_bytes(MS, W));
+    constexpr int IC = rows_at_once(MS, W);
     const float inv_alpha = __int_as_float((127 - a.alpha_log2) << 23);
-    constexpr int kUnits = MS * kNS / 2;
 #pragma unroll
-    for (int u0 = 0; u0 < kUnits; u0 += W) {
-        const int u = u0 + wave;  // (uniform over the wave)
-        if (u >= kUnits) break;
-        const int i = u / (kNS / 2), jp = u - i * (kNS / 2);
-        acc4 v[2];
-        float c[2], sa[4];
+    for (int i0 = 0; i0 < MS; i0 += IC) {
+        if (i0 > 0) __syncthreads();
 #pragma unroll
-        for (int r = 0; r < 4; ++r) sa[r] = a.a_scale[min(m0 + 16 * i + 4 * kb + r, a.M - 1)];
+        for (int ii = 0; ii < IC; ++ii)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int nl = (2 * jp + j) * 16 + li;
-            c[j] = 1.0f;
-            if constexpr (INT_SCALE) {
-                if (a.chan_scale) c[j] = a.chan_scale[min(n0 + nl, a.N - 1)];
-                c[j] *= inv_alpha;
-            }
-            v4i_t got[W];
+            for (int j = 0; j < kNS; ++j) {
+                if (i0 + ii >= MS) continue;
+                v4i_t o;
 #pragma unroll
-            for (int w = 0; w < W; ++w) got[w] = parts[((w * MS + i) * kNS + 2 * jp + j) * kWave + lane];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                if constexpr (INT_SCALE) {
-                    v[j][r] = got[0][r];
-#pragma unroll
-                    for (int w = 1; w < W; ++w) v[j][r] += got[w][r];
-                } else {
-                    v[j][r] = __int_as_float(got[0][r]);
-#pragma unroll
-                    for (int w = 1; w < W; ++w) v[j][r] += __int_as_float(got[w][r]);
+                for (int r = 0; r < 4; ++r) {
+                    if constexpr (INT_SCALE) o[r] = acc[(i0 + ii) % MS][j][r];
+                    else o[r] = __float_as_int(acc[(i0 + ii) % MS][j][r]);
                 }
+                parts[((wave * IC + ii) * kNS + j) * kWave + lane] = o;
             }
-            if constexpr (INT_SCALE) {
-                if (a.acc_out) {
+        __syncthreads();
+        constexpr int kUnits = IC * kNS / 2;
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int ml = 16 * i + 4 * kb + r;
-                        if (ml < m_rows && nl < n_rows) a.acc_out[(size_t)(m0 + ml) * a.N + n0 + nl] = v[j][r];
+        for (int u0 = 0; u0 < kUnits; u0 += W) {
+            const int u = u0 + wave;  // (uniform over the wave)
+            if (u >= kUnits) break;
+            const int ii = u / (kNS / 2), jp = u - ii * (kNS / 2), i = i0 + ii;
+            if (i >= MS) break;
+            acc4 v[2];
+            float c[2], sa[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) sa[r] = a.a_scale[min(m0 + 16 * i + 4 * kb + r, a.M - 1)];
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int nl = (2 * jp + j) * 16 + li;
+                c[j] = 1.0f;
+                if constexpr (INT_SCALE) {
+                    if (a.chan_scale) c[j] = a.chan_scale[min(n0 + nl, a.N - 1)];
+                    c[j] *= inv_alpha;
+                }
+                v4i_t got[W];
+#pragma unroll
+                for (int w = 0; w < W; ++w) got[w] = parts[((w * IC + ii) * kNS + 2 * jp + j) * kWave + lane];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    if constexpr (INT_SCALE) {
+                        v[j][r] = got[0][r];
+#pragma unroll
+                        for (int w = 1; w < W; ++w) v[j][r] += got[w][r];
+                    } else {
+                        v[j][r] = __int_as_float(got[0][r]);
+#pragma unroll
+                        for (int w = 1; w < W; ++w) v[j][r] += __int_as_float(got[w][r]);
+                    }
+                }
+                if constexpr (INT_SCALE) {
+                    if (a.acc_out) {
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const int ml = 16 * i + 4 * kb + r;
+                            if (ml < m_rows && nl < n_rows) a.acc_out[(size_t)(m0 + ml) * a.N + n0 + nl] = v[j][r];
+                        }
                     }
                 }
             }
-        }
-        // FLOAT(acc) * s_a[m] * c[n] / alpha (Eq. (2)), or facc * s_a[m] (Eq. (1))
-        auto result = [&](int j, int r) {
-            if constexpr (INT_SCALE) return __float2half_rn((float)v[j][r] * sa[r] * c[j]);
-            else return __float2half_rn(v[j][r] * sa[r]);
-        };
+            // FLOAT(acc) * s_a[m] * c[n] / alpha (Eq. (2)), or facc * s_a[m] (Eq. (1))
+            auto result = [&](int j, int r) {
+                if constexpr (INT_SCALE) return __float2half_rn((float)v[j][r] * sa[r] * c[j]);
+                else return __float2half_rn(v[j][r] * sa[r]);
+            };
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            __half* row = otile + (16 * i + 4 * kb + r) * kPitch;
-            if constexpr (SILU) {  // the two weight sub-tiles are the gate and up rows of the same 16 outputs
-                row[jp * 16 + li] = __float2half_rn(silu_mul(__half2float(result(0, r)), __half2float(result(1, r))));
-            } else {
-                row[2 * jp * 16 + li] = result(0, r);
-                row[(2 * jp + 1) * 16 + li] = result(1, r);
+            for (int r = 0; r < 4; ++r) {
+                __half* row = otile + (16 * i + 4 * kb + r) * kPitch;
+                if constexpr (SILU) {  // the two weight sub-tiles are the gate and up rows of the same 16 outputs
+                    row[jp * 16 + li] = __float2half_rn(silu_mul(__half2float(result(0, r)), __half2float(result(1, r))));
+                } else {
+                    row[2 * jp * 16 + li] = result(0, r);
+                    row[(2 * jp + 1) * 16 + li] = result(1, r);
+                }
             }
         }
     }
@@ -401,51 +413,87 @@ hipError_t launch_instance(const WavekArgs& a, hipStream_t stream) {
 
 template <bool INT_SCALE, bool W8, bool SILU>
 hipError_t launch_shape(const WavekArgs& a, const WavekPlan& p, hipStream_t stream) {
+    if (p.ms == 5) return p.waves == 8 ? launch_instance<INT_SCALE, W8, 5, 8, SILU>(a, stream) : launch_instance<INT_SCALE, W8, 5, 4, SILU>(a, stream);
     if (p.ms == 3) return p.waves == 8 ? launch_instance<INT_SCALE, W8, 3, 8, SILU>(a, stream) : launch_instance<INT_SCALE, W8, 3, 4, SILU>(a, stream);
     return p.waves == 8 ? launch_instance<INT_SCALE, W8, 4, 8, SILU>(a, stream) : launch_instance<INT_SCALE, W8, 4, 4, SILU>(a, stream);
 }
 
 }  // namespace
 
-WavekPlan wavek_plan(int M, int N) {
+// A call's time with row tiles of 16 ms rows and workgroups of `waves`, in microseconds: launches, preparation and the like; per workgroup
+// of a compute unit (four waves: two of them at a time) its start and end, and per K step of a wave a share by rows, with the SIMD to
+// itself or shared; the weights' way from memory.  Fits of 96 calls with int4 and 60 with int8 weights, each with six plans (65 to 1000
+// rows, 2048 to 28672 columns, K 4096 to 28672): 3 and 6 % off, and the best plan by them costs 0.4 and 0.5 % on average, 7 and 10 %
+// at most.
+static double wavek_us(int M, int N, int K, bool w8, int ms, int waves) {
+    struct Fit {
+        double call, end, end_rows, both, both_rows, alone, alone_rows, weights;
+    };
+    constexpr Fit kInt4{6.7, 0.88, 0.53, 0.23, 0.23, 0.27, 0.089, 0.0063}, kInt8{4.3, 0.65, 1.1, 0.93, 0.15, 0.77, 0.013, 0.13};
+    const Fit& f = w8 ? kInt8 : kInt4;
+    const long long tiles = (long long)((N + kTN - 1) / kTN) * ((M + ms * 16 - 1) / (ms * 16));
+    const double per_cu = (double)((tiles + cu_count() - 1) / cu_count()), run = ((K >> 7) + waves - 1) / waves;
+    const double ends = f.end + f.end_rows * ms, both = ends + run * (f.both + f.both_rows * ms), alone = ends + run * (f.alone + f.alone_rows * ms);
+    const double pairs = floor(per_cu / 2);
+    return f.call + (waves == 8 ? per_cu * both : pairs * both + (per_cu - 2 * pairs) * alone) + f.weights * 1e-6 * N * (double)K;
+}
+
+WavekPlan wavek_plan(int M, int N, int K, bool w8) {
     WavekPlan p;
+    const auto tiles = [&](int ms) { return (long long)((N + kTN - 1) / kTN) * ((M + ms * 16 - 1) / (ms * 16)); };
     // row tiles of 48 or 64 rows, whichever pads less
     const int m16 = (M + 15) / 16;
     p.ms = (m16 + 2) / 3 * 3 < (m16 + 3) / 4 * 4 ? 3 : 4;
-    p.tiles = (long long)((N + kTN - 1) / kTN) * ((M + p.ms * 16 - 1) / (p.ms * 16));
+    p.tiles = tiles(p.ms);
     // Eight waves where workgroups of four would leave every compute unit with one wave per SIMD at most (65 x 4096 x 14336:
     // 22.1 against 24.0 us); two workgroups of four share a unit otherwise, one's start and end under the other's K loop.
     p.waves = p.tiles <= cu_count() ? 8 : 4;
+    // Long runs and more than a few tiles: by time, and tiles of 80 rows too.  What decides is how the tiles fill the units (300 x 4096: 320
+    // tiles of 64 rows give a quarter of the 256 units two, 256 tiles of 80 rows give each one): W8A8 300 x 4096 x 14336 54.6 -> 42.4 us,
+    // 400 rows 87 -> 53, 1024 rows 128 -> 111; int4 weights 300 x 4096 x 14336 41.9 -> 32.4, 200 rows 49.9 (tiled kernel) -> 27.8.
+    if (K >= 2048 && p.tiles >= cu_count() / 8) {
+        double best = 0.0;
+        for (int ms = 3; ms <= 5; ++ms)
+            for (int waves = 4; waves <= 8; waves += 4) {
+                const double us = wavek_us(M, N, K, w8, ms, waves);
+                if (best == 0.0 || us < best) {
+                    best = us;
+                    p.ms = ms;
+                    p.waves = waves;
+                }
+            }
+        p.tiles = tiles(p.ms);
+    }
     return p;
 }
 
-// Both kernels' times from what bounds them, in microseconds; the constants are fits, checked on 1482 calls with int4 weights (65 to
-// 8192 rows, 200 to 65536 columns, K 128 to 28672, integer and float scales), on which the wrong choice of this kernel costs 6 %
-// at most.
-// This kernel: 10 us of launches, preparation, start and end, and 0.76 us per K step of a wave on every SIMD (for 12 KB of
-// operands; 10 KB with 48 rows).  The tiled kernel: 6 us, 2.3 us per K step for a round of two tiles per unit (1.56 when a
-// unit has one, 1.31 of a long K range: 1024 x 8192 x 28672 286 us there, 313 us here), and 14 us more to pass the partial tiles
-// of a cut K range through memory.  With one full round of the tiled kernel or more there are sixteen rounds of tiles here, and
-// their starts and ends, which these times leave out, add up (540 x 53283 x 1536 97 us there, 108 us here; 4096 x 4608 x 2304 73
-// and 79 us; the best of such calls here is 3 % ahead).
-// With int8 weights: 16 KB of operands (14 KB) here; the tiled kernel of that recipe works on one tile per unit at a time, 1.03 us
-// per K step, behind 9.5 us of launches and scale transposition.  There the ends decide short K ranges, 2 us a round here and
-// 10 us a tile there: 4096 x 4096 x 128 38 us here and 30 us there, 1109 x 719 x 384 11 and 20 us.  Checked on 864 calls: the
-// wrong choice costs 8 % at most, the choice without the ends up to 54 %.
+// This kernel's time against the tiled kernel's, in microseconds.  The tiled kernel with int4 weights: 20 us and 1.15 us per K step where a
+// unit has one of its tiles at most (702 x 9559 x 2816 46 us, 1024 x 8192 x 8192 86, 512 x 16384 x 14336 144, 1024 x 8192 x 28672 286),
+// 22 us and 1.62 us per step for two (762 x 12009 x 2048 50 us, 1000 x 12288 x 4096 72, 1000 x 10240 x 8192 124), and for few tiles, whose
+// K range it cuts, 20 us to pass partial tiles through memory.  With one full round of the tiled kernel or more there are sixteen
+// rounds of tiles here, and their starts and ends add up (540 x 53283 x 1536 97 us there, 108 us here; 4096 x 4608 x 2304 73 and 79 us; the
+// best of such calls here is 3 % ahead).  4 % to spare with int4 weights: the long runs of large calls are slower than the fit says (1024 x 8192 x 28672
+// 313 us here).
+// With int8 weights the tiled kernel works on one tile per unit at a time, 1.03 us per K step, behind 9.5 us of launches and scale
+// transposition; there the ends decide short K ranges, 2 us a round here and 10 us a tile there: 4096 x 4096 x 128 38 us here and 30 us there,
+// 1109 x 719 x 384 11 and 20 us, 504 x 18148 x 1664 50 and 57 us; wide matrices are faster here than the fit says (104 x 24840 x 3712 46 and
+// 54 us).
 bool wavek_is_faster(int M, int N, int K, bool w8) {
     const int steps = K >> 7, cus = cu_count();
-    const WavekPlan p = wavek_plan(M, N);
-    const long long tiles = (long long)((N + 255) / 256) * ((M + 127) / 128), here_rounds = (p.tiles + cus - 1) / cus;
+    const WavekPlan p = wavek_plan(M, N, K, w8);
+    const long long tiles = (long long)((N + 255) / 256) * ((M + 127) / 128);
+    double here = (w8 ? 0.95 : 1.04) * wavek_us(M, N, K, w8, p.ms, p.waves);
     if (w8) {
-        const double filled = std::max(1.0, 0.5 * ((double)here_rounds + (double)p.tiles / cus));
-        const double here = 8.0 + filled * (2.0 + 0.72 * 0.25 * steps * (2 * p.ms + 8) / 12.0);
+        if (steps < 16) {  // (runs of a few steps a wave: by steps, not by the longest wave's)
+            const double filled = std::max(1.0, 0.5 * ((double)((p.tiles + cus - 1) / cus) + (double)p.tiles / cus));
+            here = 8.0 + filled * (2.0 + 0.72 * 0.25 * steps * (2 * p.ms + 8) / 12.0);
+        }
         return here < 9.5 + (double)((tiles + cus - 1) / cus) * (10.0 + 1.03 * steps);
     }
-    const double here = 10.0 + 0.76 * 0.25 * (double)here_rounds * steps * (2 * p.ms + 4) / 12.0;
     if (tiles >= 2 * cus) return false;
-    if (tiles > cus) return here < 6.0 + 2.3 * steps;
+    if (tiles > cus) return here < 22.0 + 1.62 * steps;
     const int parts = std::min(std::min(cus / (int)tiles, 8), std::max(steps / 8, 1));
-    return here < 6.0 + (parts > 1 ? 1.56 * steps / parts + 14.0 : std::min(1.56 * steps, 25.0 + 1.31 * steps));
+    return here < 20.0 + (parts > 1 ? 1.56 * steps / parts : 1.15 * steps);
 }
 
 void wavek_kernel_name(const WavekPlan& p, bool int_scale, bool w8, bool silu, char* buf, size_t len) {
