@@ -76,9 +76,10 @@ bool pk_takes_tile(int M, int N, int K) {
 }
 
 // Which of the others the kernel takes whose waves split K over the canonical activations (gemm_few_pk.hip): those of 2 to 64
-// rows.  One row stays on the weight-streaming kernel, whose scale step works on the one result register that carries it and which
-// quantises an fp16 token itself (on 60 calls of one row the two are within -10 and +6 % of each other, 3 % on average).
-bool takes_few(int M) { return M >= 2 && M <= 64; }
+// rows, and of quantised single rows those with K < 12288: there it is 5 % ahead of the weight-streaming kernel on average (6144 x 4096 6.0
+// -> 5.5 us, 4096 x 11008 7.6 -> 7.1, 14069 x 10880 23.4 -> 17.6, 57344 x 8192 49.0 -> 44.9; 8192 x 8192 9.0 -> 9.2), beyond it up to 6 %
+// behind (5673 x 12416 10.5 and 11.1 us, 3408 x 19328 9.5 and 10.1).  An fp16 row is quantised inside the weight-streaming kernel.
+bool takes_few(int M, int K) { return M >= 2 ? M <= 64 : M == 1 && K < 12288; }
 
 bool wants_prefill(int M, int num_experts, int group) {
     return !general_forced() && !gemm_small_group_covers(group) && M > 64 * num_experts;
@@ -490,7 +491,7 @@ static int gemm_pk_common(const int8_t* xq, const void* x_fp16, const float* a_s
     a.group = group;
     a.alpha_log2 = int_scale ? alpha_log2 : 0;
     a.pair = (pair && tiled) ? 1 : 0;  // (the fused epilogue is the tiled kernel's)
-    if (!tiled && takes_few(M)) {
+    if (!tiled && x_fp16 == nullptr && takes_few(M, K)) {
         FewArgs f;
         f.xq = xq;
         f.a_scale = a_scale;
@@ -579,7 +580,7 @@ static int gate_up_silu_common(const int8_t* xq, const float* a_scale, const voi
     if (!ok_ptr(out_fp16)) return IS_ERR_INVALID_ARG;
     const size_t gemm = pad_256(is_gemm_prepacked_workspace_bytes(M, N, K, group));
     __half* gu = reinterpret_cast<__half*>(static_cast<unsigned char*>(workspace) + gemm);
-    if (takes_few(M))  // SiLU * up as that kernel's epilogue: the [M, 2 inter] tensor's place stays unused
+    if (takes_few(M, K))  // SiLU * up as that kernel's epilogue: the [M, 2 inter] tensor's place stays unused
         return gemm_pk_common(xq, nullptr, a_scale, nullptr, wpack, spack, chan_scale_packed, M, N, K, group, alpha_log2, out_fp16,
                               acc_out, workspace, gemm, stream, int_scale, false, true);
     const int st = gemm_pk_common(xq, nullptr, a_scale, nullptr, wpack, spack, chan_scale_packed, M, N, K, group,
@@ -813,12 +814,12 @@ int is_describe_prepacked(int M, int N, int K, int group, int int_scale, int fp1
         return IS_OK;
     }
     PkPlan plan;
-    if (takes_few(M)) {
+    const bool fused = fp16_in != 0 && M == 1 && pk_decode_plan(1, N, K, group, true, &plan);
+    if (!fused && takes_few(M, K)) {
         if (!pk_decode_plan(M, N, K, group, false, &plan)) return IS_ERR_UNSUPPORTED;
         few_kernel_name(few_plan(M, N, K, false), int_scale != 0, false, names, names_len);
         return IS_OK;
     }
-    const bool fused = fp16_in != 0 && M == 1 && pk_decode_plan(1, N, K, group, true, &plan);
     if (!fused && !pk_decode_plan(M, N, K, group, false, &plan)) return IS_ERR_UNSUPPORTED;
     pk_decode_kernel_name(plan, int_scale != 0, fused, names, names_len);
     return IS_OK;
