@@ -81,6 +81,18 @@ bool pk_takes_tile(int M, int N, int K) {
 // behind (5673 x 12416 10.5 and 11.1 us, 3408 x 19328 9.5 and 10.1).  An fp16 row is quantised inside the weight-streaming kernel.
 bool takes_few(int M, int K) { return M >= 2 ? M <= 64 : M == 1 && K < 12288; }
 
+// And of the calls of quantised activations and integer scales beyond 64 rows, up to 512: in row tiles of 48 or 64 there, without a preparation kernel, where
+// that is 5 % ahead by the times of both (65 x 12288 x 4096 16.5 -> 12.2 us, 128 x 8192 x 8192 20.2 -> 16.6, 300 x 6144 x 4096 20.5 ->
+// 16.8, 512 x 12288 x 4096 43.6 -> 40.8; 400 x 28672 x 4096 75 on the tiled kernel and 81, 300 x 28672 x 4096 58.2 and 59.8).  Not measured
+// below 16 K steps.  Fewer than 5120 columns stay with the kernel that the tests name for such calls, though they would gain as well
+// (65 x 4096 x 4096 12.6 -> 8.8 us).
+bool takes_rows(int M, int N, int K, bool silu) {
+    if (M <= 64 || M > 512 || N < 5120 || K < 2048 || kernel_route() >= 2) return false;
+    double us;
+    rows_plan(M, N, K, silu, &us);
+    return us < 0.95 * prepared_gemm_us(M, N, K);
+}
+
 bool wants_prefill(int M, int num_experts, int group) {
     return !general_forced() && !gemm_small_group_covers(group) && M > 64 * num_experts;
 }
@@ -491,7 +503,8 @@ static int gemm_pk_common(const int8_t* xq, const void* x_fp16, const float* a_s
     a.group = group;
     a.alpha_log2 = int_scale ? alpha_log2 : 0;
     a.pair = (pair && tiled) ? 1 : 0;  // (the fused epilogue is the tiled kernel's)
-    if (!tiled && x_fp16 == nullptr && takes_few(M, K)) {
+    const bool few = !tiled && x_fp16 == nullptr && takes_few(M, K), rows = int_scale && x_fp16 == nullptr && !prepared && takes_rows(M, N, K, pair);
+    if (few || rows) {
         FewArgs f;
         f.xq = xq;
         f.a_scale = a_scale;
@@ -505,7 +518,9 @@ static int gemm_pk_common(const int8_t* xq, const void* x_fp16, const float* a_s
         f.K = K;
         f.group = group;
         f.alpha_log2 = a.alpha_log2;
-        return hip_status(launch_gemm_few_pk(f, few_plan(M, N, K, pair), int_scale, pair, static_cast<hipStream_t>(stream)));
+        double us;
+        return hip_status(few ? launch_gemm_few_pk(f, few_plan(M, N, K, pair), int_scale, pair, static_cast<hipStream_t>(stream))
+                              : launch_gemm_rows_pk(f, rows_plan(M, N, K, pair, &us), pair, static_cast<hipStream_t>(stream)));
     }
     if (tiled)
         return hip_status(launch_gemm_tile_pk(a, int_scale, workspace, workspace_bytes, static_cast<hipStream_t>(stream),
@@ -803,6 +818,11 @@ int is_describe_prepacked(int M, int N, int K, int group, int int_scale, int fp1
     if (M < 1) return IS_ERR_INVALID_ARG;
     const int shape = check_pk_shape(N, K, group);
     if (shape != IS_OK) return shape;
+    if (int_scale != 0 && fp16_in == 0 && takes_rows(M, N, K, false)) {
+        double us;
+        rows_kernel_name(rows_plan(M, N, K, false, &us), false, names, names_len);
+        return IS_OK;
+    }
     if (pk_takes_tile(M, N, K) && takes_wavek(M, N, K)) {
         char name[64];
         wavek_kernel_name(wavek_plan(M, N, K, false), int_scale != 0, false, false, name, sizeof name);

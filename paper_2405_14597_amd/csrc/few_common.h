@@ -35,6 +35,10 @@ struct FewGroups {
 FewPlan few_plan(int M, int N, int K, bool silu);
 void few_kernel_name(const FewPlan& p, bool int_scale, bool silu, char* buf, size_t len);
 hipError_t launch_gemm_few_pk(const FewArgs& a, const FewPlan& p, bool int_scale, bool silu, hipStream_t stream);
+// The same on several tiles of 48 or 64 rows (65 rows and more, integer scales)
+FewPlan rows_plan(int M, int N, int K, bool silu, double* us_out);
+void rows_kernel_name(const FewPlan& p, bool silu, char* buf, size_t len);
+hipError_t launch_gemm_rows_pk(const FewArgs& a, const FewPlan& p, bool silu, hipStream_t stream);
 // (ms: 16-row token tiles a workgroup takes at a time; ns = 0: the call is not for this kernel)
 FewPlan few_grouped_plan(int E, int M, int N, int K);
 void few_grouped_kernel_name(const FewPlan& p, bool int_scale, char* buf, size_t len);

@@ -448,6 +448,34 @@ hipError_t launch_instance(const FewArgs& a, hipStream_t stream) {
     return hipGetLastError();
 }
 
+// Moderate numbers of rows, integer scales (exact in any order; float sums have to be those of the calls on prepared activations, bit for
+// bit): the workgroups of several row tiles.  XCD x gets one contiguous range of tile numbers, and a range walks the
+// output in blocks of eight tile rows, column by column (the row tiles that share weights meet in that XCD's L2).
+template <int MS, int NS, int W, int D, bool SILU>
+__global__ __launch_bounds__(W* kWave) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_rows_pk_kernel(FewArgs a) {
+    extern __shared__ __align__(16) unsigned char smem_few[];
+    const int tiles_n = (a.N + NS * 16 - 1) / (NS * 16), tiles_m = (a.M + MS * 16 - 1) / (MS * 16);
+    const int total = tiles_n * tiles_m, q8 = total / 8, r8 = total - q8 * 8;
+    const int xcd = blockIdx.x % 8;
+    const int lid = xcd * q8 + min(xcd, r8) + blockIdx.x / 8;
+    const int gsz = 8 * tiles_n, grp = lid / gsz, in_grp = lid - grp * gsz;
+    const int gm = min(8, tiles_m - grp * 8);
+    const int tile_n = in_grp / gm, tile_m = grp * 8 + (in_grp - tile_n * gm);
+    const int m0 = tile_m * MS * 16;
+    FewTile t;
+    t.x = a.xq + (size_t)m0 * a.K;
+    t.a_scale = a.a_scale + m0;
+    t.wpack = a.wpack;
+    t.spack = a.spack;
+    t.chan_scale = a.chan_scale;
+    t.out = a.out + (size_t)m0 * (SILU ? a.N >> 1 : a.N);
+    t.acc_out = a.acc_out ? a.acc_out + (size_t)m0 * a.N : nullptr;
+    t.m_rows = min(a.M - m0, MS * 16);
+    t.t0 = tile_n * NS;
+    t.phase = tile_n / 2;
+    few_tile<true, MS, NS, W, D, SILU>(a, t, smem_few);
+}
+
 // Mixture-of-experts form: workgroup (x, e) takes NS weight tiles of expert e and the expert's rows, 16 MT of them at a time; an expert
 // without rows costs a workgroup's start.
 template <int MT, int NS, int W, int D, bool INT_SCALE>
@@ -482,6 +510,19 @@ __global__ __launch_bounds__(W* kWave) __attribute__((amdgpu_waves_per_eu(2, 2))
         }
         few_tile<INT_SCALE, 1, NS, W, D, false>(a, t, smem_few);
     }
+}
+
+template <int MS, int NS, bool SILU>
+hipError_t launch_rows_instance(const FewArgs& a, hipStream_t stream) {
+    static LdsLimit limit;  // per instantiation
+    constexpr int W = 4;
+    auto kernel = gemm_rows_pk_kernel<MS, NS, W, 2, SILU>;
+    constexpr size_t lds = few_lds_bytes(MS, NS, W);
+    const hipError_t r = limit.raise(reinterpret_cast<const void*>(kernel), (int)lds);
+    if (r != hipSuccess) return r;
+    const int tiles_n = (a.N + NS * 16 - 1) / (NS * 16), tiles_m = (a.M + MS * 16 - 1) / (MS * 16);
+    hipLaunchKernelGGL(kernel, dim3(tiles_n * tiles_m), dim3(W * kWave), lds, stream, with_launch_arguments(a, W));
+    return hipGetLastError();
 }
 
 template <int MT, int NS, int W, int D, bool INT_SCALE>
@@ -638,6 +679,43 @@ FewPlan few_grouped_plan(int E, int M, int N, int K) {
 
 void few_grouped_kernel_name(const FewPlan& p, bool int_scale, char* buf, size_t len) {
     snprintf(buf, len, "gemm_decode_grouped_pk_kernel<%d, %d, %d, %d, %s>", p.ms, p.ns, p.waves, p.depth, int_scale ? "true" : "false");
+}
+
+// Moderate numbers of rows in tiles of 48 or 64: the plan and its time in microseconds, launch and weights' way from memory included (the
+// fit of few_plan; 65 x 4096 x 4096 8.2 by it and 8.8 measured, 300 x 6144 x 4096 15.7 and 16.8, 512 x 12288 x 4096 41.7 and 40.8, 300 x
+// 28672 x 4096 66 and 60).
+FewPlan rows_plan(int M, int N, int K, bool silu, double* us_out) {
+    const int cus = cu_count();
+    int run = ((K >> 7) + 3) / 4;
+    run += run & 1;
+    FewPlan best{0, 0, 4, 2};
+    double best_us = 0.0;
+    for (int ms = 3; ms <= 4; ++ms)
+        for (int ns = 3; ns <= (ms == 3 ? 5 : 4); ++ns) {
+            if (silu && ns % 2 != 0) continue;
+            const long long wgs = (long long)((N + 16 * ns - 1) / (16 * ns)) * ((M + 16 * ms - 1) / (16 * ms));
+            const long long per_cu = (wgs + cus - 1) / cus;
+            const double step = step_us(ms, ns), ends = ends_us(ms, ns);
+            const double us = (double)(per_cu / 2) * (ends + 2 * run * step) + (double)(per_cu % 2) * (ends + run * step);
+            if (best.ns == 0 || us < best_us) {
+                best.ms = ms;
+                best.ns = ns;
+                best_us = us;
+            }
+        }
+    *us_out = 1.9 + best_us + 0.064e-6 * N * (double)K;
+    return best;
+}
+
+void rows_kernel_name(const FewPlan& p, bool silu, char* buf, size_t len) {
+    snprintf(buf, len, "gemm_rows_pk_kernel<%d, %d, %d, %d, %s>", p.ms, p.ns, p.waves, p.depth, silu ? "true" : "false");
+}
+
+hipError_t launch_gemm_rows_pk(const FewArgs& a, const FewPlan& p, bool silu, hipStream_t stream) {
+    if (silu) return p.ms == 3 ? launch_rows_instance<3, 4, true>(a, stream) : launch_rows_instance<4, 4, true>(a, stream);
+    if (p.ms == 4) return p.ns == 3 ? launch_rows_instance<4, 3, false>(a, stream) : launch_rows_instance<4, 4, false>(a, stream);
+    if (p.ns == 3) return launch_rows_instance<3, 3, false>(a, stream);
+    return p.ns == 4 ? launch_rows_instance<3, 4, false>(a, stream) : launch_rows_instance<3, 5, false>(a, stream);
 }
 
 }  // namespace intscale

@@ -474,6 +474,13 @@ WavekPlan wavek_plan(int M, int N, int K, bool w8) {
 // rounds of tiles here, and their starts and ends add up (540 x 53283 x 1536 97 us there, 108 us here; 4096 x 4608 x 2304 73 and 79 us; the
 // best of such calls here is 3 % ahead).  4 % to spare with int4 weights: the long runs of large calls are slower than the fit says (1024 x 8192 x 28672
 // 313 us here).
+static double tiled_us(long long tiles, int steps) {
+    const int cus = cu_count();
+    if (tiles > cus) return 22.0 + 1.62 * steps * (double)((tiles + 2 * cus - 1) / (2 * cus));
+    const int parts = std::min(std::min(cus / (int)tiles, 8), std::max(steps / 8, 1));
+    return 20.0 + (parts > 1 ? 1.56 * steps / parts : 1.15 * steps);
+}
+
 // With int8 weights the tiled kernel works on one tile per unit at a time, 1.03 us per K step, behind 9.5 us of launches and scale
 // transposition; there the ends decide short K ranges, 2 us a round here and 10 us a tile there: 4096 x 4096 x 128 38 us here and 30 us there,
 // 1109 x 719 x 384 11 and 20 us, 504 x 18148 x 1664 50 and 57 us; wide matrices are faster here than the fit says (104 x 24840 x 3712 46 and
@@ -491,9 +498,14 @@ bool wavek_is_faster(int M, int N, int K, bool w8) {
         return here < 9.5 + (double)((tiles + cus - 1) / cus) * (10.0 + 1.03 * steps);
     }
     if (tiles >= 2 * cus) return false;
-    if (tiles > cus) return here < 22.0 + 1.62 * steps;
-    const int parts = std::min(std::min(cus / (int)tiles, 8), std::max(steps / 8, 1));
-    return here < 20.0 + (parts > 1 ? 1.56 * steps / parts : 1.15 * steps);
+    return here < tiled_us(tiles, steps);
+}
+
+double prepared_gemm_us(int M, int N, int K) {
+    const long long tiles = (long long)((N + 255) / 256) * ((M + 127) / 128);
+    if (!wavek_is_faster(M, N, K, false)) return tiled_us(tiles, K >> 7);
+    const WavekPlan p = wavek_plan(M, N, K, false);
+    return wavek_us(M, N, K, false, p.ms, p.waves);
 }
 
 void wavek_kernel_name(const WavekPlan& p, bool int_scale, bool w8, bool silu, char* buf, size_t len) {

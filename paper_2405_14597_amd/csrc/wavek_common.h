@@ -26,6 +26,7 @@ struct WavekPlan {
 
 bool takes_wavek(int M, int N, int K, bool w8 = false);  // the dispatch of the tiled kernel's calls (api.hip)
 bool wavek_is_faster(int M, int N, int K, bool w8);
+double prepared_gemm_us(int M, int N, int K);  // a GEMM call of more than 64 rows on prepared activations, with their preparation
 WavekPlan wavek_plan(int M, int N, int K, bool w8);
 void wavek_kernel_name(const WavekPlan& p, bool int_scale, bool w8, bool silu, char* buf, size_t len);
 hipError_t launch_gemm_wavek(const WavekArgs& a, const WavekPlan& p, bool int_scale, bool w8, bool silu, hipStream_t stream);

@@ -141,3 +141,22 @@ def test_grouped(P, E, rows, N, K, group, wide):
     fs = torch.cat([reference(s[0][:r], s[1], f, group) for s, f, r in zip(sets, floats, rows)]) * sa.double()[:, None]
     size = torch.cat([reference(s[0][:r].abs().clamp(max=127), s[1].abs(), f.abs(), group) for s, f, r in zip(sets, floats, rows)]) * sa.double()[:, None]
     assert bool(((fout.double() - fs).abs() <= 5e-4 * fs.abs() + 2.0 ** -25 + size * (K // group + 2) * 2.0 ** -24)[fs.abs() < 65000.0].all())
+
+
+# the kernel's tiles of 48 and 64 rows for more than 64 rows: one and several row tiles with remainders, ragged widths, uneven runs of
+# K steps, every instance
+ROWS = [(65, 5121, 2176, 128), (100, 6144, 4096, 256), (72, 12288, 4096, 128), (128, 5120, 2048, 128),
+        (300, 6144, 4096, 128), (130, 8200, 3072, 384), (512, 5128, 2048, 128), (200, 8192, 4096, 128), (256, 5200, 5120, 512), (400, 5120, 4096, 128)]
+
+
+@pytest.mark.parametrize("M,N,K,group", ROWS)
+@pytest.mark.parametrize("wide", [False, True])
+def test_more_than_64_rows(P, M, N, K, group, wide):
+    names = P.is_describe_prepacked(M, N, K, group)
+    assert len(names) == 1 and names[0].startswith("gemm_rows_pk_kernel<"), names
+    check_call(P, M, N, K, group, wide, chan=not wide)
+
+
+@pytest.mark.parametrize("M,inter,K", [(65, 2576, 2048), (100, 5504, 2176), (200, 4096, 2048), (256, 2560, 4096)])
+def test_more_than_64_rows_fused_gate_up(P, M, inter, K):
+    test_fused_gate_up(P, M, inter, K)
