@@ -448,18 +448,23 @@ WavekPlan wavek_plan(int M, int N, int K, bool w8) {
     // Eight waves where workgroups of four would leave every compute unit with one wave per SIMD at most (65 x 4096 x 14336:
     // 22.1 against 24.0 us); two workgroups of four share a unit otherwise, one's start and end under the other's K loop.
     p.waves = p.tiles <= cu_count() ? 8 : 4;
+    p.us = wavek_us(M, N, K, w8, p.ms, p.waves);
     // Long runs and more than a few tiles: by time, and tiles of 80 rows too.  What decides is how the tiles fill the units (300 x 4096: 320
     // tiles of 64 rows give a quarter of the 256 units two, 256 tiles of 80 rows give each one): W8A8 300 x 4096 x 14336 54.6 -> 42.4 us,
     // 400 rows 87 -> 53, 1024 rows 128 -> 111; int4 weights 300 x 4096 x 14336 41.9 -> 32.4, 200 rows 49.9 (tiled kernel) -> 27.8.
     if (K >= 2048 && p.tiles >= cu_count() / 8) {
-        double best = 0.0;
+        // The rule's tiles stay unless a twentieth is to be gained: near ties are decided by what the times leave out (173 x 15206 x 8064:
+        // both 41.9 us by the times, 42.8 with 64 rows and 45.9 with 48).
+        const double rule = p.us;
         for (int ms = 3; ms <= 5; ++ms)
             for (int waves = 4; waves <= 8; waves += 4) {
                 const double us = wavek_us(M, N, K, w8, ms, waves);
-                if (best == 0.0 || us < best) {
-                    best = us;
-                    p.ms = ms;
-                    p.waves = waves;
+                if (us < p.us) {
+                    p.us = us;
+                    if (us < 0.95 * rule) {
+                        p.ms = ms;
+                        p.waves = waves;
+                    }
                 }
             }
         p.tiles = tiles(p.ms);
@@ -489,7 +494,7 @@ bool wavek_is_faster(int M, int N, int K, bool w8) {
     const int steps = K >> 7, cus = cu_count();
     const WavekPlan p = wavek_plan(M, N, K, w8);
     const long long tiles = (long long)((N + 255) / 256) * ((M + 127) / 128);
-    double here = (w8 ? 0.95 : 1.04) * wavek_us(M, N, K, w8, p.ms, p.waves);
+    double here = (w8 ? 0.95 : 1.04) * p.us;
     if (w8) {
         if (steps < 16) {  // (runs of a few steps a wave: by steps, not by the longest wave's)
             const double filled = std::max(1.0, 0.5 * ((double)((p.tiles + cus - 1) / cus) + (double)p.tiles / cus));
@@ -504,8 +509,7 @@ bool wavek_is_faster(int M, int N, int K, bool w8) {
 double prepared_gemm_us(int M, int N, int K) {
     const long long tiles = (long long)((N + 255) / 256) * ((M + 127) / 128);
     if (!wavek_is_faster(M, N, K, false)) return tiled_us(tiles, K >> 7);
-    const WavekPlan p = wavek_plan(M, N, K, false);
-    return wavek_us(M, N, K, false, p.ms, p.waves);
+    return wavek_plan(M, N, K, false).us;
 }
 
 void wavek_kernel_name(const WavekPlan& p, bool int_scale, bool w8, bool silu, char* buf, size_t len) {

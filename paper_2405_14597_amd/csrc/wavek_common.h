@@ -22,6 +22,7 @@ struct WavekPlan {
     int ms;           // 16-row token sub-tiles of a tile
     int waves;        // waves of a workgroup (the K split)
     long long tiles;  // workgroups
+    double us;        // its fitted time
 };
 
 bool takes_wavek(int M, int N, int K, bool w8 = false);  // the dispatch of the tiled kernel's calls (api.hip)
