@@ -12,7 +12,7 @@ LIB_PATH = os.environ.get("INTSCALE_LIBRARY", os.path.join(PKG_DIR, "libintscale
 
 SOURCES = ["api.hip", "quantize.hip", "act_producers.hip", "gemm_skinny.hip", "gemm_decode.hip", "gemm_prefill.hip",
            "gemm_tile_w8.hip", "overflow.hip", "probe.hip", "prepack.hip", "gemm_decode_pk.hip", "gemm_tile_pk.hip",
-           "gemm_small_group.hip", "gemm_wavek.hip", "gemm_few_pk.hip"]
+           "gemm_small_group.hip", "gemm_wavek.hip", "gemm_few_pk.hip", "gemm_few_w8.hip"]
 HEADERS = ["is_common.h", "act_common.h", "tile_common.h", "pk_common.h", "wavek_common.h", "few_common.h"]
 
 HIPCC_FLAGS = [

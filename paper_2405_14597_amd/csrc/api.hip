@@ -902,7 +902,24 @@ static int gemm_w8_common(const int8_t* xq, const float* a_scale, const int8_t* 
     a.alpha_log2 = int_scale ? alpha_log2 : 0;
     a.num_experts = 1;
     a.w_bits = 8;
-    // up to 64 token rows the layer is a weight stream: the bandwidth-bound general kernel; else the tiled kernel
+    // up to 64 token rows the layer is a weight stream: integer scales and K from 1024 on to the kernel whose waves split K, the rest to the
+    // bandwidth-bound general kernel; beyond, the tiled kernel
+    if (int_scale && kernel_route() == 0 && few_w8_tiles(M, N, K) > 0) {
+        FewArgs f;
+        f.xq = xq;
+        f.a_scale = a_scale;
+        f.wpack = a.qweight;
+        f.spack = static_cast<const uint8_t*>(scale);
+        f.chan_scale = chan_scale;
+        f.out = a.out;
+        f.acc_out = acc_out;
+        f.M = M;
+        f.N = N;
+        f.K = K;
+        f.group = group;
+        f.alpha_log2 = alpha_log2;
+        return hip_status(launch_gemm_few_w8(f, static_cast<hipStream_t>(stream)));
+    }
     if (M <= 64 && !general_forced_off())
         return hip_status(launch_gemm_skinny(a, int_scale, static_cast<hipStream_t>(stream)));
     // a moderate number of rows: activations to the blocks the kernel reads, then the kernel whose waves split K (a

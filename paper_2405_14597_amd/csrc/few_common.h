@@ -43,5 +43,9 @@ hipError_t launch_gemm_rows_pk(const FewArgs& a, const FewPlan& p, bool silu, hi
 FewPlan few_grouped_plan(int E, int M, int N, int K);
 void few_grouped_kernel_name(const FewPlan& p, bool int_scale, char* buf, size_t len);
 hipError_t launch_gemm_few_grouped_pk(const FewArgs& a, const FewGroups& g, const FewPlan& p, bool int_scale, hipStream_t stream);
+// Row-major int8 weights in `wpack`, row-major integer scales in `spack` (gemm_few_w8.hip): weight tiles of a workgroup, 0 where the call
+// is not for this kernel
+int few_w8_tiles(int M, int N, int K);
+hipError_t launch_gemm_few_w8(const FewArgs& a, hipStream_t stream);
 
 }  // namespace intscale

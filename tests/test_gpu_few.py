@@ -160,3 +160,23 @@ def test_more_than_64_rows(P, M, N, K, group, wide):
 @pytest.mark.parametrize("M,inter,K", [(65, 2576, 2048), (100, 5504, 2176), (200, 4096, 2048), (256, 2560, 4096)])
 def test_more_than_64_rows_fused_gate_up(P, M, inter, K):
     test_fused_gate_up(P, M, inter, K)
+
+
+# int8 weights: 16-row token tiles of 1 to 4, one and two weight tiles a workgroup (more than 4096 columns), ragged rows and columns,
+# uneven runs of K steps, groups of several steps
+@pytest.mark.parametrize("M,N,K,group", [(1, 20, 1024, 128), (16, 4100, 1152, 128), (1, 4112, 3072, 256), (17, 300, 2176, 128), (32, 4097, 1536, 512),
+                                         (33, 1003, 1152, 384), (48, 5120, 1024, 128), (49, 97, 1152, 1152), (64, 4104, 1664, 128),
+                                         (64, 16, 14336, 256), (64, 40, 28672, 128), (5, 4136, 28672, 128)])
+@pytest.mark.parametrize("wide", [False, True])
+def test_int8_weights(P, M, N, K, group, wide):
+    xq, _, _, scale, sa, c = case(M, N, K, group, wide, seed=7)
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(N + K)
+    q = torch.randint(-128, 128, (N, K), generator=gen, device="cuda:0", dtype=torch.int8)
+    cc, sa = (None if wide else c), sa * 2.0 ** -6
+    acc = wrapped(reference(xq, q, scale, group))
+    out, got = P.is_gemm_w8a8_intscale(xq, sa, q, scale, cc, group, 10, want_acc=True)
+    assert torch.equal(got, acc), "int32 accumulators"
+    want = acc.double() * sa.double()[:, None] * (1.0 if wide else c.double()[None, :]) / 1024.0
+    # two fp32 products and one rounding to fp16: 2^-11 of the value and a little more, and half a step of the smallest numbers
+    assert bool(((out.double() - want).abs() <= 5e-4 * want.abs() + 2.0 ** -25)[want.abs() < 65000.0].all())
