@@ -5,7 +5,7 @@
 // What bounds this regime.  A few hundred token rows make a few dozen tiles of 128 x 256, far fewer than the chip has
 // compute units; cutting their K range over workgroups moves partial tiles of 128 KB through memory, and one workgroup per tile
 // adds them up while the others are done (300 x 4096 x 4096: 8 K steps a workgroup, 31 us).  Here a workgroup owns a
-// small output tile (up to 64 x 64) over all of K, each of its waves multiplies the whole tile over its own run of K steps,
+// small output tile (up to 80 x 64) over all of K, each of its waves multiplies the whole tile over its own run of K steps,
 // and the partial tiles meet in LDS.  300 rows make 320 workgroups of 4096 columns, no partial tile leaves the compute
 // unit, and no wave waits for another before the end: there is no barrier in the K loop.
 //
@@ -29,9 +29,9 @@
 // 43.7 with the loads, 41.7 us without).
 //
 // Measured (GEMM on int8 codes, its preparation included, graph replay), the tiled kernel's time first: 65 x 4096 x 4096
-// 32.9 -> 12.6 us, 300 x 4096 x 4096 36.4 -> 19.5 us, 512 x 6144 x 4096 42.2 -> 28.5 us, 300 x 28672 x 4096 72.9 -> 63.0 us,
-// 128 x 4096 x 14336 46.2 -> 25.0 us; W8A8 300 x 4096 x 14336 126.4 -> 55.9 us, 1024 x 4096 x 14336 129 -> 103 us;
-// W4A8 1024 x 28672 x 4096 147 against 181 us (stays on the tiled kernel).
+// 32.9 -> 12.6 us, 300 x 4096 x 4096 36.4 -> 19.5 us, 512 x 6144 x 4096 42.2 -> 28.5 us, 300 x 28672 x 4096 72.9 -> 58.2 us,
+// 128 x 4096 x 14336 46.2 -> 25.0 us, 300 x 4096 x 14336 32.4 us (41.9 in tiles of 64 rows); W8A8 300 x 4096 x 14336 126.4 -> 42.4 us,
+// 1024 x 4096 x 14336 129 -> 103 us; W4A8 1024 x 28672 x 4096 147 against 181 us (stays on the tiled kernel).
 #include <math.h>
 #include <stdio.h>
 
@@ -464,6 +464,7 @@ WavekPlan wavek_plan(int M, int N, int K, bool w8) {
                     if (us < 0.95 * rule) {
                         p.ms = ms;
                         p.waves = waves;
+                        p.by_padding = false;
                     }
                 }
             }
@@ -478,7 +479,9 @@ WavekPlan wavek_plan(int M, int N, int K, bool w8) {
 // K range it cuts, 20 us to pass partial tiles through memory.  With one full round of the tiled kernel or more there are sixteen
 // rounds of tiles here, and their starts and ends add up (540 x 53283 x 1536 97 us there, 108 us here; 4096 x 4608 x 2304 73 and 79 us; the
 // best of such calls here is 3 % ahead).  4 % to spare with int4 weights: the long runs of large calls are slower than the fit says (1024 x 8192 x 28672
-// 313 us here).
+// 313 us here).  Where the two times are within 15 % and the tiles are those that pad least, a coarser time decides that counts rounds of
+// 0.76 us per K step of a wave on every SIMD and was fitted to 1482 calls (wrong by 6 % at most near the line, the finer one by 8 %:
+// 929 x 11092 x 2944 60.1 us here and 64.7 there, 946 x 11917 x 6784 108.3 and 113.9, 943 x 11445 x 4352 77.7 and 81.1).
 static double tiled_us(long long tiles, int steps) {
     const int cus = cu_count();
     if (tiles > cus) return 22.0 + 1.62 * steps * (double)((tiles + 2 * cus - 1) / (2 * cus));
@@ -503,7 +506,12 @@ bool wavek_is_faster(int M, int N, int K, bool w8) {
         return here < 9.5 + (double)((tiles + cus - 1) / cus) * (10.0 + 1.03 * steps);
     }
     if (tiles >= 2 * cus) return false;
-    return here < tiled_us(tiles, steps);
+    const double there = tiled_us(tiles, steps);
+    if (steps < 16 || !p.by_padding || here < 0.85 * there || here > 1.15 * there) return here < there;
+    const double coarse = 10.0 + 0.76 * 0.25 * (double)((p.tiles + cus - 1) / cus) * steps * (2 * p.ms + 4) / 12.0;
+    if (tiles > cus) return coarse < 6.0 + 2.3 * steps;
+    const int parts = std::min(std::min(cus / (int)tiles, 8), std::max(steps / 8, 1));
+    return coarse < 6.0 + (parts > 1 ? 1.56 * steps / parts + 14.0 : std::min(1.56 * steps, 25.0 + 1.31 * steps));
 }
 
 double prepared_gemm_us(int M, int N, int K) {

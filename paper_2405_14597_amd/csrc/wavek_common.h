@@ -19,10 +19,11 @@ struct WavekArgs {
 };
 
 struct WavekPlan {
-    int ms;           // 16-row token sub-tiles of a tile
-    int waves;        // waves of a workgroup (the K split)
-    long long tiles;  // workgroups
-    double us;        // its fitted time
+    int ms;                  // 16-row token sub-tiles of a tile
+    int waves;               // waves of a workgroup (the K split)
+    long long tiles;         // workgroups
+    double us;               // its fitted time
+    bool by_padding = true;  // the row tiles that pad least
 };
 
 bool takes_wavek(int M, int N, int K, bool w8 = false);  // the dispatch of the tiled kernel's calls (api.hip)
