@@ -7,7 +7,7 @@ activations, alpha = 2^10) in decode (M = 1 and M = 32 token rows) and in prefil
 whole hot path over that workload: for every M, every linear and every one of `--layers` layers (each with its own
 weight buffers, so every decode GEMM streams cold weights from HBM as in a real decode step), the linear call on fp16
 activations: the per-token activation quantiser and the integer-scale GEMM of Eq. (2) with its float epilogue (one
-kernel for M = 1, quantiser + weight-streaming kernel for M = 32, quantising preparation pass + MFMA-bound tiled kernel
+kernel for M = 1, quantiser + the kernel for few rows for M = 32, quantising preparation pass + MFMA-bound tiled kernel
 for M = 2048).  Inputs are synthetic (seeded) and resident in HBM before the timed region.  The launches of one
 (M, linear) pair are recorded into a HIP graph and replayed; HIP events between the replays give each pair's average
 duration inside the timed region.
@@ -776,8 +776,8 @@ def gate_up_main(args):
     `down`, two ways on the prepacked route: (fused) the gate_up GEMM with SiLU(gate) * up as its epilogue, then the plain
     activation quantiser on [M, inter]; (unfused) the plain GEMM to [M, 2 inter], then SiLU * up folded into the
     quantiser.  LLaMA-3-8B (4096 -> 2 x 14336) at M = 4096 and LLaMA-2-70B (8192 -> 2 x 28672) at M = 2048 (tiled
-    kernel: the epilogue is fused), and both at M = 32 (weight-streaming kernel: the [M, 2 inter] tensor goes through the
-    workspace and a second kernel).  Each sequence is replayed as a HIP graph over `--layers` (default 2) weight copies.
+    kernel: the epilogue is fused), and both at M = 32 (the kernel for few rows: fused as well).  Each sequence is replayed as a HIP graph
+    over `--layers` (default 2) weight copies.
     `value` = int8 operations of the fused sequences / their time."""
     import numpy as np
     import torch

@@ -178,19 +178,20 @@ int is_prepack_w4(const void* qweight, const int32_t* scale_i32, const float* sc
  * is_gemm_w4a8_floatscale (accumulators bit for bit; the float-scale sums in a different but fixed order).
  *   qweight_packed, scales_packed   from is_prepack_w4 (integer scales for the first, float scales for the second)
  *   workspace   at least is_gemm_prepacked_workspace_bytes(M,N,K,group) bytes.
- *               (Which kernel: for M > 64 the one whose waves split K where a fitted time says that it is faster,
- *               roughly up to a few hundred rows, else the tiled one, which 33 <= M <= 64 takes too when N * K >= 2^27;
- *               else the weight-streaming one.  Ask is_gemm_prepacked_workspace_bytes / is_describe_prepacked, do not
- *               guess.)
- *               M <= 64 (the weight-streaming kernel): 0 for most shapes; when it is not 0 the K dimension is split
+ *               (Which kernel: up to 64 rows the one for few rows whose waves split K, but the weight-streaming one for a
+ *               single row with K >= 12288, and the tiled one for 33 <= M <= 64 when N * K >= 2^27; for M > 64 one of the
+ *               two whose waves split K where a fitted time says that it is faster, roughly up to a few hundred rows, else
+ *               the tiled one.  Ask is_gemm_prepacked_workspace_bytes / is_describe_prepacked, do not guess.)
+ *               M <= 64: 0 for most shapes; when it is not 0 the weight-streaming kernel splits the K dimension
  *               across workgroups and the first 64 KB of the workspace are arrival counters: they must be ZERO when a
- *               call starts and every call leaves them zero, so zero the workspace once after allocating it.
+ *               call starts and every call leaves them zero, so zero the workspace once after allocating it (the kernel
+ *               for few rows leaves the workspace alone; the size and the rule are the same whichever takes the call).
  *               M > 64: the activations re-ordered into MFMA operand blocks (ceil(M/16) * 16 * K bytes) and one
  *               zero-point correction per token row and K step, written by a preparation kernel of the call; when the
  *               last round of the tiled kernel's output tiles would leave most of the chip idle, also partial tiles (up
  *               to 64 MB) of a K split of that round, reduced exactly in int32 (the float-scale form adds its float
- *               partial sums in a fixed order).  The size is the same whichever kernel the call takes (the one whose
- *               waves split K reads the operand blocks alone).  No requirement on the contents.
+ *               partial sums in a fixed order).  The size is the same whichever kernel the call takes (the ones whose
+ *               waves split K read the operand blocks alone, or prepare nothing).  No requirement on the contents.
  *               Calls sharing one workspace must not overlap.
  * Covered: M >= 1, N up to 16 * 256 * (compute units) rows when M <= 64, ceil(M/16) * 16 * K below 2^31 beyond
  * (IS_ERR_UNSUPPORTED otherwise).  M = 0 is a no-op.
@@ -298,8 +299,8 @@ int is_gemm_w4a8_floatscale_grouped_prepacked(const int8_t* xq, const float* a_s
  *   is_gemm_w4a8_*_gate_up_silu_prepacked: out [M, inter] fp16, out[m, n] = fp16(SiLU(g) * u) with g, u the fp16
  *     results of the integer-scale (float-scale) GEMM of Eq. (2) (Eq. (1)) for gate row n and up row n: the value of
  *     the unfused sequence GEMM -> fp16 tensor -> SiLU * up, bit for bit, without the [M, 2 inter] tensor's trip
- *     through memory when M > 64 (the epilogue of either kernel that takes such calls; for M <= 64 the weight-streaming
- *     kernel writes that tensor into the workspace and a second kernel reads it).  SiLU(g) = g / (1 + e^-g) in single precision,
+ *     through memory (the epilogue of every kernel that takes such calls; only one row with a long K goes through the
+ *     workspace and a second kernel).  SiLU(g) = g / (1 + e^-g) in single precision,
  *     e^-g by the operation sequence stated in the oracle.  acc_out (may be NULL): [M, 2 inter] int32 accumulators
  *     in the packed row order.  workspace >= is_gemm_gate_up_silu_prepacked_workspace_bytes(M, inter, K, group),
  *     zero-filled once (same rules as the prepacked GEMM's).
@@ -355,7 +356,8 @@ size_t is_gemm_grouped_workspace_bytes(int num_experts, int M_total, int N, int 
  * The GEMMs compute Eq. (2) resp. Eq. (1) exactly as their W4A8 counterparts (a group's partial sum is at most 2^21
  * in magnitude, so the same integer scale step applies); group and K multiples of 128, any M >= 0, any N >= 1;
  * `workspace` of at least is_gemm_w8a8_workspace_bytes(M,N,K,group) bytes is always needed (transposed scales, or, where
- * more than 64 token rows take the kernel whose waves split K, the activations re-ordered into operand blocks).  Such a
+ * more than 64 token rows take the kernel whose waves split K, the activations re-ordered into operand blocks; up to 64
+ * rows with integer scales leave it alone).  Such a
  * call accepts a workspace of the transposed scales' size as well and then runs the tiled kernel: the same accumulators
  * and integer-scale results, float-scale sums in that kernel's order.
  */

@@ -66,11 +66,9 @@ bool general_forced() { return kernel_route() == 1; }
 bool general_forced_off() { return kernel_route() == 2; }
 
 // Which calls on the prepacked layout prepare their activations, for the tiled kernel or the one whose waves split K (takes_wavek):
-// those of more than 64 token rows.  The others take the weight-streaming kernel.  33..64 rows:
-// the weight-streaming kernel cannot keep a long K slab of 64 rows in LDS, so it splits K many times and moves partial
-// tiles and activation slabs of about the weights' own size; from 2^27 weights on (measured: LLaMA-2-70B gate 50 -> 47 us,
-// down 62 -> 53 us at 64 rows; every smaller shape of the LLaMA-2-7B / LLaMA-3-8B / LLaMA-2-70B layers is slower there)
-// the tiled kernel's 64-row instance is ahead.  Same bits either way; route 3 sends every such call there (tests).
+// those of more than 64 token rows (some of those up to 512 rows need no preparation either, takes_rows).  33..64 rows: from 2^27 weights
+// on the tiled kernel's 64-row instance (LLaMA-2-70B gate 47 us, down 53 us at 64 rows), which reads the activations once per 256 columns
+// where the kernel of takes_few reads them once per 16 to 64.  Same bits either way; route 3 sends every such call there (tests).
 bool pk_takes_tile(int M, int N, int K) {
     return M > 64 || (M > 32 && (kernel_route() == 3 || (long long)N * K >= (1LL << 27)));
 }
@@ -81,8 +79,8 @@ bool pk_takes_tile(int M, int N, int K) {
 // behind (5673 x 12416 10.5 and 11.1 us, 3408 x 19328 9.5 and 10.1).  An fp16 row is quantised inside the weight-streaming kernel.
 bool takes_few(int M, int K) { return M >= 2 ? M <= 64 : M == 1 && K < 12288; }
 
-// And of the calls of quantised activations and integer scales beyond 64 rows, up to 512: in row tiles of 48 or 64 there, without a preparation kernel, where
-// that is 5 % ahead by the times of both (65 x 12288 x 4096 16.5 -> 12.2 us, 128 x 8192 x 8192 20.2 -> 16.6, 300 x 6144 x 4096 20.5 ->
+// And of the calls of quantised activations and integer scales beyond 64 rows, up to 512: in row tiles of 48 or 64 there, without a
+// preparation kernel, where that is 5 % ahead by the times of both (65 x 12288 x 4096 16.5 -> 12.2 us, 128 x 8192 x 8192 20.2 -> 16.6, 300 x 6144 x 4096 20.5 ->
 // 16.8, 512 x 12288 x 4096 43.6 -> 40.8; 400 x 28672 x 4096 75 on the tiled kernel and 81, 300 x 28672 x 4096 58.2 and 59.8).  Not measured
 // below 16 K steps.  Fewer than 5120 columns stay with the kernel that the tests name for such calls, though they would gain as well
 // (65 x 4096 x 4096 12.6 -> 8.8 us).
@@ -135,10 +133,8 @@ int static_scratch(void** ptr_out) {
 
 namespace intscale {
 // The calls of the tiled kernel that the kernel takes whose waves split K (more than 64 rows, where it is faster; routes 2
-// and 3 keep them on the tiled kernel).  The line at 64 rows is the weight-streaming kernel's, which prepares nothing; at 64
-// rows it takes 11.9 / 17.1 / 19.5 us for 4096 x 4096 / 4096 x 11008 / 4096 x 14336 (N x K) where this kernel with its
-// preparation takes 13.3 / 20.7 / 23.9 us.  For wide matrices the line could lie lower: 12288 x 4096 17.0 against 15.1 us here,
-// 28672 x 4096 26.3 against 22.5, 10240 x 8192 22.7 against 19.0.
+// and 3 keep them on the tiled kernel).  Up to 64 rows the kernel of takes_few, which prepares nothing, is ahead: 4096 x 4096 /
+// 12288 x 4096 / 22016 x 4096 / 10240 x 8192 at 64 rows 7.3 / 10.3 / 18.7 / 17.2 us there and 13.3 / 15.1 / 20.5 / 19.0 us here.
 bool takes_wavek(int M, int N, int K, bool w8) {
     return M > 64 && kernel_route() < 2 && (!w8 || (long long)((M + 15) / 16) * 16 * K < (1LL << 31)) && wavek_is_faster(M, N, K, w8);
 }
@@ -475,7 +471,7 @@ static int gemm_pk_common(const int8_t* xq, const void* x_fp16, const float* a_s
     if (M > 0 && !tiled && !pk_decode_plan(M, N, K, group, x_fp16 != nullptr, &plan)) return IS_ERR_UNSUPPORTED;
     if (tiled && (long long)((M + 15) / 16) * 16 * K >= (1LL << 31)) return IS_ERR_UNSUPPORTED;  // 32-bit offsets
     // (on the fixed scratch the tiled route takes what it needs at least: the K split of its last round uses what is left)
-    if (prepared && M > 0 && !tiled) return IS_ERR_UNSUPPORTED;  // (the weight-streaming kernel reads the codes themselves)
+    if (prepared && M > 0 && !tiled) return IS_ERR_UNSUPPORTED;  // (the others read the codes themselves)
     const size_t need = ((fixed_scratch || prepared) && tiled) ? gemm_tile_pk_min_workspace_bytes(M, K)
                                                   : is_gemm_prepacked_workspace_bytes(M, N, K, group);
     if (need > 0 && (workspace == nullptr || workspace_bytes < need)) return IS_ERR_WORKSPACE;
@@ -573,7 +569,8 @@ int is_prepack_w4_gate_up(const void* qweight, const int32_t* scale_i32, const f
 size_t is_gemm_gate_up_silu_prepacked_workspace_bytes(int M, int inter, int K, int group) {
     if (M <= 0 || inter <= 0 || inter > (1 << 29) || inter % 16 != 0 || check_pk_shape(2 * inter, K, group) != IS_OK) return 0;
     const size_t gemm = is_gemm_prepacked_workspace_bytes(M, 2 * inter, K, group);
-    // up to 64 token rows: the weight-streaming kernel writes the [M, 2 inter] fp16 tensor here, a second kernel reads it
+    // up to 64 token rows: room for the [M, 2 inter] fp16 tensor, which the weight-streaming kernel (one row, long K) writes and a second
+    // kernel reads
     return !pk_takes_tile(M, 2 * inter, K) ? pad_256(gemm) + pad_256((size_t)M * 2 * inter * 2) : gemm;
 }
 
@@ -623,7 +620,7 @@ int is_prepare_activations_prepacked(const int8_t* xq, int M, int K, void* works
                                      void* stream) {
     if (M < 0 || K <= 0) return IS_ERR_INVALID_ARG;
     if (K % 128 != 0 || K > (1 << 20) || M > (1 << 20)) return IS_ERR_UNSUPPORTED;
-    if (M > 0 && M <= 32) return IS_ERR_UNSUPPORTED;  // such calls take the weight-streaming kernel, which needs none
+    if (M > 0 && M <= 32) return IS_ERR_UNSUPPORTED;  // such calls take kernels that need none
     if ((long long)((M + 15) / 16) * 16 * K >= (1LL << 31)) return IS_ERR_UNSUPPORTED;  // 32-bit offsets
     if (M == 0) return IS_OK;
     if (!ok_ptr(workspace) || workspace_bytes < gemm_tile_pk_min_workspace_bytes(M, K)) return IS_ERR_WORKSPACE;

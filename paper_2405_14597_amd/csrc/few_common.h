@@ -1,4 +1,4 @@
-// Interface of the kernel for 2 to 64 token rows whose waves split K (gemm_few_pk.hip).
+// Interface of the kernels for few token rows whose waves split K (gemm_few_pk.hip; int8 weights: gemm_few_w8.hip).
 #pragma once
 #include "is_common.h"
 

@@ -1,5 +1,6 @@
-// Decode regime (at most 64 token rows) of the fine-grained W4A8 GEMM on prepacked weights: a weight-streaming kernel
-// with no synchronisation inside its main loop.  Integer-scale form: Eq. (2) / Table 2 "Ours" of the Integer Scale
+// One token row of the fine-grained W4A8 GEMM on prepacked weights (fp16, quantised inside the kernel, or int8 codes with a long K; 2 to 64
+// rows and the other single rows: gemm_few_pk.hip): a weight-streaming kernel with no synchronisation inside its main loop.  Its plan
+// covers up to 64 rows: it says how large the workspace of such calls is.  Integer-scale form: Eq. (2) / Table 2 "Ours" of the Integer Scale
 // paper; float-scale form: Eq. (1) / Table 2 "Atom".
 //
 // Work split.  The weight matrix is a grid of 1 KB blocks (16 weight rows x 128 k, see pk_common.h).  K is cut into

@@ -1,6 +1,7 @@
-// Decode regime of the fine-grained W4A8 GEMM on prepacked weights, 2 to 64 token rows: the waves of a workgroup split K.
+// Fine-grained W4A8 GEMM on prepacked weights, 1 to 64 token rows (and, in row tiles, some calls of up to 512): the waves of a workgroup
+// split K.
 // Integer-scale form: Eq. (2) / Table 2 "Ours" of the Integer Scale paper; float-scale form: Eq. (1) / Table 2 "Atom".
-// (One token row has a kernel of its own, gemm_decode_pk.hip.)
+// (An fp16 row, and a quantised row with a long K, have a kernel of their own, gemm_decode_pk.hip.)
 //
 // What bounds this regime: the weight stream from memory where the matrix is large and the rows are few, the kernel's start and end
 // where it is small, and with 64 rows the activations, which every compute unit pulls from its L2 in full (per K step of 64 rows 8 KB
