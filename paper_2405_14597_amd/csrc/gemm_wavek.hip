@@ -15,11 +15,11 @@
 // need no preparation, cost 71 cycles per load and compute unit in 16 pieces of 64 bytes against about 30: 2048 x 28672 x 4096
 // 519 against 344 us, and no gain at 65 rows.)  Each register is asked for again as soon as its last use has been
 // issued, a K step ahead; two waves per SIMD cover the rest of the latency.  What bounds it, from counters: with int4 weights
-// (300 x 28672 x 4096, 58 us) a wave issues 44 % of its time, waits for an issue slot 37 % and for loads 19 %, so that the two
-// waves of a SIMD leave it little room, and the L2 delivers 35 bytes per cycle and compute unit (12 KB of operands per 32 MFMAs
+// (300 x 28672 x 4096, 58 us) a wave issues 43 % of its time, waits for an issue slot 36 % and for loads 21 %, so that the two
+// waves of a SIMD leave it little room, and the L2 delivers 34 bytes per cycle and compute unit (14 KB of operands per 40 MFMAs
 // of a wave; tile loads alone sustain 40 to 55): large calls stay on the tiled kernel, which shares its operands through LDS
-// (takes_wavek says where the line lies).  With int8 weights (300 x 4096 x 14336, 48 us) it waits for loads: 46 % of a wave's
-// time, 27 % issuing, 24 bytes per cycle.  There the weight lines are requested by assembly, which the compiler does not
+// (takes_wavek says where the line lies).  With int8 weights (300 x 4096 x 14336, 42 us) it waits for loads: 49 % of a wave's
+// time, 34 % issuing, 29 bytes per cycle.  There the weight lines are requested by assembly, which the compiler does not
 // count, so that its waits for the activations (7 and 6 outstanding) hold up until the lines just requested have come too: they
 // are less than a K step ahead; and the copy of the scales every fourth step waits for everything.
 //
