@@ -179,7 +179,7 @@ int is_prepack_w4(const void* qweight, const int32_t* scale_i32, const float* sc
  *   qweight_packed, scales_packed   from is_prepack_w4 (integer scales for the first, float scales for the second)
  *   workspace   at least is_gemm_prepacked_workspace_bytes(M,N,K,group) bytes.
  *               (Which kernel: up to 64 rows the one for few rows whose waves split K, but the weight-streaming one for a
- *               single row with K >= 12288, and the tiled one for 33 <= M <= 64 when N * K >= 2^27; for M > 64 one of the
+ *               single row with K >= 12288 or float scales, and the tiled one for 33 <= M <= 64 when N * K >= 2^27; for M > 64 one of the
  *               two whose waves split K where a fitted time says that it is faster, roughly up to a few hundred rows, else
  *               the tiled one.  Ask is_gemm_prepacked_workspace_bytes / is_describe_prepacked, do not guess.)
  *               M <= 64: 0 for most shapes; when it is not 0 the weight-streaming kernel splits the K dimension
@@ -299,8 +299,8 @@ int is_gemm_w4a8_floatscale_grouped_prepacked(const int8_t* xq, const float* a_s
  *   is_gemm_w4a8_*_gate_up_silu_prepacked: out [M, inter] fp16, out[m, n] = fp16(SiLU(g) * u) with g, u the fp16
  *     results of the integer-scale (float-scale) GEMM of Eq. (2) (Eq. (1)) for gate row n and up row n: the value of
  *     the unfused sequence GEMM -> fp16 tensor -> SiLU * up, bit for bit, without the [M, 2 inter] tensor's trip
- *     through memory (the epilogue of every kernel that takes such calls; only one row with a long K goes through the
- *     workspace and a second kernel).  SiLU(g) = g / (1 + e^-g) in single precision,
+ *     through memory (the epilogue of every kernel that takes such calls; one row with a long K, and float-scale calls of
+ *     up to 64 rows whose plain GEMM does not pair the tiles, go through the workspace and a second kernel).  SiLU(g) = g / (1 + e^-g) in single precision,
  *     e^-g by the operation sequence stated in the oracle.  acc_out (may be NULL): [M, 2 inter] int32 accumulators
  *     in the packed row order.  workspace >= is_gemm_gate_up_silu_prepacked_workspace_bytes(M, inter, K, group),
  *     zero-filled once (same rules as the prepacked GEMM's).

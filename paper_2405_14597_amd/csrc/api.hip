@@ -76,8 +76,9 @@ bool pk_takes_tile(int M, int N, int K) {
 // Which of the others the kernel takes whose waves split K over the canonical activations (gemm_few_pk.hip): those of 2 to 64
 // rows, and of quantised single rows those with K < 12288: there it is 5 % ahead of the weight-streaming kernel on average (6144 x 4096 6.0
 // -> 5.5 us, 4096 x 11008 7.6 -> 7.1, 14069 x 10880 23.4 -> 17.6, 57344 x 8192 49.0 -> 44.9; 8192 x 8192 9.0 -> 9.2), beyond it up to 6 %
-// behind (5673 x 12416 10.5 and 11.1 us, 3408 x 19328 9.5 and 10.1).  An fp16 row is quantised inside the weight-streaming kernel.
-bool takes_few(int M, int K) { return M >= 2 ? M <= 64 : M == 1 && K < 12288; }
+// behind (5673 x 12416 10.5 and 11.1 us, 3408 x 19328 9.5 and 10.1).  An fp16 row is quantised inside the weight-streaming kernel, and a
+// float-scale row on codes has to have its sums in that kernel's order.
+bool takes_few(int M, int K, bool int_scale) { return M >= 2 ? M <= 64 : M == 1 && int_scale && K < 12288; }
 
 // And of the calls of quantised activations and integer scales beyond 64 rows, up to 512: in row tiles of 48 or 64 there, without a
 // preparation kernel, where that is 5 % ahead by the times of both (65 x 12288 x 4096 16.5 -> 12.2 us, 128 x 8192 x 8192 20.2 -> 16.6, 300 x 6144 x 4096 20.5 ->
@@ -499,7 +500,7 @@ static int gemm_pk_common(const int8_t* xq, const void* x_fp16, const float* a_s
     a.group = group;
     a.alpha_log2 = int_scale ? alpha_log2 : 0;
     a.pair = (pair && tiled) ? 1 : 0;  // (the fused epilogue is the tiled kernel's)
-    const bool few = !tiled && x_fp16 == nullptr && takes_few(M, K), rows = int_scale && x_fp16 == nullptr && !prepared && takes_rows(M, N, K, pair);
+    const bool few = !tiled && x_fp16 == nullptr && takes_few(M, K, int_scale), rows = int_scale && x_fp16 == nullptr && !prepared && takes_rows(M, N, K, pair);
     if (few || rows) {
         FewArgs f;
         f.xq = xq;
@@ -515,7 +516,7 @@ static int gemm_pk_common(const int8_t* xq, const void* x_fp16, const float* a_s
         f.group = group;
         f.alpha_log2 = a.alpha_log2;
         double us;
-        return hip_status(few ? launch_gemm_few_pk(f, few_plan(M, N, K, pair), int_scale, pair, static_cast<hipStream_t>(stream))
+        return hip_status(few ? launch_gemm_few_pk(f, few_plan(M, N, K, pair && int_scale), int_scale, pair, static_cast<hipStream_t>(stream))
                               : launch_gemm_rows_pk(f, rows_plan(M, N, K, pair, &us), pair, static_cast<hipStream_t>(stream)));
     }
     if (tiled)
@@ -569,8 +570,7 @@ int is_prepack_w4_gate_up(const void* qweight, const int32_t* scale_i32, const f
 size_t is_gemm_gate_up_silu_prepacked_workspace_bytes(int M, int inter, int K, int group) {
     if (M <= 0 || inter <= 0 || inter > (1 << 29) || inter % 16 != 0 || check_pk_shape(2 * inter, K, group) != IS_OK) return 0;
     const size_t gemm = is_gemm_prepacked_workspace_bytes(M, 2 * inter, K, group);
-    // up to 64 token rows: room for the [M, 2 inter] fp16 tensor, which the weight-streaming kernel (one row, long K) writes and a second
-    // kernel reads
+    // up to 64 token rows: room for the [M, 2 inter] fp16 tensor, which a GEMM without the fused epilogue writes and a second kernel reads
     return !pk_takes_tile(M, 2 * inter, K) ? pad_256(gemm) + pad_256((size_t)M * 2 * inter * 2) : gemm;
 }
 
@@ -592,7 +592,10 @@ static int gate_up_silu_common(const int8_t* xq, const float* a_scale, const voi
     if (!ok_ptr(out_fp16)) return IS_ERR_INVALID_ARG;
     const size_t gemm = pad_256(is_gemm_prepacked_workspace_bytes(M, N, K, group));
     __half* gu = reinterpret_cast<__half*>(static_cast<unsigned char*>(workspace) + gemm);
-    if (takes_few(M, K))  // SiLU * up as that kernel's epilogue: the [M, 2 inter] tensor's place stays unused
+    // SiLU * up as that kernel's epilogue: the [M, 2 inter] tensor's place stays unused.  Float sums have to be the plain call's, whose order
+    // goes with its plan: fused on that plan where it pairs the tiles (8 rows, 2 x 11008 x 4096: 11.3 us), else the plain call and
+    // the second kernel (2 x 14336 x 4096 15.7 us, 13.0 fused on a plan of its own; 2 x 6144 x 4096 10.4 and 8.1).
+    if (takes_few(M, K, int_scale) && (int_scale || few_plan(M, N, K, false).ns % 2 == 0))
         return gemm_pk_common(xq, nullptr, a_scale, nullptr, wpack, spack, chan_scale_packed, M, N, K, group, alpha_log2, out_fp16,
                               acc_out, workspace, gemm, stream, int_scale, false, true);
     const int st = gemm_pk_common(xq, nullptr, a_scale, nullptr, wpack, spack, chan_scale_packed, M, N, K, group,
@@ -832,7 +835,7 @@ int is_describe_prepacked(int M, int N, int K, int group, int int_scale, int fp1
     }
     PkPlan plan;
     const bool fused = fp16_in != 0 && M == 1 && pk_decode_plan(1, N, K, group, true, &plan);
-    if (!fused && takes_few(M, K)) {
+    if (!fused && takes_few(M, K, int_scale != 0)) {
         if (!pk_decode_plan(M, N, K, group, false, &plan)) return IS_ERR_UNSUPPORTED;
         few_kernel_name(few_plan(M, N, K, false), int_scale != 0, false, names, names_len);
         return IS_OK;

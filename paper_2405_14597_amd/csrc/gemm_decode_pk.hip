@@ -789,8 +789,9 @@ bool pk_decode_plan(int M, int N, int K, int group, bool fp16_in, PkPlan* plan) 
     const long long blocks = (long long)tiles_max * pl.max_steps;
     int waves = pl.mt == 4 ? 8 : 4;
     while (waves < (pl.mt == 4 ? 8 : 16) && (long long)waves * 2 * dt <= blocks) waves *= 2;
-    if (fp16_in)
-        while ((K >> 3) > kFuseChunks * waves * kWave) waves *= 2;  // the token's chunks over the threads
+    // The token's chunks over the threads; of int8 codes as well, where the row could have come in fp16: float sums then have one order.
+    if (M == 1 && (K >> 3) <= kFuseChunks * 1024)
+        while ((K >> 3) > kFuseChunks * waves * kWave) waves *= 2;
     static const int env_waves = env_int("INTSCALE_PK_WAVES", 0);  // experiments; read once
     if (env_waves) {
         const int w = env_waves;

@@ -4,6 +4,8 @@ is the same sums in plain PyTorch (exact in float64: a group's partial sum is be
 import pytest
 import torch
 
+from oracle import oracle as O
+
 pytestmark = pytest.mark.gpu
 
 G = 128
@@ -105,6 +107,44 @@ def test_fused_gate_up(P, M, inter, K):
     g, u = gu[:, :inter].double(), gu[:, inter:].double()
     want = g / (1.0 + torch.exp(-g)) * u
     assert bool(((fused.double() - want).abs() <= 1e-3 * want.abs() + 2.0 ** -24)[want.abs() < 65000.0].all())
+
+
+def order_shows(xq, q, scale, size):
+    """Float scales (powers of two times `scale`) whose sums show their order: the first and the last group are alike but for the sign of a
+    large scale, so that what is added between the two loses bits that depend on what."""
+    xq[:, -G:] = xq[:, :G]
+    q[:, -G:] = q[:, :G]
+    s = scale.float() * size
+    s[:, 0] = size * 2.0 ** 24
+    s[:, -1] = -size * 2.0 ** 24
+    return ((q[:, 0::2] & 15) | ((q[:, 1::2] & 15) << 4)).to(torch.uint8).contiguous(), s.contiguous()
+
+
+# one row: K whose fused quantiser needs more waves than the sums would, a narrow matrix with a long K (K cut over workgroups)
+@pytest.mark.parametrize("N,K", [(4096, 4096), (300, 11008), (12288, 4096), (64, 28672), (64, 32768), (16, 20480)])
+def test_one_float_row_sums_in_one_order(P, N, K):
+    """Float sums depend on their order: the linear call on one fp16 row gives the bits of the quantiser and the GEMM on its codes."""
+    codes, q, _, scale, _, _ = case(1, N, K, seed=5)
+    qw, s = order_shows(codes, q, scale, 2.0 ** -17)
+    pk = P.is_prepack_w4(qw, s, G)
+    x = codes.half()
+    xq, sa = P.is_quantize_act_int8_token(x)
+    assert torch.equal(P.is_linear_w4a8_floatscale_prepacked(x, pk), P.is_gemm_w4a8_floatscale_prepacked(xq, sa, pk))
+
+
+# widths whose plain call takes an odd number of weight tiles a workgroup, or other waves, than the paired one; long runs of K steps
+@pytest.mark.parametrize("M,inter,K", [(1, 2048, 4096), (8, 6144, 4096), (32, 6144, 4096), (16, 2048, 4096), (32, 2048, 8192), (64, 6144, 4096),
+                                       (48, 2064, 11008), (5, 14336, 4096), (16, 64, 65536), (17, 11008, 4096)])
+def test_fused_gate_up_float_sums_in_one_order(P, M, inter, K):
+    """The fused epilogue works on the bits of the float-scale GEMM's own outputs."""
+    xq, q, _, scale, sa, _ = case(M, 2 * inter, K, seed=6)
+    qw, s = order_shows(xq, q, scale, 2.0 ** -24)
+    gu = P.is_prepack_w4_gate_up(qw, s, None, G)
+    fused = P.is_gemm_w4a8_floatscale_gate_up_silu_prepacked(xq, sa, gu)
+    plain = P.is_gemm_w4a8_floatscale_prepacked(xq, sa, gu.packed).view(M, inter // 16, 2, 16)
+    gate, up = plain[:, :, 0].reshape(M, inter), plain[:, :, 1].reshape(M, inter)
+    want = O.silu_mul_fp16(torch.cat([gate, up], dim=1).cpu().numpy())
+    assert bool((fused.cpu().numpy().view("uint16") == want.view("uint16")).all())
 
 
 # experts without rows, with one, with more than a workgroup takes at a time (32 or 64), ragged widths, groups of several steps
