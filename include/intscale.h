@@ -179,9 +179,9 @@ int is_prepack_w4(const void* qweight, const int32_t* scale_i32, const float* sc
  *   qweight_packed, scales_packed   from is_prepack_w4 (integer scales for the first, float scales for the second)
  *   workspace   at least is_gemm_prepacked_workspace_bytes(M,N,K,group) bytes.
  *               (Which kernel: up to 64 rows the one for few rows whose waves split K, but the weight-streaming one for a
- *               single row with K >= 12288 or float scales, and the tiled one for 33 <= M <= 64 when N * K >= 2^27; for M > 64 one of the
- *               two whose waves split K where a fitted time says that it is faster, roughly up to a few hundred rows, else
- *               the tiled one.  Ask is_gemm_prepacked_workspace_bytes / is_describe_prepacked, do not guess.)
+ *               single row with K >= 12288 or float scales and for narrow matrices with a long K, and the tiled one for
+ *               33 <= M <= 64 when N * K >= 2^27; for M > 64 one of the two whose waves split K where a fitted time says
+ *               that it is faster, roughly up to a few hundred rows, else the tiled one.  Ask is_gemm_prepacked_workspace_bytes / is_describe_prepacked, do not guess.)
  *               M <= 64: 0 for most shapes; when it is not 0 the weight-streaming kernel splits the K dimension
  *               across workgroups and the first 64 KB of the workspace are arrival counters: they must be ZERO when a
  *               call starts and every call leaves them zero, so zero the workspace once after allocating it (the kernel

@@ -77,8 +77,17 @@ bool pk_takes_tile(int M, int N, int K) {
 // rows, and of quantised single rows those with K < 12288: there it is 5 % ahead of the weight-streaming kernel on average (6144 x 4096 6.0
 // -> 5.5 us, 4096 x 11008 7.6 -> 7.1, 14069 x 10880 23.4 -> 17.6, 57344 x 8192 49.0 -> 44.9; 8192 x 8192 9.0 -> 9.2), beyond it up to 6 %
 // behind (5673 x 12416 10.5 and 11.1 us, 3408 x 19328 9.5 and 10.1).  An fp16 row is quantised inside the weight-streaming kernel, and a
-// float-scale row on codes has to have its sums in that kernel's order.
-bool takes_few(int M, int K, bool int_scale) { return M >= 2 ? M <= 64 : M == 1 && int_scale && K < 12288; }
+// float-scale row on codes has to have its sums in that kernel's order.  On a narrow matrix with a long K a few workgroups would walk
+// all of it: there the weight-streaming kernel stays, which cuts K over workgroups, by the fitted times of both (64 x 512 x 28672 17.4 us
+// there and 23.9 here, 16 x 1024 x 65536 15.5 and 19.9, 2 x 64 x 131072 12.0 and 28.7, 32 x 64 x 524288 35 and 209; 5 x 1295 x 22144
+// 10.6 and 9.1; on 691 calls with such a cut the choice costs 0.2 % on average and 12 % at most).
+bool takes_few(int M, int N, int K, bool int_scale) {
+    if (M == 1) return int_scale && K < 12288;
+    if (M < 2 || M > 64) return false;
+    PkPlan split;
+    return !pk_decode_plan(M, N, K, 128, false, &split) || split.slabs == 1 ||
+           2.9 + 0.95 * few_plan(M, N, K, false).us + 0.049e-6 * N * (double)K <= pk_decode_split_us(split, N, K) / 0.97;
+}
 
 // And of the calls of quantised activations and integer scales beyond 64 rows, up to 512: in row tiles of 48 or 64 there, without a
 // preparation kernel, where that is 5 % ahead by the times of both (65 x 12288 x 4096 16.5 -> 12.2 us, 128 x 8192 x 8192 20.2 -> 16.6, 300 x 6144 x 4096 20.5 ->
@@ -500,7 +509,7 @@ static int gemm_pk_common(const int8_t* xq, const void* x_fp16, const float* a_s
     a.group = group;
     a.alpha_log2 = int_scale ? alpha_log2 : 0;
     a.pair = (pair && tiled) ? 1 : 0;  // (the fused epilogue is the tiled kernel's)
-    const bool few = !tiled && x_fp16 == nullptr && takes_few(M, K, int_scale), rows = int_scale && x_fp16 == nullptr && !prepared && takes_rows(M, N, K, pair);
+    const bool few = !tiled && x_fp16 == nullptr && takes_few(M, N, K, int_scale), rows = int_scale && x_fp16 == nullptr && !prepared && takes_rows(M, N, K, pair);
     if (few || rows) {
         FewArgs f;
         f.xq = xq;
@@ -595,7 +604,7 @@ static int gate_up_silu_common(const int8_t* xq, const float* a_scale, const voi
     // SiLU * up as that kernel's epilogue: the [M, 2 inter] tensor's place stays unused.  Float sums have to be the plain call's, whose order
     // goes with its plan: fused on that plan where it pairs the tiles (8 rows, 2 x 11008 x 4096: 11.3 us), else the plain call and
     // the second kernel (2 x 14336 x 4096 15.7 us, 13.0 fused on a plan of its own; 2 x 6144 x 4096 10.4 and 8.1).
-    if (takes_few(M, K, int_scale) && (int_scale || few_plan(M, N, K, false).ns % 2 == 0))
+    if (takes_few(M, N, K, int_scale) && (int_scale || few_plan(M, N, K, false).ns % 2 == 0))
         return gemm_pk_common(xq, nullptr, a_scale, nullptr, wpack, spack, chan_scale_packed, M, N, K, group, alpha_log2, out_fp16,
                               acc_out, workspace, gemm, stream, int_scale, false, true);
     const int st = gemm_pk_common(xq, nullptr, a_scale, nullptr, wpack, spack, chan_scale_packed, M, N, K, group,
@@ -835,12 +844,12 @@ int is_describe_prepacked(int M, int N, int K, int group, int int_scale, int fp1
     }
     PkPlan plan;
     const bool fused = fp16_in != 0 && M == 1 && pk_decode_plan(1, N, K, group, true, &plan);
-    if (!fused && takes_few(M, K, int_scale != 0)) {
+    if (!fused && takes_few(M, N, K, int_scale != 0)) {
         if (!pk_decode_plan(M, N, K, group, false, &plan)) return IS_ERR_UNSUPPORTED;
         few_kernel_name(few_plan(M, N, K, false), int_scale != 0, false, names, names_len);
         return IS_OK;
     }
-    if (!fused && !pk_decode_plan(M, N, K, group, false, &plan)) return IS_ERR_UNSUPPORTED;
+    if (!fused && !pk_decode_plan(M, N, K, group, false, &plan, int_scale == 0)) return IS_ERR_UNSUPPORTED;
     pk_decode_kernel_name(plan, int_scale != 0, fused, names, names_len);
     return IS_OK;
 }

@@ -22,6 +22,7 @@ struct FewPlan {
     int ns;     // 16-row weight tiles of a workgroup
     int waves;  // waves of a workgroup (the K split)
     int depth;  // K steps whose weights a wave has on their way
+    double us = 0.0;  // few_plan: fitted time of its loops and ends
 };
 
 // Mixture-of-experts form: xq / a_scale / out hold all experts' rows sorted by expert, expert e owning rows

@@ -1,6 +1,6 @@
-// One token row of the fine-grained W4A8 GEMM on prepacked weights (fp16, quantised inside the kernel, or int8 codes with a long K; 2 to 64
-// rows and the other single rows: gemm_few_pk.hip): a weight-streaming kernel with no synchronisation inside its main loop.  Its plan
-// covers up to 64 rows: it says how large the workspace of such calls is.  Integer-scale form: Eq. (2) / Table 2 "Ours" of the Integer Scale
+// Decode regime (at most 64 token rows) of the fine-grained W4A8 GEMM on prepacked weights: a weight-streaming kernel with no
+// synchronisation inside its main loop.  It takes single rows (fp16, quantised inside the kernel, or codes) and narrow matrices with a long
+// K, whose K range it cuts over workgroups; the kernel of gemm_few_pk.hip takes the rest.  Integer-scale form: Eq. (2) / Table 2 "Ours" of the Integer Scale
 // paper; float-scale form: Eq. (1) / Table 2 "Atom".
 //
 // Work split.  The weight matrix is a grid of 1 KB blocks (16 weight rows x 128 k, see pk_common.h).  K is cut into
@@ -716,19 +716,26 @@ constexpr int ring_depth(int mt) { return mt == 4 ? 6 : INTSCALE_PK_RING; }
 // Waves per workgroup the instantiations exist for (dispatch_waves and pk_decode_kernel_name both round with this).
 constexpr int waves_instance(int mt, int waves) { return waves <= 4 ? 4 : (waves <= 8 || mt == 4) ? 8 : 16; }
 
-template <bool INT_SCALE, bool FUSEQ>
+template <bool INT_SCALE, bool FUSEQ, int MT, int NR>
 hipError_t dispatch_waves(const PkArgs& a, const PkKernelPlan& kp, const PkPlan& plan, hipStream_t stream) {
-    constexpr int DT = ring_depth(1);
-    switch (waves_instance(1, plan.waves)) {
-        case 4: return launch_pk<1, DT, 4, 1, INT_SCALE, FUSEQ>(a, kp, plan, stream);
-        case 8: return launch_pk<1, DT, 8, 1, INT_SCALE, FUSEQ>(a, kp, plan, stream);
-        default: return launch_pk<1, DT, 16, 1, INT_SCALE, FUSEQ>(a, kp, plan, stream);
+    constexpr int DT = ring_depth(MT);
+    constexpr bool FQ = MT == 1 && FUSEQ;
+    switch (waves_instance(MT, plan.waves)) {
+        case 4: return launch_pk<MT, DT, 4, NR, INT_SCALE, FQ>(a, kp, plan, stream);
+        case 8: return launch_pk<MT, DT, 8, NR, INT_SCALE, FQ>(a, kp, plan, stream);
+        default:
+            if constexpr (MT != 4) return launch_pk<MT, DT, 16, NR, INT_SCALE, FQ>(a, kp, plan, stream);
+            return hipErrorInvalidValue;
     }
 }
 
 template <bool INT_SCALE>
 hipError_t dispatch_pk(const PkArgs& a, const PkKernelPlan& kp, const PkPlan& plan, hipStream_t stream) {
-    return a.x_fp16 ? dispatch_waves<INT_SCALE, true>(a, kp, plan, stream) : dispatch_waves<INT_SCALE, false>(a, kp, plan, stream);
+    if (a.x_fp16) return dispatch_waves<INT_SCALE, true, 1, 1>(a, kp, plan, stream);
+    if (a.M == 1) return dispatch_waves<INT_SCALE, false, 1, 1>(a, kp, plan, stream);
+    if (plan.mt == 1) return dispatch_waves<INT_SCALE, false, 1, 4>(a, kp, plan, stream);
+    if (plan.mt == 2) return dispatch_waves<INT_SCALE, false, 2, 4>(a, kp, plan, stream);
+    return dispatch_waves<INT_SCALE, false, 4, 4>(a, kp, plan, stream);
 }
 
 constexpr size_t kActBudget = 128 * 1024;  // LDS bytes for the slab's activations (the fused quantiser's scratch follows)
@@ -736,7 +743,7 @@ constexpr size_t kActBudget = 128 * 1024;  // LDS bytes for the slab's activatio
 }  // namespace
 
 // The split of a problem over the chip; false if this kernel does not cover it.
-bool pk_decode_plan(int M, int N, int K, int group, bool fp16_in, PkPlan* plan) {
+bool pk_decode_plan(int M, int N, int K, int group, bool fp16_in, PkPlan* plan, bool float_sums) {
     if (M < 1 || M > 64 || K % 128 != 0 || group % 128 != 0 || K % group != 0) return false;
     if (fp16_in && (M != 1 || (K >> 3) > kFuseChunks * 1024)) return false;
     if (pk_weight_bytes(N, K) >= (1ull << 31)) return false;
@@ -789,8 +796,9 @@ bool pk_decode_plan(int M, int N, int K, int group, bool fp16_in, PkPlan* plan) 
     const long long blocks = (long long)tiles_max * pl.max_steps;
     int waves = pl.mt == 4 ? 8 : 4;
     while (waves < (pl.mt == 4 ? 8 : 16) && (long long)waves * 2 * dt <= blocks) waves *= 2;
-    // The token's chunks over the threads; of int8 codes as well, where the row could have come in fp16: float sums then have one order.
-    if (M == 1 && (K >> 3) <= kFuseChunks * 1024)
+    // The token's chunks over the threads; for float sums of int8 codes as well, so that one row has them in one order whichever way it came
+    // (integer sums: 16 x 28672 7.0 us with 8 waves, 8.0 with 16)
+    if (fp16_in || (float_sums && M == 1 && (K >> 3) <= kFuseChunks * 1024))
         while ((K >> 3) > kFuseChunks * waves * kWave) waves *= 2;
     static const int env_waves = env_int("INTSCALE_PK_WAVES", 0);  // experiments; read once
     if (env_waves) {
@@ -830,9 +838,17 @@ size_t pk_decode_workspace_bytes(int M, int N, int K, int group) {
     return kPkCounterBytes + (size_t)((N + 15) / 16) * pl.slabs * pl.mt * 1024;
 }
 
+// A call's time in microseconds where K is cut: start, counters and end; blocks a workgroup carries, partial tiles the last one to arrive adds, the
+// slab of activations, the weights' way from memory (fit of 524 calls, 2 to 64 rows, 16 to 8000 columns, K up to 524288: 9 % off).
+double pk_decode_split_us(const PkPlan& p, int N, int K) {
+    const int tiles = ((N + 15) / 16 + p.wg_per_slab - 1) / p.wg_per_slab;
+    const double fill = (double)p.rows * p.mt * 128 * p.max_steps / kActBudget;
+    return 6.4 + 0.02 * p.mt * tiles * p.max_steps + 0.075 * p.mt * p.slabs + 3.6 * fill + 0.046e-6 * N * (double)K;
+}
+
 hipError_t launch_gemm_decode_pk(const PkArgs& a, bool int_scale, hipStream_t stream) {
     PkPlan plan;
-    if (a.M != 1 || !pk_decode_plan(a.M, a.N, a.K, a.group, a.x_fp16 != nullptr, &plan)) return hipErrorInvalidValue;
+    if (!pk_decode_plan(a.M, a.N, a.K, a.group, a.x_fp16 != nullptr, &plan, !int_scale)) return hipErrorInvalidValue;
     PkKernelPlan kp;
     kp.n16 = (a.N + 15) / 16;
     kp.steps = a.K / 128;

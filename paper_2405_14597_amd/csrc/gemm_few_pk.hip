@@ -627,7 +627,7 @@ FewPlan few_plan(int M, int N, int K, bool silu) {
         const double step = step_us(ms, ns), ends = ends_us(ms, ns);
         const double us = waves == 8 ? per_cu * (ends + 2 * run * step) : (per_cu / 2) * (ends + 2 * run * step) + (per_cu % 2) * (ends + run * step);
         if (best.ns == 0 || us < best_us) {
-            best = FewPlan{ms, ns, waves, depth};
+            best = FewPlan{ms, ns, waves, depth, us};
             best_us = us;
         }
     }

@@ -66,13 +66,14 @@ struct PkArgs {
     int pair = 0;
 };
 
-bool pk_decode_plan(int M, int N, int K, int group, bool fp16_in, PkPlan* plan);
+bool pk_decode_plan(int M, int N, int K, int group, bool fp16_in, PkPlan* plan, bool float_sums = false);
 size_t pk_decode_workspace_bytes(int M, int N, int K, int group);
+double pk_decode_split_us(const PkPlan& p, int N, int K);  // for plans of more than one slab
 hipError_t launch_prepack_w4(const uint8_t* qweight, const void* scale, bool float_scales, int N, int K, int group,
                              uint8_t* wpack, uint8_t* spack, hipStream_t stream, int pair_inter = 0,
                              const float* chan_scale = nullptr, float* chan_scale_packed = nullptr);
 // out[m, n] = fp16(SiLU(gu[m, 32 p + r]) * gu[m, 32 p + 16 + r]) for n = 16 p + r: the fp16 output of a GEMM on paired rows
-// (the route for up to 64 token rows, whose kernel has no fused epilogue)
+// (where the GEMM has no fused epilogue)
 hipError_t launch_silu_mul_paired(const __half* gu, int M, int N, __half* out, hipStream_t stream);
 hipError_t launch_gemm_decode_pk(const PkArgs& a, bool int_scale, hipStream_t stream);
 void pk_decode_kernel_name(const PkPlan& plan, bool int_scale, bool fp16_in, char* buf, size_t len);

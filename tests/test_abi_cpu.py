@@ -307,6 +307,17 @@ def test_described_kernels_are_the_sources_kernels():
         assert found[name.split("<")[0]] == ("<" in name), name
 
 
+# measured: a few workgroups that walk all of K lose 1.3 to 7 times to the kernel that cuts K over workgroups on the first six, and are 1.1 to
+# 1.7 times ahead on the others; the two kernels' names differ in their number of template arguments
+@pytest.mark.parametrize("M,N,K,cut", [(2, 64, 131072, True), (16, 2048, 65536, True), (64, 512, 28672, True), (64, 1024, 65536, True),
+                                       (32, 64, 524288, True), (16, 16, 65536, True), (32, 2048, 4096, False), (64, 1024, 4096, False),
+                                       (16, 4096, 11008, False), (32, 8192, 28672, False)])
+def test_which_kernel_prepacked_calls_of_few_rows_take(M, N, K, cut):
+    for int_scale in (True, False):
+        (name,) = P.is_describe_prepacked(M, N, K, 128, int_scale)
+        assert name.startswith("gemm_decode_pk_kernel<") and (name.count(",") == 5) == cut, name
+
+
 # measured: the tiled kernel is 5 to 15 % ahead on the first five (every unit has one tile and a long K range, or more than a full
 # round of tiles), the kernel whose waves split K 1.2 to 2.8 times on the others
 @pytest.mark.parametrize("M,N,K,wavek", [(1024, 8192, 28672, False), (2048, 4096, 20480, False), (512, 16384, 14336, False),

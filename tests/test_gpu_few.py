@@ -92,6 +92,14 @@ def test_groups_ragged_sizes_and_wide_scales(P, M, N, K, group, wide):
     check_call(P, M, N, K, group, wide, chan=not wide)
 
 
+# narrow matrices with a long K stay on the kernel that cuts K over workgroups
+@pytest.mark.parametrize("M,N,K", [(2, 20, 65536), (8, 64, 32768), (16, 300, 65536), (17, 33, 65536), (32, 528, 65536), (33, 48, 28672), (64, 512, 28672)])
+@pytest.mark.parametrize("wide", [False, True])
+def test_narrow_matrices_with_a_long_k(P, M, N, K, wide):
+    assert P.is_gemm_prepacked_workspace_bytes(M, N, K, G) > 0 and P.is_describe_prepacked(M, N, K, G)[-1].count(",") == 5
+    check_call(P, M, N, K, wide=wide)
+
+
 @pytest.mark.parametrize("M,inter,K", [(2, 16, 128), (16, 48, 1024), (17, 1200, 512), (40, 5504, 256), (64, 2064, 4096), (9, 14336, 256)])
 def test_fused_gate_up(P, M, inter, K):
     """The epilogue gives the bits of the GEMM's fp16 outputs taken through SiLU * up (the quantiser of that product, on either)."""
