@@ -270,9 +270,9 @@ int is_linear_w4a8_floatscale_prepacked(const void* x_fp16, const void* qweight_
  * sets prepacked one by one by is_prepack_w4 and stored back to back: expert e's weights at qweight_packed +
  * e * is_prepack_w4_weight_bytes(N,K), its scales (header included) at scales_packed + e * is_prepack_w4_scale_bytes(
  * N,K,group).  chan_scale [E,N] (may be NULL), row_offsets device int32 [E+1] as for the canonical grouped calls.
- * Every row count takes the MFMA-bound tiled kernel with 128-row tiles per expert (the call is built for prefill-sized
- * batches; for a handful of rows per expert the canonical grouped call streams the weights better).  The workspace
- * (is_gemm_grouped_prepacked_workspace_bytes, contents arbitrary) receives the activations re-ordered into MFMA
+ * Calls of up to about 40 rows per expert on average take a kernel for few rows where a fitted time says that it is
+ * faster, the others the MFMA-bound tiled kernel with 128-row tiles per expert.  For the latter the workspace
+ * (is_gemm_grouped_prepacked_workspace_bytes for either, contents arbitrary) receives the activations re-ordered into MFMA
  * operand blocks with every expert padded to whole 16-row tiles, the zero-point corrections and a table of the row
  * tiles.  Limits: num_experts <= 1024, (ceil(M_total/16) + num_experts) * 16 * K below 2^31.
  */

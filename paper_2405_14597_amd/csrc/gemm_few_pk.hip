@@ -477,39 +477,66 @@ __global__ __launch_bounds__(W* kWave) __attribute__((amdgpu_waves_per_eu(2, 2))
     few_tile<true, MS, NS, W, D, SILU>(a, t, smem_few);
 }
 
-// Mixture-of-experts form: workgroup (x, e) takes NS weight tiles of expert e and the expert's rows, 16 MT of them at a time; an expert
-// without rows costs a workgroup's start.
+// The nth of the row tiles (`rows_a_tile` rows) that experts have beside their first, by expert; false past the last one.  Uniform over
+// the wave, 64 experts at a time, a lane each.
+__device__ __forceinline__ bool further_tile(const FewGroups& g, int M, int rows_a_tile, int nth, int& expert, int& tile) {
+    const int lane = threadIdx.x & (kWave - 1);
+    for (int e0 = 0, base = 0; e0 < g.num_experts; e0 += kWave) {
+        const int e = e0 + lane;
+        const int rows = e < g.num_experts ? min(g.row_offsets[e + 1], M) - max(g.row_offsets[e], 0) : 0;
+        const int further = rows > 0 ? (rows - 1) / rows_a_tile : 0;
+        if (__ballot(further > 0) == 0) continue;
+        const int upto = base + lanes_up_to(further, lane);
+        const unsigned long long past = __ballot(nth < upto);
+        if (past != 0) {
+            const int who = __builtin_ctzll(past);
+            expert = __builtin_amdgcn_readfirstlane(e0 + who);
+            tile = __builtin_amdgcn_readfirstlane(nth - __shfl(upto - further, who, kWave) + 1);
+            return true;
+        }
+        base = __builtin_amdgcn_readfirstlane(__shfl(upto, kWave - 1, kWave));
+    }
+    return false;
+}
+
+// Mixture-of-experts form: workgroup (x, y) takes NS weight tiles of an expert and 16 MT of its rows at a time: the first E along y the
+// first rows of expert y (an expert without rows costs a workgroup's start), the others share what rows there are beyond them, so that an
+// expert that many rows come to has many workgroups at work (in turns of one workgroup, 64 experts of 2816 x 2048 and all 1536 rows at
+// one: #O us, #N this way; the tiled kernel 37).
 template <int MT, int NS, int W, int D, bool INT_SCALE>
 __global__ __launch_bounds__(W* kWave) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_decode_grouped_pk_kernel(FewArgs a, FewGroups g) {
     extern __shared__ __align__(16) unsigned char smem_few[];
-    const int e = blockIdx.y;
-    const int lo = max(g.row_offsets[e], 0), hi = min(g.row_offsets[e + 1], a.M);
-    FewTile t;
-    t.wpack = a.wpack + e * g.wstride;
-    t.spack = a.spack + e * g.sstride;
-    t.chan_scale = a.chan_scale ? a.chan_scale + (size_t)e * a.N : nullptr;
-    t.t0 = blockIdx.x * NS;
-    t.phase = blockIdx.x / 16;
-    for (int m = lo; m < hi; m += 16 * MT) {
-        if (m > lo) __syncthreads();  // the output tile of the rows before has been read
+    auto rows_of_expert = [&](int e, int m, int hi) __attribute__((always_inline)) {  // rows m to hi, 16 MT at most
+        FewTile t;
+        t.wpack = a.wpack + e * g.wstride;
+        t.spack = a.spack + e * g.sstride;
+        t.chan_scale = a.chan_scale ? a.chan_scale + (size_t)e * a.N : nullptr;
+        t.t0 = blockIdx.x * NS;
+        t.phase = blockIdx.x / 16;
         t.x = a.xq + (size_t)m * a.K;
         t.a_scale = a.a_scale + m;
         t.out = a.out + (size_t)m * a.N;
         t.acc_out = a.acc_out ? a.acc_out + (size_t)m * a.N : nullptr;
         t.m_rows = min(hi - m, 16 * MT);
         if constexpr (MT >= 4) {
-            if (t.m_rows > 32) {
-                few_tile<INT_SCALE, 4, NS, W, D, false>(a, t, smem_few);
-                continue;
-            }
+            if (t.m_rows > 32) return few_tile<INT_SCALE, 4, NS, W, D, false>(a, t, smem_few);
         }
         if constexpr (MT >= 2) {
-            if (t.m_rows > 16) {
-                few_tile<INT_SCALE, 2, NS, W, D, false>(a, t, smem_few);
-                continue;
-            }
+            if (t.m_rows > 16) return few_tile<INT_SCALE, 2, NS, W, D, false>(a, t, smem_few);
         }
         few_tile<INT_SCALE, 1, NS, W, D, false>(a, t, smem_few);
+    };
+    const int E = g.num_experts;
+    if ((int)blockIdx.y < E) {  // (twice in the code: what a loop keeps alive does not fit the registers, 4 % of 8 x 28672 x 4096)
+        const int m = max(g.row_offsets[blockIdx.y], 0), hi = min(g.row_offsets[blockIdx.y + 1], a.M);
+        if (m < hi) rows_of_expert(blockIdx.y, m, hi);
+        return;
+    }
+    int e = 0, tile = 0;
+    for (int nth = blockIdx.y - E; further_tile(g, a.M, 16 * MT, nth, e, tile); nth += gridDim.y - E) {
+        const int m = __builtin_amdgcn_readfirstlane(max(g.row_offsets[e], 0) + tile * 16 * MT);
+        rows_of_expert(e, m, __builtin_amdgcn_readfirstlane(min(g.row_offsets[e + 1], a.M)));
+        __syncthreads();  // the output tile has been read
     }
 }
 
@@ -533,8 +560,9 @@ hipError_t launch_grouped_instance(const FewArgs& a, const FewGroups& g, hipStre
     constexpr size_t lds = few_lds_bytes(MT, NS, W);
     const hipError_t r = limit.raise(reinterpret_cast<const void*>(kernel), (int)lds);
     if (r != hipSuccess) return r;
-    const int n16 = (a.N + 15) / 16;
-    hipLaunchKernelGGL(kernel, dim3((n16 + NS - 1) / NS, g.num_experts), dim3(W * kWave), lds, stream, with_launch_arguments(a, W), g);
+    // beside the experts' first tiles: as many workgroups as the chip holds at a time, or as there can be further tiles
+    const int wgs = ((a.N + 15) / 16 + NS - 1) / NS, further = std::min((a.M - 1) / (16 * MT), (2 * cu_count() + wgs - 1) / wgs);
+    hipLaunchKernelGGL(kernel, dim3(wgs, g.num_experts + further), dim3(W * kWave), lds, stream, with_launch_arguments(a, W), g);
     return hipGetLastError();
 }
 
@@ -653,8 +681,13 @@ hipError_t launch_gemm_few_grouped_pk(const FewArgs& a, const FewGroups& g, cons
 // 16 tokens, 115.7 -> 93.0 us, 64 tokens 109 -> 96.7; 4096 x 14336 61.3 -> 47.0 and 63.7 -> 47.9; 4 experts of 6144 x 2048, one per
 // token, 32 tokens 18.6 -> 8.6).  At 32 rows an expert the tiled kernel is ahead where the weights are large (28672 x 4096 115.6
 // against 123.4 us here) and behind where they are not (4096 x 14336 72.7 and 68.2, 6144 x 2048 23.7 and 10.6).
-// Rows are dealt as if the router were uniform (the offsets are on the device): workgroups of 32 rows, of 64 from 24 rows an expert on;
-// an expert with more is worked on in turns.
+// Rows are dealt as if the router were uniform (the offsets are on the device): workgroups of 32 rows, of 64 from 24 rows an expert on.
+// Within these limits by fitted times of both kernels (408 calls, 1 to 1024 experts, 12 and 18 % off): short K ranges and experts without
+// rows, whose workgroups start for nothing, belong to the tiled kernel, whose table leaves them out (128 experts of 15648 x 128, 7 rows, 14.6
+// us there and 52 here; 512 of 6192 x 256, 57 rows, 38 and 102; 256 of 8752 x 256, 3524 rows, 128 and 237; 128 of 2048 x 768, 512 rows 33 and
+// 36).  With a tenth to spare, on 259 other calls with rows dealt evenly, by Zipf's law, half at one expert or all: 0.52 to 0.61 of the tiled
+// kernel's time, two of 1036 slower than there by more than the runs differ (512 experts of 560 x 2432, 12282 rows, by Zipf's law 134 and
+// 144 us, all at one 68 and 91).
 FewPlan few_grouped_plan(int E, int M, int N, int K) {
     const int tiles = (N + 15) / 16;
     const double rows = (double)M / E;
@@ -662,12 +695,13 @@ FewPlan few_grouped_plan(int E, int M, int N, int K) {
     const int ms = rows <= 10.0 ? 1 : rows <= 24.0 ? 2 : 3;
     double idle = 1.0;  // share of the experts that no row comes to
     for (int i = 0; i < M && idle > 1e-3; ++i) idle *= 1.0 - 1.0 / E;
+    const double used = E * (1.0 - idle);
     int run = ((K >> 7) + 3) / 4;
     run += run & 1;
     FewPlan best{rows <= 24.0 ? 2 : 4, 0, 4, 2};
     double best_us = 0.0;
     for (int ns = 2; ns <= (best.ms == 2 ? 5 : 3); ++ns) {
-        const double per_cu = (tiles + ns - 1) / ns * (E * (1.0 - idle)) / cu_count();
+        const double per_cu = (tiles + ns - 1) / ns * used / cu_count();
         // rounds of two workgroups a unit, the last one as long as the others
         const double us = per_cu <= 1.05 ? ends_us(ms, ns) + run * step_us(ms, ns) : ceil(per_cu / 2 - 0.05) * (ends_us(ms, ns) + 2 * run * step_us(ms, ns));
         if (best.ns == 0 || us < best_us) {
@@ -675,7 +709,12 @@ FewPlan few_grouped_plan(int E, int M, int N, int K) {
             best_us = us;
         }
     }
-    return best;
+    const int slots = 2 * cu_count(), wgs = (tiles + best.ns - 1) / best.ns;
+    const double bytes = 1e-6 * N * (double)K * used;
+    const double here = 3.1 + 0.33 * wgs * E * idle / slots +
+                        std::max(1.0, wgs * used / slots) * (1.34 + 0.59 * ends_us(ms, best.ns) + 0.51 * 2 * run * step_us(ms, best.ns)) + 0.075 * bytes;
+    const double there = 10.4 + 0.085 * std::max(1.0, (N + 255) / 256 * used / cu_count()) * (19.5 + (K >> 7)) + 0.112 * bytes;
+    return here < 0.9 * there ? best : FewPlan{0, 0, 0, 0};
 }
 
 void few_grouped_kernel_name(const FewPlan& p, bool int_scale, char* buf, size_t len) {

@@ -138,16 +138,6 @@ __global__ __launch_bounds__(256) void prepare_activations_pk_kernel(const int8_
         if (s0 + j < steps) store_block((size_t)mt * steps + s0 + j, lane, v[j][0], v[j][1], xp, c0);
 }
 
-// Sum of v over the lanes up to and including this one.
-__device__ __forceinline__ int lanes_up_to(int v, int lane) {
-#pragma unroll
-    for (int d = 1; d < kWave; d *= 2) {
-        const int below = __shfl_up(v, d, kWave);
-        if (lane >= d) v += below;
-    }
-    return v;
-}
-
 // Mixture-of-experts form of the kernel above: block x is a 16-row tile of the padded row space (the 16-row tiles of
 // expert 0, then those of expert 1, ...); the first workgroup also lists the 128-row tiles.
 __global__ __launch_bounds__(256) void prepare_activations_grouped_pk_kernel(const int8_t* __restrict__ xq, int K,

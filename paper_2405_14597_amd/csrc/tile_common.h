@@ -101,6 +101,16 @@ __host__ __device__ inline int tile_slots(int M, int num_experts) { return (M + 
 
 inline size_t pad256(size_t bytes) { return (bytes + 255) & ~(size_t)255; }
 
+// Sum of v over the lanes up to and including this one.
+__device__ __forceinline__ int lanes_up_to(int v, int lane) {
+#pragma unroll
+    for (int d = 1; d < kWave; d *= 2) {
+        const int below = __shfl_up(v, d, kWave);
+        if (lane >= d) v += below;
+    }
+    return v;
+}
+
 }  // namespace
 }  // namespace intscale
 #endif

@@ -328,6 +328,18 @@ def test_which_kernel_prepacked_calls_of_moderate_rows_take(M, N, K, wavek):
         assert P.is_describe_prepacked(M, N, K, 128, int_scale)[1].startswith("gemm_wavek_kernel<" if wavek else "gemm_tile_pk_kernel<")
 
 
+# mixture of experts, measured with a uniform router: the tiled kernel is 1.1 to 3.6 times ahead on the first six (short K ranges, many
+# experts without rows), the kernel for few rows 1.2 to 3 times on the others
+@pytest.mark.parametrize("E,M,N,K,few", [(128, 7, 15648, 128, False), (512, 57, 6192, 256, False), (256, 3524, 8752, 256, False),
+                                         (128, 2243, 11216, 256, False), (64, 10, 29392, 512, False), (1024, 4000, 512, 512, False),
+                                         (8, 32, 28672, 4096, True), (8, 128, 4096, 14336, True), (128, 14, 432, 11776, True),
+                                         (4, 3, 624, 2944, True), (64, 384, 2816, 2048, True)])
+def test_which_kernel_mixture_calls_take(E, M, N, K, few):
+    for int_scale in (True, False):
+        name = P.is_describe_grouped_prepacked(E, M, N, K, 128, int_scale)[-1]
+        assert name.startswith("gemm_decode_grouped_pk_kernel<" if few else "gemm_tile_grouped_pk_kernel<"), name
+
+
 # the same for int8 weights (short K ranges, whose tiles' starts and ends decide), told by the workspace: the kernel whose waves
 # split K wants room for the activations' blocks
 @pytest.mark.parametrize("M,N,K,wavek", [(2048, 4096, 128, False), (4096, 4096, 128, False), (1579, 9442, 128, False),

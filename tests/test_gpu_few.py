@@ -158,7 +158,10 @@ def test_fused_gate_up_float_sums_in_one_order(P, M, inter, K):
 # experts without rows, with one, with more than a workgroup takes at a time (32 or 64), ragged widths, groups of several steps
 GROUPED = [(1, [5], 100, 256, 128), (4, [0, 3, 16, 17], 300, 640, 128), (8, [0, 0, 40, 1, 0, 33, 0, 0], 1000, 1536, 384),
            (4, [70, 1, 0, 25], 520, 1024, 128), (4, [40, 33, 64, 15], 264, 2048, 256), (16, [2] * 15 + [0], 4104, 384, 128),
-           (3, [0, 31, 64], 84, 1152, 1152), (2, [12, 4], 28672, 256, 128)]
+           (3, [0, 31, 64], 84, 1152, 1152), (2, [12, 4], 28672, 256, 128),
+           # many turns of one expert's rows, shared by more and by fewer workgroups; experts in several sets of 64
+           (64, [1] * 20 + [301] + [0] * 30 + [65] + [2] * 12, 200, 640, 128), (130, [0] * 66 + [97, 33] + [1] * 60 + [0, 200], 68, 1024, 256),
+           (4, [0, 0, 0, 155], 4112, 512, 128)]
 
 
 @pytest.mark.parametrize("E,rows,N,K,group", GROUPED)
@@ -189,6 +192,48 @@ def test_grouped(P, E, rows, N, K, group, wide):
     fs = torch.cat([reference(s[0][:r], s[1], f, group) for s, f, r in zip(sets, floats, rows)]) * sa.double()[:, None]
     size = torch.cat([reference(s[0][:r].abs().clamp(max=127), s[1].abs(), f.abs(), group) for s, f, r in zip(sets, floats, rows)]) * sa.double()[:, None]
     assert bool(((fout.double() - fs).abs() <= 5e-4 * fs.abs() + 2.0 ** -25 + size * (K // group + 2) * 2.0 ** -24)[fs.abs() < 65000.0].all())
+
+
+@pytest.mark.parametrize("E,M,N,K", [(64, 1536, 2816, 2048), (8, 190, 4096, 4096)])
+def test_grouped_with_all_rows_at_one_expert_takes_its_share_of_the_chip(P, E, M, N, K):
+    """The plan does not know the router: an expert that all rows come to must not be left to a few workgroups, turn after turn (5.5 times the
+    tiled kernel's time on the first of these once; half of it with the rows shared out).  Replayed graphs, the least of five."""
+    gen = torch.Generator(device="cuda:0").manual_seed(E + M)
+    q = torch.randint(0, 256, (E, N, K // 2), generator=gen, device="cuda:0", dtype=torch.uint8)
+    packed = P.is_prepack_w4_experts(q, torch.randint(0, 1025, (E, N, K // G), generator=gen, device="cuda:0", dtype=torch.int32), G)
+    xq = torch.randint(-128, 128, (M, K), generator=gen, device="cuda:0", dtype=torch.int8)
+    sa = torch.rand((M,), generator=gen, device="cuda:0")
+    offsets = torch.tensor([0] * (E // 2) + [M] * (E - E // 2 + 1), dtype=torch.int32, device="cuda:0")
+    ws = torch.zeros((P.is_gemm_grouped_prepacked_workspace_bytes(E, M, N, K, G),), dtype=torch.uint8, device="cuda:0")
+    us, outs = [], []
+    for route in ("auto", "tiled64"):
+        before = P.is_set_kernel_route(route)
+        try:
+            name = P.is_describe_grouped_prepacked(E, M, N, K, G)[-1]
+            assert name.startswith("gemm_decode_grouped_pk_kernel<") == (route == "auto"), name
+            out = torch.empty((M, N), dtype=torch.float16, device="cuda:0")
+            call = lambda: P.is_gemm_w4a8_intscale_grouped_prepacked(xq, sa, packed, None, offsets, 10, out=out, workspace=ws)
+            call()
+            torch.cuda.synchronize()
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph):
+                call()
+        finally:
+            P.is_set_kernel_route(before)
+        graph.replay()
+        least = 1e9
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(8):
+                graph.replay()
+            b.record()
+            torch.cuda.synchronize()
+            least = min(least, a.elapsed_time(b) * 125.0)
+        us.append(least)
+        outs.append(out.clone())
+    assert torch.equal(*outs)
+    assert us[0] < 1.5 * us[1], us
 
 
 # the kernel's tiles of 48 and 64 rows for more than 64 rows: one and several row tiles with remainders, ragged widths, uneven runs of
