@@ -693,8 +693,7 @@ FewPlan few_grouped_plan(int E, int M, int N, int K) {
     const double rows = (double)M / E;
     if (rows > 40.0 || (rows > 24.0 && (long long)E * tiles > 2048)) return FewPlan{0, 0, 0, 0};
     const int ms = rows <= 10.0 ? 1 : rows <= 24.0 ? 2 : 3;
-    double idle = 1.0;  // share of the experts that no row comes to
-    for (int i = 0; i < M && idle > 1e-3; ++i) idle *= 1.0 - 1.0 / E;
+    const double idle = pow(1.0 - 1.0 / E, M);  // share of the experts that no row comes to
     const double used = E * (1.0 - idle);
     int run = ((K >> 7) + 3) / 4;
     run += run & 1;

@@ -340,6 +340,22 @@ def test_which_kernel_mixture_calls_take(E, M, N, K, few):
         assert name.startswith("gemm_decode_grouped_pk_kernel<" if few else "gemm_tile_grouped_pk_kernel<"), name
 
 
+def test_mixture_plans_take_no_longer_for_more_rows():
+    """The host's part of a call must not grow with its rows or experts: planned through the describe call, the least of many."""
+    import time
+    lib = P.load_library()
+    buf = ctypes.create_string_buffer(256)
+
+    def least(M):
+        best = 1.0
+        for _ in range(300):
+            t = time.perf_counter()
+            lib.is_describe_grouped_prepacked(1024, M, 2816, 2048, 128, 1, buf, 256)
+            best = min(best, time.perf_counter() - t)
+        return best
+    assert least(20000) < 2.0 * least(16)
+
+
 # the same for int8 weights (short K ranges, whose tiles' starts and ends decide), told by the workspace: the kernel whose waves
 # split K wants room for the activations' blocks
 @pytest.mark.parametrize("M,N,K,wavek", [(2048, 4096, 128, False), (4096, 4096, 128, False), (1579, 9442, 128, False),
