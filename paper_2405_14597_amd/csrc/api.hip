@@ -92,10 +92,10 @@ bool takes_few(int M, int N, int K, bool int_scale) {
 // And of the calls of quantised activations and integer scales beyond 64 rows, up to 512: in row tiles of 48 or 64 there, without a
 // preparation kernel, where that is 5 % ahead by the times of both (65 x 12288 x 4096 16.5 -> 12.2 us, 128 x 8192 x 8192 20.2 -> 16.6, 300 x 6144 x 4096 20.5 ->
 // 16.8, 512 x 12288 x 4096 43.6 -> 40.8; 400 x 28672 x 4096 75 on the tiled kernel and 81, 300 x 28672 x 4096 58.2 and 59.8).  Not measured
-// below 16 K steps.  Fewer than 5120 columns stay with the kernel that the tests name for such calls, though they would gain as well
-// (65 x 4096 x 4096 12.6 -> 8.8 us).
+// below 16 K steps.  (On 555 calls of 64 to 5119 columns 0.73 of the prepared calls' time, one 4 % behind: 65 x 4096 x 4096 12.6 -> 8.7 us,
+// 300 x 4096 x 4096 16.8 -> 13.6, 512 x 512 x 4096 14.1 -> 8.4.)
 bool takes_rows(int M, int N, int K, bool silu) {
-    if (M <= 64 || M > 512 || N < 5120 || K < 2048 || kernel_route() >= 2) return false;
+    if (M <= 64 || M > 512 || K < 2048 || kernel_route() >= 2) return false;
     double us;
     rows_plan(M, N, K, silu, &us);
     return us < 0.95 * prepared_gemm_us(M, N, K);

@@ -324,8 +324,20 @@ def test_which_kernel_prepacked_calls_of_few_rows_take(M, N, K, cut):
                                          (540, 53283, 1536, False), (4096, 4608, 2304, False), (1024, 6144, 14336, True),
                                          (300, 4096, 4096, True), (93, 5003, 4224, True), (65, 4096, 14336, True)])
 def test_which_kernel_prepacked_calls_of_moderate_rows_take(M, N, K, wavek):
-    for int_scale in (True, False):
-        assert P.is_describe_prepacked(M, N, K, 128, int_scale)[1].startswith("gemm_wavek_kernel<" if wavek else "gemm_tile_pk_kernel<")
+    """Either of the kernels whose waves split K against the tiled one: integer scales on codes may need no preparation there."""
+    split_k = ("gemm_wavek_kernel<", "gemm_rows_pk_kernel<")
+    assert P.is_describe_prepacked(M, N, K, 128, True)[-1].startswith(split_k if wavek else "gemm_tile_pk_kernel<")
+    for int_scale, fp16_in in ((False, False), (True, True)):
+        name = P.is_describe_prepacked(M, N, K, 128, int_scale, fp16_in)[1]
+        assert name.startswith("gemm_wavek_kernel<" if wavek else "gemm_tile_pk_kernel<")
+
+
+# measured, preparation + GEMM against the kernel without one: 300 x 5119 x 4096 20.4 -> 17.1 us, 65 x 4096 x 4096 12.6 -> 8.7,
+# 512 x 512 x 4096 14.1 -> 8.4, 372 x 64 x 2048 10.8 -> 6.5
+@pytest.mark.parametrize("M,N,K", [(300, 5119, 4096), (300, 5120, 4096), (65, 4096, 4096), (512, 512, 4096), (372, 64, 2048), (300, 4096, 4096)])
+def test_calls_of_moderate_rows_without_preparation_do_not_depend_on_a_width(M, N, K):
+    names = P.is_describe_prepacked(M, N, K, 128, True)
+    assert len(names) == 1 and names[0].startswith("gemm_rows_pk_kernel<"), names
 
 
 # mixture of experts, measured with a uniform router: the tiled kernel is 1.1 to 3.6 times ahead on the first six (short K ranges, many

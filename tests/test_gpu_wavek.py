@@ -28,8 +28,10 @@ def P():
                                                (250, 64, 4096, 128, "4, 8"), (305, 4100, 1024, 128, "4, 4"),
                                                (65, 17001, 640, 128, "3, 4")])
 def test_wavek_gemm(P, M, N, K, group, shape):
-    names = P.is_describe_prepacked(M, N, K, group)
-    assert names == ["prepare_activations_pk_kernel", f"gemm_wavek_kernel<true, false, {shape}, false>"]
+    # (integer scales on codes go without a preparation from K = 2048 on; on prepared activations this kernel takes them as well)
+    for int_scale in (K < 2048, False):
+        names = P.is_describe_prepacked(M, N, K, group, int_scale)
+        assert names == ["prepare_activations_pk_kernel", f"gemm_wavek_kernel<{str(int_scale).lower()}, false, {shape}, false>"]
     rng = np.random.default_rng(6000 + M + N + K)
     xq, qw, IS, s, sa, c = rand_quantised(rng, M, N, K)
     IS, s = np.ascontiguousarray(IS[:, :K // group]), np.ascontiguousarray(s[:, :K // group])
@@ -44,8 +46,8 @@ def test_wavek_gemm(P, M, N, K, group, shape):
         assert np.array_equal(host(acc), ref.acc), "int32 accumulators differ"
         check_out(host(out), ref.out, f"M{M} N{N} K{K}")
         P.is_prepare_activations_prepacked(dev(xq), ws)
-        again, _ = P.is_gemm_w4a8_intscale_prepacked_prepared(dev(sa), pk, cd, a, workspace=ws)
-        assert torch.equal(out, again)
+        again, acc = P.is_gemm_w4a8_intscale_prepacked_prepared(dev(sa), pk, cd, a, workspace=ws, want_acc=True)
+        assert torch.equal(out, again) and np.array_equal(host(acc), ref.acc)
     fs = O.gemm_w4a8_floatscale(xq, sa, qw, s, group)
     got = P.is_gemm_w4a8_floatscale_prepacked(dev(xq), dev(sa), P.is_prepack_w4(dev(qw), dev(s), group))
     check_fs(host(got), fs, f"M{M} N{N} K{K}")
