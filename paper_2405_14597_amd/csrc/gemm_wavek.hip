@@ -506,8 +506,18 @@ bool wavek_is_faster(int M, int N, int K, bool w8) {
         return here < 9.5 + (double)((tiles + cus - 1) / cus) * (10.0 + 1.03 * steps);
     }
     if (tiles >= 2 * cus) return false;
-    const double there = tiled_us(tiles, steps);
-    if (steps < 16 || !p.by_padding || here < 0.85 * there || here > 1.15 * there) return here < there;
+    double there = tiled_us(tiles, steps), tie = 0.15;
+    if (steps < 16) {
+        // Runs of a few steps a wave: rounds of tiles of which the last may be part filled, against starts that weigh more than steps (fits of
+        // 1583 calls, 65 to 2100 rows, 256 to 40000 columns: 7 and 3 % off; with the coarser time for near ties the choice costs 0.1 % on
+        // average and 11 % at most): 85 x 6496 x 256 8.4 us here and 15.7 there; 802 x 8064 x 512 24.3 and 20.7, 657 x 11968 x 512 27.7 and 24.5;
+        // near ties: 300 x 27136 x 1664 38 and 41.
+        const double rounds = std::max(1.0, 0.5 * ((double)((p.tiles + cus - 1) / cus) + (double)p.tiles / cus));
+        here = 8.1 + rounds * (0.6 + 0.03 * p.ms + (steps + p.waves - 1) / p.waves * (0.155 + 0.106 * p.ms)) + 0.032e-6 * N * K;
+        there = 12.95 + (tiles <= cus ? 0.77 + 1.1 * steps : 1.4 + 1.57 * steps);
+        tie = 0.08;
+    }
+    if (!p.by_padding || here < (1.0 - tie) * there || here > (1.0 + tie) * there) return here < there;
     const double coarse = 10.0 + 0.76 * 0.25 * (double)((p.tiles + cus - 1) / cus) * steps * (2 * p.ms + 4) / 12.0;
     if (tiles > cus) return coarse < 6.0 + 2.3 * steps;
     const int parts = std::min(std::min(cus / (int)tiles, 8), std::max(steps / 8, 1));

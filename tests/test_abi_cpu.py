@@ -322,7 +322,10 @@ def test_which_kernel_prepacked_calls_of_few_rows_take(M, N, K, cut):
 # round of tiles), the kernel whose waves split K 1.2 to 2.8 times on the others
 @pytest.mark.parametrize("M,N,K,wavek", [(1024, 8192, 28672, False), (2048, 4096, 20480, False), (512, 16384, 14336, False),
                                          (540, 53283, 1536, False), (4096, 4608, 2304, False), (1024, 6144, 14336, True),
-                                         (300, 4096, 4096, True), (93, 5003, 4224, True), (65, 4096, 14336, True)])
+                                         (300, 4096, 4096, True), (93, 5003, 4224, True), (65, 4096, 14336, True),
+                                         # short K ranges: 8 to 18 % apart, the last two 9 and 46 %
+                                         (802, 8064, 512, False), (657, 11968, 512, False), (814, 7040, 256, False), (207, 24080, 128, False),
+                                         (269, 25264, 256, False), (300, 27136, 1664, True), (85, 6496, 256, True)])
 def test_which_kernel_prepacked_calls_of_moderate_rows_take(M, N, K, wavek):
     """Either of the kernels whose waves split K against the tiled one: integer scales on codes may need no preparation there."""
     split_k = ("gemm_wavek_kernel<", "gemm_rows_pk_kernel<")
