@@ -405,13 +405,9 @@ __device__ __forceinline__ void few_tile(const FewArgs& a, const FewTile& t, uns
     }
 }
 
-// Row classes of the work split: 1, 2 or 4 tiles of 16 token rows, MS of which hold rows.
-constexpr int row_class(int ms) { return ms == 3 ? 4 : ms; }
-
 // (two waves per SIMD: 256 registers a wave, and MFMA results in ordinary registers, where the scale step reads them)
-template <int MT, int MS, int NS, int W, int D, bool INT_SCALE, bool SILU>
-__global__ __launch_bounds__(W* kWave) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_decode_pk_kernel(FewArgs a) {
-    static_assert(MT == row_class(MS), "row class");
+template <int MS, int NS, int W, int D, bool INT_SCALE, bool SILU>
+__global__ __launch_bounds__(W* kWave) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_few_pk_kernel(FewArgs a) {
     extern __shared__ __align__(16) unsigned char smem_few[];
     FewTile t;
     t.x = a.xq;
@@ -439,7 +435,7 @@ FewArgs with_launch_arguments(const FewArgs& a, int waves) {
 template <bool INT_SCALE, int MS, int NS, int W, int D, bool SILU>
 hipError_t launch_instance(const FewArgs& a, hipStream_t stream) {
     static LdsLimit limit;  // per instantiation
-    auto kernel = gemm_decode_pk_kernel<row_class(MS), MS, NS, W, D, INT_SCALE, SILU>;
+    auto kernel = gemm_few_pk_kernel<MS, NS, W, D, INT_SCALE, SILU>;
     constexpr size_t lds = few_lds_bytes(MS, NS, W);
     static_assert(lds <= 160 * 1024, "LDS of a compute unit");
     const hipError_t r = limit.raise(reinterpret_cast<const void*>(kernel), (int)lds);
@@ -504,7 +500,7 @@ __device__ __forceinline__ bool further_tile(const FewGroups& g, int M, int rows
 // expert that many rows come to has many workgroups at work (in turns of one workgroup, 64 experts of 2816 x 2048 and all 1536 rows at
 // one: #O us, #N this way; the tiled kernel 37).
 template <int MT, int NS, int W, int D, bool INT_SCALE>
-__global__ __launch_bounds__(W* kWave) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_decode_grouped_pk_kernel(FewArgs a, FewGroups g) {
+__global__ __launch_bounds__(W* kWave) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_few_grouped_pk_kernel(FewArgs a, FewGroups g) {
     extern __shared__ __align__(16) unsigned char smem_few[];
     auto rows_of_expert = [&](int e, int m, int hi) __attribute__((always_inline)) {  // rows m to hi, 16 MT at most
         FewTile t;
@@ -556,7 +552,7 @@ hipError_t launch_rows_instance(const FewArgs& a, hipStream_t stream) {
 template <int MT, int NS, int W, int D, bool INT_SCALE>
 hipError_t launch_grouped_instance(const FewArgs& a, const FewGroups& g, hipStream_t stream) {
     static LdsLimit limit;  // per instantiation
-    auto kernel = gemm_decode_grouped_pk_kernel<MT, NS, W, D, INT_SCALE>;
+    auto kernel = gemm_few_grouped_pk_kernel<MT, NS, W, D, INT_SCALE>;
     constexpr size_t lds = few_lds_bytes(MT, NS, W);
     const hipError_t r = limit.raise(reinterpret_cast<const void*>(kernel), (int)lds);
     if (r != hipSuccess) return r;
@@ -663,8 +659,7 @@ FewPlan few_plan(int M, int N, int K, bool silu) {
 }
 
 void few_kernel_name(const FewPlan& p, bool int_scale, bool silu, char* buf, size_t len) {
-    snprintf(buf, len, "gemm_decode_pk_kernel<%d, %d, %d, %d, %d, %s, %s>", row_class(p.ms), p.ms, p.ns, p.waves, p.depth,
-             int_scale ? "true" : "false", silu ? "true" : "false");
+    snprintf(buf, len, "gemm_few_pk_kernel<%d, %d, %d, %d, %s, %s>", p.ms, p.ns, p.waves, p.depth, int_scale ? "true" : "false", silu ? "true" : "false");
 }
 
 hipError_t launch_gemm_few_pk(const FewArgs& a, const FewPlan& p, bool int_scale, bool silu, hipStream_t stream) {
@@ -717,7 +712,7 @@ FewPlan few_grouped_plan(int E, int M, int N, int K) {
 }
 
 void few_grouped_kernel_name(const FewPlan& p, bool int_scale, char* buf, size_t len) {
-    snprintf(buf, len, "gemm_decode_grouped_pk_kernel<%d, %d, %d, %d, %s>", p.ms, p.ns, p.waves, p.depth, int_scale ? "true" : "false");
+    snprintf(buf, len, "gemm_few_grouped_pk_kernel<%d, %d, %d, %d, %s>", p.ms, p.ns, p.waves, p.depth, int_scale ? "true" : "false");
 }
 
 // Moderate numbers of rows in tiles of 48 or 64: the plan and its time in microseconds, launch and weights' way from memory included (the

@@ -349,10 +349,10 @@ def test_prepacked_33_to_64_rows_random_shapes_match_the_canonical_call(P, tiled
 @pytest.mark.parametrize("M,N,K", [(64, 8192, 28672), (40, 28672, 8192)])
 def test_prepacked_33_to_64_rows_on_large_weights_take_the_tiled_kernel(P, M, N, K):
     """From 2^27 weights on the library itself picks the tiled kernel for 33..64 rows (the LLaMA-2-70B gate and down
-    projections), and the weight-streaming kernel below (its qkv projection)."""
+    projections), and the kernel for few rows below (its qkv projection, and these up to 32 rows)."""
     assert P.is_describe_prepacked(M, N, K, G)[-1] == "gemm_tile_pk_kernel<true>"
-    assert P.is_describe_prepacked(M, 10240, 8192, G)[-1].startswith("gemm_decode_pk_kernel<4, ")
-    assert P.is_describe_prepacked(32, N, K, G)[-1].startswith("gemm_decode_pk_kernel<2, ")
+    assert P.is_describe_prepacked(M, 10240, 8192, G)[-1].startswith(f"gemm_few_pk_kernel<{(M + 15) // 16}, ")
+    assert P.is_describe_prepacked(32, N, K, G)[-1].startswith("gemm_few_pk_kernel<2, ")
     rng = np.random.default_rng(3950 + M)
     xq, qw, IS, s, sa, c = rand_quantised(rng, M, N, K)
     ref = O.gemm_w4a8_intscale(xq, sa, qw, IS, c, G, 10)
