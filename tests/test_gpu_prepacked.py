@@ -104,10 +104,12 @@ def test_prepacked_gemm_floatscale(P, M, N, K):
     check_fs(host(out), fs, f"M{M} N{N} K{K}")
 
 
-@pytest.mark.parametrize("M,K", [(16, 4096), (64, 4096), (32, 8192)])
+@pytest.mark.parametrize("M,K", [(16, 4096), (64, 4096), (32, 8192), (1, 28672), (16, 65536), (32, 65536), (64, 28672)])
 def test_prepacked_extreme_codes_and_wide_scales(P, M, K):
     """All codes at -128 / -8, negative and wider-than-24-bit integer scales, wrap-around; with and without K split."""
     N = 32
+    assert P.is_describe_prepacked(M, N, K, G)[0].startswith("gemm_decode_pk_kernel<" if K >= 28672 else "gemm_few_pk_kernel<")
+    assert K < 28672 or P.is_gemm_prepacked_workspace_bytes(M, N, K, G) > 0
     xq = np.full((M, K), -128, np.int8)
     q = np.full((N, K), -8, np.int8)
     xq[1::2] = 127
@@ -146,8 +148,8 @@ def test_prepacked_wider_groups(P, M, group):
 
 
 def test_prepacked_split_k_workspace_reuse(P):
-    """The arrival counters of the K split are left zero: one zeroed workspace serves call after call, of different
-    shapes, and the results do not change from call to call."""
+    """One zeroed workspace of the size asked for serves call after call, of different shapes, and the results do not change from call to
+    call (the kernel that takes these shapes leaves it alone; the ones that use it: below)."""
     shapes = [(64, 2064, 4096), (32, 528, 8192), (64, 48, 11008), (64, 2064, 4096)]
     need = max(P.is_gemm_prepacked_workspace_bytes(M, N, K, G) for M, N, K in shapes)
     assert need > 0
@@ -169,6 +171,47 @@ def test_prepacked_split_k_workspace_reuse(P):
         assert torch.equal(a, b), "float-scale partials are added in a fixed order"
     torch.cuda.synchronize()
     assert int(ws[: 64 * 1024].view(torch.int32).abs().max()) == 0
+
+
+# K cut over workgroups: one row (on codes, and in fp16 through the linear call) and narrow matrices with a long K
+SPLIT_K_SHAPES = [(1, 64, 16384), (64, 512, 28672), (1, 64, 28672), (16, 64, 65536), (33, 48, 28672), (2, 300, 65536), (1, 48, 12288), (17, 64, 65536)]
+
+
+def test_prepacked_split_k_leaves_the_counters_zero(P):
+    """The calls that store partial tiles and raise arrival counters, one workspace for all of them, of different shapes in turn; and the linear
+    call on one fp16 row, whose GEMM part of the workspace lies behind the codes and the token scale."""
+    need = max(P.is_gemm_prepacked_workspace_bytes(M, N, K, G) for M, N, K in SPLIT_K_SHAPES)
+    ws = torch.zeros((need,), dtype=torch.uint8, device="cuda:0")
+    for M, N, K in SPLIT_K_SHAPES + SPLIT_K_SHAPES[:2]:
+        for int_scale in (True, False):
+            assert P.is_gemm_prepacked_workspace_bytes(M, N, K, G) > 64 * 1024
+            assert P.is_describe_prepacked(M, N, K, G, int_scale)[0].startswith("gemm_decode_pk_kernel<")
+        rng = np.random.default_rng(301 + M + N + K)
+        xq, qw, IS, s, sa, c = rand_quantised(rng, M, N, K)
+        ref = O.gemm_w4a8_intscale(xq, sa, qw, IS, c, G, 10)
+        pk, pkf = P.is_prepack_w4(dev(qw), dev(IS), G), P.is_prepack_w4(dev(qw), dev(s), G)
+        fs = O.gemm_w4a8_floatscale(xq, sa, qw, s, G)
+        floats = []
+        for _ in range(2):
+            ws[64 * 1024:].random_(0, 256)   # the partial tiles' place may hold anything
+            out, acc = P.is_gemm_w4a8_intscale_prepacked(dev(xq), dev(sa), pk, dev(c), 10, want_acc=True, workspace=ws)
+            assert np.array_equal(host(acc), ref.acc), f"M{M} N{N} K{K}"
+            check_out(host(out), ref.out)
+            floats.append(P.is_gemm_w4a8_floatscale_prepacked(dev(xq), dev(sa), pkf, workspace=ws))
+            check_fs(host(floats[-1]), fs)
+            assert int(ws[: 64 * 1024].view(torch.int32).abs().max()) == 0
+        assert torch.equal(*floats), "float-scale partials are added in a fixed order"
+        if M == 1:
+            assert P.is_describe_prepacked(M, N, K, G, True, True)[0].endswith("true, true>")
+            lin = torch.zeros((P.is_linear_prepacked_workspace_bytes(M, N, K, G),), dtype=torch.uint8, device="cuda:0")
+            x = S.activations_outlier(M, K, 9)
+            xr, sr = O.quantize_act_int8_token(x)
+            want = O.gemm_w4a8_intscale(xr, sr, qw, IS, c, G, 10).acc
+            at = (K + 255) // 256 * 256 + 256
+            for _ in range(3):
+                _, acc = P.is_linear_w4a8_intscale_prepacked(dev(x), pk, dev(c), 10, want_acc=True, workspace=lin)
+                assert np.array_equal(host(acc), want)
+                assert int(lin[at:at + 64 * 1024].view(torch.int32).abs().max()) == 0
 
 
 LINEAR_PK_SHAPES = [(1, 4096, 4096), (1, 12288, 4096), (1, 4096, 11008), (1, 272, 12288), (1, 40, 1024), (1, 16, 128),

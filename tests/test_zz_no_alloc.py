@@ -38,6 +38,12 @@ def run_both(M, N, K, seed, dev):
 def test_noalloc_matches_workspace_form_on_two_calls_in_a_row():
     dev = torch.device("cuda:0")
     # K split across workgroups: partial sums and arrival counters live in the scratch
+    for shape in ((64, 512, 28672), (1, 64, 28672), (16, 64, 65536), (64, 512, 28672), (1, 64, 16384)):
+        assert P.is_gemm_prepacked_workspace_bytes(*shape, G) > 64 * 1024
+        assert P.is_describe_prepacked(*shape, G)[0].startswith("gemm_decode_pk_kernel<")
+        print("noalloc split K", shape, flush=True)
+        run_both(*shape, 10 + shape[0], dev)
+    # calls of few rows that ask for a workspace and leave it alone
     big, small = (32, 2048, 28672), (5, 528, 8192)
     assert P.is_gemm_prepacked_workspace_bytes(*big, G) > 0 and P.is_gemm_prepacked_workspace_bytes(*small, G) > 0
     assert P.is_gemm_prepacked_workspace_bytes(*small, G) < P.is_gemm_prepacked_workspace_bytes(*big, G)
@@ -51,9 +57,11 @@ def test_noalloc_matches_workspace_form_on_two_calls_in_a_row():
     print("noalloc tiled", tbig, tsmall, flush=True)
     run_both(*tbig, 21, dev)
     run_both(*tsmall, 22, dev)
-    # a shape without workspace, and the decode shape again after the tiled calls wrote over the counters' place
+    # a shape without workspace, and decode shapes again after the tiled calls wrote over the counters' place
     run_both(3, 4096, 4096, 31, dev)
     run_both(*small, 32, dev)
+    run_both(1, 64, 28672, 33, dev)
+    run_both(64, 512, 28672, 34, dev)
 
 
 def test_noalloc_rejects_sizes_beyond_the_scratch():
