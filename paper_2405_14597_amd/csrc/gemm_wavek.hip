@@ -413,7 +413,10 @@ hipError_t launch_instance(const WavekArgs& a, hipStream_t stream) {
 
 template <bool INT_SCALE, bool W8, bool SILU>
 hipError_t launch_shape(const WavekArgs& a, const WavekPlan& p, hipStream_t stream) {
-    if (p.ms == 5) return p.waves == 8 ? launch_instance<INT_SCALE, W8, 5, 8, SILU>(a, stream) : launch_instance<INT_SCALE, W8, 5, 4, SILU>(a, stream);
+    if constexpr (!W8) {
+        if (p.ms == 5 && p.waves == 8) return launch_instance<INT_SCALE, W8, 5, 8, SILU>(a, stream);
+    }
+    if (p.ms == 5) return launch_instance<INT_SCALE, W8, 5, 4, SILU>(a, stream);
     if (p.ms == 3) return p.waves == 8 ? launch_instance<INT_SCALE, W8, 3, 8, SILU>(a, stream) : launch_instance<INT_SCALE, W8, 3, 4, SILU>(a, stream);
     return p.waves == 8 ? launch_instance<INT_SCALE, W8, 4, 8, SILU>(a, stream) : launch_instance<INT_SCALE, W8, 4, 4, SILU>(a, stream);
 }
@@ -457,7 +460,7 @@ WavekPlan wavek_plan(int M, int N, int K, bool w8) {
         // both 41.9 us by the times, 42.8 with 64 rows and 45.9 with 48).
         const double rule = p.us;
         for (int ms = 3; ms <= 5; ++ms)
-            for (int waves = 4; waves <= 8; waves += 4) {
+            for (int waves = 4; waves <= (w8 && ms == 5 ? 4 : 8); waves += 4) {  // (80 rows of int8 weights: eight waves never ahead by these times)
                 const double us = wavek_us(M, N, K, w8, ms, waves);
                 if (us < p.us) {
                     p.us = us;
