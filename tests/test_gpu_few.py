@@ -253,6 +253,11 @@ def test_more_than_64_rows(P, M, N, K, group, wide):
 @pytest.mark.parametrize("M,inter,K", [(65, 2576, 2048), (100, 5504, 2176), (200, 4096, 2048), (256, 2560, 4096)])
 def test_more_than_64_rows_fused_gate_up(P, M, inter, K):
     test_fused_gate_up(P, M, inter, K)
+    # which kernel took the call: this one leaves the workspace alone, the others write the activations' blocks to it
+    xq, _, qw, scale, sa, c = case(M, 2 * inter, K)
+    ws = torch.full((P.is_gemm_gate_up_silu_prepacked_workspace_bytes(M, inter, K, G),), 0x5A, dtype=torch.uint8, device="cuda:0")
+    P.is_gemm_w4a8_intscale_gate_up_silu_prepacked(xq, sa, P.is_prepack_w4_gate_up(qw, scale, c, G), 10, workspace=ws)
+    assert bool((ws == 0x5A).all())
 
 
 # int8 weights: 16-row token tiles of 1 to 4, one and two weight tiles a workgroup (more than 4096 columns), ragged rows and columns,

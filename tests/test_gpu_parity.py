@@ -415,11 +415,12 @@ def test_w8_weight_quantizer_bit_exact(P, N, K, group, alpha, mode):
                                          (65, 256, 128, 128), (129, 300, 1024, 128), (300, 700, 1152, 128),
                                          (200, 264, 1024, 256), (130, 80, 512, 512), (513, 257, 512, 128),
                                          (1, 4096, 14336, 128), (24, 1040, 2048, 256), (33, 100, 1024, 1024),
-                                         (48, 2064, 3584, 128)])
-@pytest.mark.parametrize("route", ["auto", "tiled"])
+                                         (48, 2064, 3584, 128), (3, 272, 896, 128), (64, 100, 768, 256)])
+@pytest.mark.parametrize("route", ["auto", "general", "tiled"])
 def test_w8a8_gemm(P, route_setting, route, M, N, K, group):
-    """Up to 64 token rows the library takes the general (bandwidth-bound) kernel, above that the tiled one; "tiled"
-    sends every shape to the tiled kernel."""
+    """Up to 64 token rows the library takes the kernel whose waves split K (integer scales, K from 1024 on) or the general one, above that
+    the other kernel whose waves split K or the tiled one; "general" sends all of up to 64 rows to the general kernel, "tiled" every shape to
+    the tiled one."""
     route_setting(route)
     rng = np.random.default_rng(4000 + M + N + K)
     xq = rng.integers(-128, 128, size=(M, K)).astype(np.int8)

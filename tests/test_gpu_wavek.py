@@ -6,6 +6,7 @@ import numpy as np
 import pytest
 
 from oracle import oracle as O
+import test_gpu_few as few
 from test_gpu_parity import check_fs, check_out, dev, host, rand_quantised
 
 torch = pytest.importorskip("torch")
@@ -105,6 +106,55 @@ def test_wavek_w8(P, M, N, K, group):
     s = (rng.random((N, K // group)) * 1e-4).astype(np.float32)
     fs = O.gemm_w8a8_floatscale(xq, sa, q, s, group)
     check_fs(host(P.is_gemm_w8a8_floatscale(dev(xq), dev(sa), dev(q), dev(s), group)), fs, f"M{M} N{N} K{K}")
+
+
+# row tiles of 80 rows: workgroups of eight waves, whose partial sums meet in two passes, and of four; the last row tile part filled
+EIGHTY = [(675, 1500, 2688, 384, "5, 8"), (530, 2048, 2688, 128, "5, 8"), (515, 4100, 2048, 256, "5, 4"), (645, 3008, 2048, 128, "5, 4")]
+
+
+@pytest.mark.parametrize("M,N,K,group,shape", EIGHTY)
+@pytest.mark.parametrize("wide", [False, True])
+def test_wavek_tiles_of_80_rows(P, M, N, K, group, shape, wide):
+    for int_scale in (True, False):
+        name = P.is_describe_prepacked(M, N, K, group, int_scale)[-1]
+        assert name == f"gemm_wavek_kernel<{str(int_scale).lower()}, false, {shape}, false>"
+    few.check_call(P, M, N, K, group, wide, chan=not wide)
+
+
+@pytest.mark.parametrize("M,inter,K,shape", [(530, 1024, 2688, "5, 8"), (645, 1504, 2048, "5, 4")])
+def test_wavek_tiles_of_80_rows_fused_gate_up(P, M, inter, K, shape):
+    for int_scale in (True, False):
+        assert P.is_describe_prepacked(M, 2 * inter, K, 128, int_scale)[-1] == f"gemm_wavek_kernel<{str(int_scale).lower()}, false, {shape}, false>"
+    few.test_fused_gate_up(P, M, inter, K)
+    few.test_fused_gate_up_float_sums_in_one_order(P, M, inter, K)
+
+
+@pytest.mark.parametrize("M,N,K,group", [(65, 8200, 2688, 384), (195, 4100, 2688, 128)])
+@pytest.mark.parametrize("wide", [False, True])
+def test_wavek_w8_tiles_of_80_rows(P, M, N, K, group, wide):
+    xq, _, _, scale, sa, c = few.case(M, N, K, group, wide, seed=8)
+    q = torch.randint(-128, 128, (N, K), generator=torch.Generator(device="cuda:0").manual_seed(N + K), device="cuda:0", dtype=torch.int8)
+    acc = few.wrapped(few.reference(xq, q, scale, group))
+    ws = torch.full((P.is_gemm_w8a8_workspace_bytes(M, N, K, group),), 0x5A, dtype=torch.uint8, device="cuda:0")
+    out, got = P.is_gemm_w8a8_intscale(xq, sa * 2.0 ** -6, q, scale, c, group, 10, want_acc=True, workspace=ws)
+    assert torch.equal(got, acc), "int32 accumulators"
+    blocks = torch.zeros((P.is_gemm_prepacked_workspace_bytes(M, N, K, group),), dtype=torch.uint8, device="cuda:0")
+    P.is_prepare_activations_prepacked(xq, blocks)
+    blocks = blocks[:(M + 15) // 16 * 16 * K]
+    assert torch.equal(ws[:blocks.numel()], blocks), "the kernel whose waves split K"
+    before = P.is_set_kernel_route("tiled")
+    try:
+        tiled, tiled_acc = P.is_gemm_w8a8_intscale(xq, sa * 2.0 ** -6, q, scale, c, group, 10, want_acc=True)
+    finally:
+        P.is_set_kernel_route(before)
+    assert torch.equal(tiled_acc, got) and torch.equal(tiled, out)
+    s = scale.float() * (2.0 ** -32 if wide else 2.0 ** -23)
+    fs = few.reference(xq, q, s, group) * sa.double()[:, None]
+    size = few.reference(xq.abs().clamp(max=127), q.abs().clamp(max=127), s.abs(), group) * sa.double()[:, None]
+    fout = P.is_gemm_w8a8_floatscale(xq, sa, q, s, group)
+    # (as for the other recipe: the sum of K / group products in fp32; magnitudes clamped at 127 for 128, hence the hundredth)
+    bound = 5e-4 * fs.abs() + 2.0 ** -25 + 1.02 * size * (K // group + 2) * 2.0 ** -24
+    assert bool(((fout.double() - fs).abs() <= bound)[fs.abs() < 65000.0].all())
 
 
 def test_w8_workspace_of_the_tiled_kernel_is_enough(P):
