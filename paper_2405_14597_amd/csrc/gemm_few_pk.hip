@@ -499,40 +499,83 @@ __device__ __forceinline__ bool further_tile(const FewGroups& g, int M, int rows
 // first rows of expert y (an expert without rows costs a workgroup's start), the others share what rows there are beyond them, so that an
 // expert that many rows come to has many workgroups at work (in turns of one workgroup, 64 experts of 2816 x 2048 and all 1536 rows at
 // one: #O us, #N this way; the tiled kernel 37).
+struct FewGroupedArgs {
+    FewArgs a;
+    FewGroups g;
+};
+
+template <class T>
+__device__ __forceinline__ T* in_global(T* p) { return (T*)(__attribute__((address_space(1))) T*)p; }
+
+// The kernel's only argument read once more, in a way that the compiler cannot see through: a loop that reads it so each time keeps nothing
+// of it alive.  (What it kept otherwise took 70 to 100 scalar registers more than there are, and scratch memory in two instances.)
+__device__ __forceinline__ FewGroupedArgs arguments_again() {
+    typedef __attribute__((address_space(4))) const FewGroupedArgs* args_t;
+    args_t p = (args_t)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    FewGroupedArgs r;
+    r.a.xq = in_global(p->a.xq);
+    r.a.a_scale = in_global(p->a.a_scale);
+    r.a.wpack = in_global(p->a.wpack);
+    r.a.spack = in_global(p->a.spack);
+    r.a.chan_scale = in_global(p->a.chan_scale);
+    r.a.out = in_global(p->a.out);
+    r.a.acc_out = in_global(p->a.acc_out);
+    r.a.M = p->a.M;
+    r.a.N = p->a.N;
+    r.a.K = p->a.K;
+    r.a.group = p->a.group;
+    r.a.alpha_log2 = p->a.alpha_log2;
+    r.a.num_groups = p->a.num_groups;
+    r.a.phase_mask = p->a.phase_mask;
+    r.g.row_offsets = in_global(p->g.row_offsets);
+    r.g.num_experts = p->g.num_experts;
+    r.g.wstride = p->g.wstride;
+    r.g.sstride = p->g.sstride;
+    return r;
+}
+
+// Rows m to hi of expert e, 16 MT of them at most
 template <int MT, int NS, int W, int D, bool INT_SCALE>
-__global__ __launch_bounds__(W* kWave) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_few_grouped_pk_kernel(FewArgs a, FewGroups g) {
+__device__ __forceinline__ void few_rows_of_expert(const FewGroupedArgs& p, int e, int m, int hi, unsigned char* smem) {
+    const FewArgs& a = p.a;
+    FewTile t;
+    t.wpack = a.wpack + e * p.g.wstride;
+    t.spack = a.spack + e * p.g.sstride;
+    t.chan_scale = a.chan_scale ? a.chan_scale + (size_t)e * a.N : nullptr;
+    t.t0 = blockIdx.x * NS;
+    t.phase = blockIdx.x / 16;
+    t.x = a.xq + (size_t)m * a.K;
+    t.a_scale = a.a_scale + m;
+    t.out = a.out + (size_t)m * a.N;
+    t.acc_out = a.acc_out ? a.acc_out + (size_t)m * a.N : nullptr;
+    t.m_rows = min(hi - m, 16 * MT);
+    if constexpr (MT >= 4) {
+        if (t.m_rows > 32) return few_tile<INT_SCALE, 4, NS, W, D, false>(a, t, smem);
+    }
+    if constexpr (MT >= 2) {
+        if (t.m_rows > 16) return few_tile<INT_SCALE, 2, NS, W, D, false>(a, t, smem);
+    }
+    few_tile<INT_SCALE, 1, NS, W, D, false>(a, t, smem);
+}
+
+template <int MT, int NS, int W, int D, bool INT_SCALE>
+__global__ __launch_bounds__(W* kWave) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_few_grouped_pk_kernel(FewGroupedArgs args) {
     extern __shared__ __align__(16) unsigned char smem_few[];
-    auto rows_of_expert = [&](int e, int m, int hi) __attribute__((always_inline)) {  // rows m to hi, 16 MT at most
-        FewTile t;
-        t.wpack = a.wpack + e * g.wstride;
-        t.spack = a.spack + e * g.sstride;
-        t.chan_scale = a.chan_scale ? a.chan_scale + (size_t)e * a.N : nullptr;
-        t.t0 = blockIdx.x * NS;
-        t.phase = blockIdx.x / 16;
-        t.x = a.xq + (size_t)m * a.K;
-        t.a_scale = a.a_scale + m;
-        t.out = a.out + (size_t)m * a.N;
-        t.acc_out = a.acc_out ? a.acc_out + (size_t)m * a.N : nullptr;
-        t.m_rows = min(hi - m, 16 * MT);
-        if constexpr (MT >= 4) {
-            if (t.m_rows > 32) return few_tile<INT_SCALE, 4, NS, W, D, false>(a, t, smem_few);
-        }
-        if constexpr (MT >= 2) {
-            if (t.m_rows > 16) return few_tile<INT_SCALE, 2, NS, W, D, false>(a, t, smem_few);
-        }
-        few_tile<INT_SCALE, 1, NS, W, D, false>(a, t, smem_few);
-    };
-    const int E = g.num_experts;
-    if ((int)blockIdx.y < E) {  // (twice in the code: what a loop keeps alive does not fit the registers, 4 % of 8 x 28672 x 4096)
-        const int m = max(g.row_offsets[blockIdx.y], 0), hi = min(g.row_offsets[blockIdx.y + 1], a.M);
-        if (m < hi) rows_of_expert(blockIdx.y, m, hi);
+    const int E = args.g.num_experts;
+    if ((int)blockIdx.y < E) {  // (apart from the loop below, whose live values cost these 4 % of 8 x 28672 x 4096)
+        const int m = max(args.g.row_offsets[blockIdx.y], 0), hi = min(args.g.row_offsets[blockIdx.y + 1], args.a.M);
+        if (m < hi) few_rows_of_expert<MT, NS, W, D, INT_SCALE>(args, blockIdx.y, m, hi, smem_few);
         return;
     }
     int e = 0, tile = 0;
-    for (int nth = blockIdx.y - E; further_tile(g, a.M, 16 * MT, nth, e, tile); nth += gridDim.y - E) {
-        const int m = __builtin_amdgcn_readfirstlane(max(g.row_offsets[e], 0) + tile * 16 * MT);
-        rows_of_expert(e, m, __builtin_amdgcn_readfirstlane(min(g.row_offsets[e + 1], a.M)));
+    for (int nth = blockIdx.y - E;;) {
+        const FewGroupedArgs p = arguments_again();
+        if (!further_tile(p.g, p.a.M, 16 * MT, nth, e, tile)) return;
+        const int m = __builtin_amdgcn_readfirstlane(max(p.g.row_offsets[e], 0) + tile * 16 * MT);
+        few_rows_of_expert<MT, NS, W, D, INT_SCALE>(p, e, m, __builtin_amdgcn_readfirstlane(min(p.g.row_offsets[e + 1], p.a.M)), smem_few);
         __syncthreads();  // the output tile has been read
+        nth += gridDim.y - p.g.num_experts;
     }
 }
 
@@ -558,7 +601,7 @@ hipError_t launch_grouped_instance(const FewArgs& a, const FewGroups& g, hipStre
     if (r != hipSuccess) return r;
     // beside the experts' first tiles: as many workgroups as the chip holds at a time, or as there can be further tiles
     const int wgs = ((a.N + 15) / 16 + NS - 1) / NS, further = std::min((a.M - 1) / (16 * MT), (2 * cu_count() + wgs - 1) / wgs);
-    hipLaunchKernelGGL(kernel, dim3(wgs, g.num_experts + further), dim3(W * kWave), lds, stream, with_launch_arguments(a, W), g);
+    hipLaunchKernelGGL(kernel, dim3(wgs, g.num_experts + further), dim3(W * kWave), lds, stream, FewGroupedArgs{with_launch_arguments(a, W), g});
     return hipGetLastError();
 }
 
