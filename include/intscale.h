@@ -181,7 +181,8 @@ int is_prepack_w4(const void* qweight, const int32_t* scale_i32, const float* sc
  *               (Which kernel: up to 64 rows the one for few rows whose waves split K, but the weight-streaming one for a
  *               single row with K >= 12288 or float scales and for narrow matrices with a long K, and the tiled one for
  *               33 <= M <= 64 when N * K >= 2^27; for M > 64 one of the two whose waves split K where a fitted time says
- *               that it is faster, roughly up to a few hundred rows, else the tiled one.  Ask is_gemm_prepacked_workspace_bytes / is_describe_prepacked, do not guess.)
+ *               that it is faster, roughly up to a few hundred rows, else the tiled one.  Ask
+ *               is_gemm_prepacked_workspace_bytes / is_describe_prepacked, do not guess.)
  *               M <= 64: 0 for most shapes; when it is not 0 the weight-streaming kernel splits the K dimension
  *               across workgroups and the first 64 KB of the workspace are arrival counters: they must be ZERO when a
  *               call starts and every call leaves them zero, so zero the workspace once after allocating it (the kernel
@@ -236,8 +237,9 @@ int is_gemm_w4a8_floatscale_prepacked_prepared(const float* a_scale, const void*
  * call uses a fixed scratch array inside the library (IS_NOALLOC_SCRATCH_BYTES of device memory per GPU, held until
  * the process ends) and allocates nothing, on the device or through any library.
  *   - Shapes whose is_gemm_prepacked_workspace_bytes(M,N,K,group) exceeds IS_NOALLOC_SCRATCH_BYTES return
- *     IS_ERR_WORKSPACE before anything is enqueued (covered: every M <= 64 shape, and larger ones up to about
- *     ceil(M/16) * 16 * K = 31 MiB; the tiled kernel splits its last round only as far as the rest of the scratch allows).
+ *     IS_ERR_WORKSPACE before anything is enqueued (covered: M <= 64 but for the widest matrices whose size asks for a K
+ *     split, 32 x 57344 x 28672 for one, and larger M up to about ceil(M/16) * 16 * K = 31 MiB; the tiled kernel splits
+ *     its last round only as far as the rest of the scratch allows).
  *   - All calls on one GPU share that GPU's array: calls that overlap in time on one GPU (two streams, two threads)
  *     race on it; serialise them or give the overlapping ones the workspace form.
  *   - The first call on a device resolves the array's address (hipGetSymbolAddress); make that call outside a graph

@@ -1,11 +1,14 @@
-// Fine-grained W4A8 GEMM on prepacked weights, 1 to 64 token rows (and, in row tiles, some calls of up to 512): the waves of a workgroup
-// split K.
+// Fine-grained W4A8 GEMM on prepacked weights, 1 to 64 token rows (and, in row tiles, calls of up to 512; and experts of few rows): the
+// waves of a workgroup split K.
 // Integer-scale form: Eq. (2) / Table 2 "Ours" of the Integer Scale paper; float-scale form: Eq. (1) / Table 2 "Atom".
-// (An fp16 row, and a quantised row with a long K, have a kernel of their own, gemm_decode_pk.hip.)
+// (An fp16 row, a float-scale row, a quantised row with a long K, and narrow matrices with a long K have a kernel of their own,
+// gemm_decode_pk.hip.)
 //
 // What bounds this regime: the weight stream from memory where the matrix is large and the rows are few, the kernel's start and end
-// where it is small, and with 64 rows the activations, which every compute unit pulls from its L2 in full (per K step of 64 rows 8 KB
-// next to 1 KB per weight tile; a unit takes 45 to 55 bytes a cycle).  So a workgroup takes a few 16-row weight tiles and all of K,
+// where it is small.  With 64 rows a compute unit mostly has one workgroup of four waves, one a SIMD, which issues 46 % of its time,
+// waits for loads 31 % and for an issue slot 23 %; the matrix pipe is busy a fifth of the time and the L2 delivers 19 bytes a
+// cycle and unit where it can 45 to 55 (64 x 12288 x 4096, 11.2 us; 9.4 without the loads of the activations, 8 KB a K step next to 1 KB
+// per weight tile).  So a workgroup takes a few 16-row weight tiles and all of K,
 // each of its 4 or 8 waves multiplies all of them over its own run of K steps, and the partial sums meet once, in LDS: no barrier in
 // the loop, no partial tile leaves the compute unit, nothing waits for the activations of a whole slab (a kernel that keeps
 // them in LDS for all its waves cuts K over workgroups where they do not fit, and the partial tiles then travel through memory).

@@ -15,11 +15,11 @@
 // need no preparation, cost 71 cycles per load and compute unit in 16 pieces of 64 bytes against about 30: 2048 x 28672 x 4096
 // 519 against 344 us, and no gain at 65 rows.)  Each register is asked for again as soon as its last use has been
 // issued, a K step ahead; two waves per SIMD cover the rest of the latency.  What bounds it, from counters: with int4 weights
-// (300 x 28672 x 4096, 58 us) a wave issues 43 % of its time, waits for an issue slot 36 % and for loads 21 %, so that the two
+// (300 x 28672 x 4096, 58 us) a wave issues 43 % of its time, waits for an issue slot 37 % and for loads 21 %, so that the two
 // waves of a SIMD leave it little room, and the L2 delivers 34 bytes per cycle and compute unit (14 KB of operands per 40 MFMAs
 // of a wave; tile loads alone sustain 40 to 55): large calls stay on the tiled kernel, which shares its operands through LDS
-// (takes_wavek says where the line lies).  With int8 weights (300 x 4096 x 14336, 42 us) it waits for loads: 49 % of a wave's
-// time, 34 % issuing, 29 bytes per cycle.  There the weight lines are requested by assembly, which the compiler does not
+// (takes_wavek says where the line lies).  With int8 weights (300 x 4096 x 14336, 42 us) it waits for loads: 48 % of a wave's
+// time, 34 % issuing, 28 bytes per cycle.  There the weight lines are requested by assembly, which the compiler does not
 // count, so that its waits for the activations (7 and 6 outstanding) hold up until the lines just requested have come too: they
 // are less than a K step ahead; and the copy of the scales every fourth step waits for everything.
 //
@@ -30,8 +30,8 @@
 //
 // Measured (GEMM on int8 codes, its preparation included, graph replay), the tiled kernel's time first: 65 x 4096 x 4096
 // 32.9 -> 12.6 us, 300 x 4096 x 4096 36.4 -> 19.5 us, 512 x 6144 x 4096 42.2 -> 28.5 us, 300 x 28672 x 4096 72.9 -> 58.2 us,
-// 128 x 4096 x 14336 46.2 -> 25.0 us, 300 x 4096 x 14336 32.4 us (41.9 in tiles of 64 rows); W8A8 300 x 4096 x 14336 126.4 -> 42.4 us,
-// 1024 x 4096 x 14336 129 -> 103 us; W4A8 1024 x 28672 x 4096 147 against 181 us (stays on the tiled kernel).
+// 128 x 4096 x 14336 46.2 -> 25.0 us, 300 x 4096 x 14336 32.4 us (41.9 in tiles of 64 rows); W8A8 300 x 4096 x 14336 122 -> 42 us,
+// 1024 x 4096 x 14336 128 -> 108 us; W4A8 1024 x 28672 x 4096 147 against 181 us (stays on the tiled kernel).
 #include <math.h>
 #include <stdio.h>
 
@@ -454,7 +454,7 @@ WavekPlan wavek_plan(int M, int N, int K, bool w8) {
     p.us = wavek_us(M, N, K, w8, p.ms, p.waves);
     // Long runs and more than a few tiles: by time, and tiles of 80 rows too.  What decides is how the tiles fill the units (300 x 4096: 320
     // tiles of 64 rows give a quarter of the 256 units two, 256 tiles of 80 rows give each one): W8A8 300 x 4096 x 14336 54.6 -> 42.4 us,
-    // 400 rows 87 -> 53, 1024 rows 128 -> 111; int4 weights 300 x 4096 x 14336 41.9 -> 32.4, 200 rows 49.9 (tiled kernel) -> 27.8.
+    // 400 rows 87 -> 58, 1024 rows 128 (tiled kernel) -> 108; int4 weights 300 x 4096 x 14336 41.9 -> 32.4, 200 rows 49.9 (tiled kernel) -> 27.8.
     if (K >= 2048 && p.tiles >= cu_count() / 8) {
         // The rule's tiles stay unless a twentieth is to be gained: near ties are decided by what the times leave out (173 x 15206 x 8064:
         // both 41.9 us by the times, 42.8 with 64 rows and 45.9 with 48).
@@ -511,7 +511,7 @@ bool wavek_is_faster(int M, int N, int K, bool w8) {
     if (tiles >= 2 * cus) return false;
     double there = tiled_us(tiles, steps), tie = 0.15;
     if (steps < 16) {
-        // Runs of a few steps a wave: rounds of tiles of which the last may be part filled, against starts that weigh more than steps (fits of
+        // Runs of a few steps a wave: rounds of tiles of which the last may be part filled, against starts that weigh more than steps (fits to
         // 1583 calls, 65 to 2100 rows, 256 to 40000 columns: 7 and 3 % off; with the coarser time for near ties the choice costs 0.1 % on
         // average and 11 % at most): 85 x 6496 x 256 8.4 us here and 15.7 there; 802 x 8064 x 512 24.3 and 20.7, 657 x 11968 x 512 27.7 and 24.5;
         // near ties: 300 x 27136 x 1664 38 and 41.
