@@ -239,7 +239,8 @@ def test_grouped_with_all_rows_at_one_expert_takes_its_share_of_the_chip(P, E, M
 # the kernel's tiles of 48 and 64 rows for more than 64 rows: one and several row tiles with remainders, ragged widths, uneven runs of
 # K steps, every instance
 ROWS = [(65, 5121, 2176, 128), (100, 6144, 4096, 256), (72, 12288, 4096, 128), (128, 5120, 2048, 128),
-        (300, 6144, 4096, 128), (130, 8200, 3072, 384), (512, 5128, 2048, 128), (200, 8192, 4096, 128), (256, 5200, 5120, 512), (400, 5120, 4096, 128)]
+        (300, 6144, 4096, 128), (130, 8200, 3072, 384), (512, 5128, 2048, 128), (200, 8192, 4096, 128), (256, 5200, 5120, 512), (400, 5120, 4096, 128),
+        (65, 1, 2048, 128), (130, 20, 2176, 128), (300, 72, 4096, 256), (97, 49, 28672, 1024), (512, 1041, 2304, 384), (66, 4096, 4096, 128)]
 
 
 @pytest.mark.parametrize("M,N,K,group", ROWS)
@@ -250,7 +251,7 @@ def test_more_than_64_rows(P, M, N, K, group, wide):
     check_call(P, M, N, K, group, wide, chan=not wide)
 
 
-@pytest.mark.parametrize("M,inter,K", [(65, 2576, 2048), (100, 5504, 2176), (200, 4096, 2048), (256, 2560, 4096)])
+@pytest.mark.parametrize("M,inter,K", [(65, 2576, 2048), (100, 5504, 2176), (200, 4096, 2048), (256, 2560, 4096), (67, 16, 2048), (130, 48, 2176)])
 def test_more_than_64_rows_fused_gate_up(P, M, inter, K):
     test_fused_gate_up(P, M, inter, K)
     # which kernel took the call: this one leaves the workspace alone, the others write the activations' blocks to it
