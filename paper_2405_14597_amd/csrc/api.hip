@@ -511,19 +511,7 @@ static int gemm_pk_common(const int8_t* xq, const void* x_fp16, const float* a_s
     a.pair = (pair && tiled) ? 1 : 0;  // (the fused epilogue is the tiled kernel's)
     const bool few = !tiled && x_fp16 == nullptr && takes_few(M, N, K, int_scale), rows = int_scale && x_fp16 == nullptr && !prepared && takes_rows(M, N, K, pair);
     if (few || rows) {
-        FewArgs f;
-        f.xq = xq;
-        f.a_scale = a_scale;
-        f.wpack = a.wpack;
-        f.spack = a.spack;
-        f.chan_scale = chan_scale;
-        f.out = a.out;
-        f.acc_out = acc_out;
-        f.M = M;
-        f.N = N;
-        f.K = K;
-        f.group = group;
-        f.alpha_log2 = a.alpha_log2;
+        const FewArgs f{xq, a_scale, a.wpack, a.spack, chan_scale, a.out, acc_out, M, N, K, group, a.alpha_log2};
         double us;
         return hip_status(few ? launch_gemm_few_pk(f, few_plan(M, N, K, pair && int_scale), int_scale, pair, static_cast<hipStream_t>(stream))
                               : launch_gemm_rows_pk(f, rows_plan(M, N, K, pair, &us), pair, static_cast<hipStream_t>(stream)));
@@ -724,19 +712,7 @@ static int gemm_grouped_pk_common(const int8_t* xq, const float* a_scale, const 
     a.alpha_log2 = int_scale ? alpha_log2 : 0;
     const FewPlan plan = kernel_route() < 2 ? few_grouped_plan(E, M, N, K) : FewPlan{};  // (routes 2 and 3: the tiled kernel)
     if (plan.ns > 0) {
-        FewArgs f;
-        f.xq = xq;
-        f.a_scale = a_scale;
-        f.wpack = a.wpack;
-        f.spack = a.spack;
-        f.chan_scale = chan_scale;
-        f.out = a.out;
-        f.acc_out = acc_out;
-        f.M = M;
-        f.N = N;
-        f.K = K;
-        f.group = group;
-        f.alpha_log2 = a.alpha_log2;
+        const FewArgs f{xq, a_scale, a.wpack, a.spack, chan_scale, a.out, acc_out, M, N, K, group, a.alpha_log2};
         const FewGroups fg{row_offsets, E, pk_weight_bytes(N, K), pk_scale_bytes(N, K, group)};
         return hip_status(launch_gemm_few_grouped_pk(f, fg, plan, int_scale, static_cast<hipStream_t>(stream)));
     }
@@ -914,19 +890,7 @@ static int gemm_w8_common(const int8_t* xq, const float* a_scale, const int8_t* 
     // up to 64 token rows the layer is a weight stream: integer scales and K from 1024 on to the kernel whose waves split K, the rest to the
     // bandwidth-bound general kernel; beyond, the tiled kernel
     if (int_scale && kernel_route() == 0 && few_w8_tiles(M, N, K) > 0) {
-        FewArgs f;
-        f.xq = xq;
-        f.a_scale = a_scale;
-        f.wpack = a.qweight;
-        f.spack = static_cast<const uint8_t*>(scale);
-        f.chan_scale = chan_scale;
-        f.out = a.out;
-        f.acc_out = acc_out;
-        f.M = M;
-        f.N = N;
-        f.K = K;
-        f.group = group;
-        f.alpha_log2 = alpha_log2;
+        const FewArgs f{xq, a_scale, a.qweight, static_cast<const uint8_t*>(scale), chan_scale, a.out, acc_out, M, N, K, group, alpha_log2};
         return hip_status(launch_gemm_few_w8(f, static_cast<hipStream_t>(stream)));
     }
     if (M <= 64 && !general_forced_off())

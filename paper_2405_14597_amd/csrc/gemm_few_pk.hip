@@ -138,17 +138,10 @@ __device__ __forceinline__ void few_tile(const FewArgs& a, const FewTile& t, uns
         x_at = s + 1 == s_end ? s_begin : s + 1;
         const unsigned base = lds_stage + slot * MS * 2048;
         if constexpr (MS == 1) {
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
-                         "buffer_load_dwordx4 %1, %3, %4 offen lds\n\t"
-                         "buffer_load_dwordx4 %2, %3, %4 offen offset:1024 lds" ::"s"(base), "v"(x_off[0]), "v"(x_off[1]), "s"(d), "s"(s * 128)
-                         : "memory");
+            load_to_lds_rows_2x1k(d, base, x_off[0], x_off[1], s * 128);
         } else {
             load_to_lds_rows_4x1k(d, base, x_off[0], x_off[1], x_off[2], x_off[3], s * 128);
-            if constexpr (MS == 3)
-                asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
-                             "buffer_load_dwordx4 %1, %3, %4 offen lds\n\t"
-                             "buffer_load_dwordx4 %2, %3, %4 offen offset:1024 lds" ::"s"(base + 4096), "v"(x_off[4]), "v"(x_off[5]), "s"(d), "s"(s * 128)
-                             : "memory");
+            if constexpr (MS == 3) load_to_lds_rows_2x1k(d, base + 4096, x_off[4], x_off[5], s * 128);
             if constexpr (MS == 4) load_to_lds_rows_4x1k(d, base + 4096, x_off[4], x_off[5], x_off[6], x_off[7], s * 128);
         }
     };
@@ -449,19 +442,13 @@ hipError_t launch_instance(const FewArgs& a, hipStream_t stream) {
 }
 
 // Moderate numbers of rows, integer scales (exact in any order; float sums have to be those of the calls on prepared activations, bit for
-// bit): the workgroups of several row tiles.  XCD x gets one contiguous range of tile numbers, and a range walks the
-// output in blocks of eight tile rows, column by column (the row tiles that share weights meet in that XCD's L2).
+// bit): the workgroups of several row tiles.
 template <int MS, int NS, int W, int D, bool SILU>
 __global__ __launch_bounds__(W* kWave) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_rows_pk_kernel(FewArgs a) {
     extern __shared__ __align__(16) unsigned char smem_few[];
     const int tiles_n = (a.N + NS * 16 - 1) / (NS * 16), tiles_m = (a.M + MS * 16 - 1) / (MS * 16);
-    const int total = tiles_n * tiles_m, q8 = total / 8, r8 = total - q8 * 8;
-    const int xcd = blockIdx.x % 8;
-    const int lid = xcd * q8 + min(xcd, r8) + blockIdx.x / 8;
-    const int gsz = 8 * tiles_n, grp = lid / gsz, in_grp = lid - grp * gsz;
-    const int gm = min(8, tiles_m - grp * 8);
-    const int tile_n = in_grp / gm, tile_m = grp * 8 + (in_grp - tile_n * gm);
-    const int m0 = tile_m * MS * 16;
+    const TileAt tile = tile_of_block(blockIdx.x, tiles_m, tiles_n);
+    const int m0 = tile.m * MS * 16;
     FewTile t;
     t.x = a.xq + (size_t)m0 * a.K;
     t.a_scale = a.a_scale + m0;
@@ -471,8 +458,8 @@ __global__ __launch_bounds__(W* kWave) __attribute__((amdgpu_waves_per_eu(2, 2))
     t.out = a.out + (size_t)m0 * (SILU ? a.N >> 1 : a.N);
     t.acc_out = a.acc_out ? a.acc_out + (size_t)m0 * a.N : nullptr;
     t.m_rows = min(a.M - m0, MS * 16);
-    t.t0 = tile_n * NS;
-    t.phase = tile_n / 2;
+    t.t0 = tile.n * NS;
+    t.phase = tile.n / 2;
     few_tile<true, MS, NS, W, D, SILU>(a, t, smem_few);
 }
 

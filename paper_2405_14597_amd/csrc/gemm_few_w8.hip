@@ -35,11 +35,7 @@ template <int T>
 __device__ __forceinline__ void tiles_to_lds(v4i d, unsigned base, const int (&off)[2 * T], int soffset) {
     if constexpr (T >= 2) load_to_lds_rows_4x1k(d, base, off[0], off[1], off[2], off[3], soffset);
     if constexpr (T == 4) load_to_lds_rows_4x1k(d, base + 4096, off[4], off[5], off[6], off[7], soffset);
-    if constexpr (T % 2 == 1)
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
-                     "buffer_load_dwordx4 %1, %3, %4 offen lds\n\t"
-                     "buffer_load_dwordx4 %2, %3, %4 offen offset:1024 lds" ::"s"(base + (T - 1) * 2048), "v"(off[2 * T - 2]), "v"(off[2 * T - 1]), "s"(d), "s"(soffset)
-                     : "memory");
+    if constexpr (T % 2 == 1) load_to_lds_rows_2x1k(d, base + (T - 1) * 2048, off[2 * T - 2], off[2 * T - 1], soffset);
 }
 
 // (two waves per SIMD: MFMA results in ordinary registers, where the scale step reads them)

@@ -50,8 +50,6 @@ typedef float v4f_t __attribute__((ext_vector_type(4)));
 
 constexpr int kNS = 4;                // 16-row weight sub-tiles of a tile: 64 output columns
 constexpr int kTN = kNS * 16;
-constexpr int kXcdCount = 8;          // workgroup i is dispatched to XCD i % 8
-constexpr int kGroupRows = 8;         // tile rows of the block of tiles an XCD works on at a time
 constexpr int kPitch = kTN + 8;       // halves per row of the output tile in LDS
 
 constexpr int kStage8 = kTN * 128;    // int8 weights of one K step
@@ -76,18 +74,9 @@ __device__ __forceinline__ void wavek_tile(const WavekArgs& a, unsigned char* sm
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int li = lane & 15, kb = lane >> 4;
-    // ---- which tile: XCD x gets one contiguous range of tile numbers, and a range walks the output in blocks of kGroupRows
-    // tile rows, column by column (the row tiles that share weights meet in that XCD's L2)
     const int tiles_n = (a.N + kTN - 1) / kTN, tiles_m = (a.M + MS * 16 - 1) / (MS * 16);
-    const int total = tiles_n * tiles_m;
-    const int q8 = total / kXcdCount, r8 = total - q8 * kXcdCount;
-    const int xcd = blockIdx.x % kXcdCount;
-    const int lid = xcd * q8 + min(xcd, r8) + blockIdx.x / kXcdCount;
-    const int gsz = kGroupRows * tiles_n;
-    const int grp = lid / gsz, in_grp = lid - grp * gsz;
-    const int gm = min(kGroupRows, tiles_m - grp * kGroupRows);
-    const int tile_n = in_grp / gm, tile_m = grp * kGroupRows + (in_grp - tile_n * gm);
-    const int m0 = tile_m * MS * 16, n0 = tile_n * kTN;
+    const TileAt tile = tile_of_block(blockIdx.x, tiles_m, tiles_n);
+    const int m0 = tile.m * MS * 16, n0 = tile.n * kTN;
     const int m_rows = min(MS * 16, a.M - m0), n_rows = min(kTN, a.N - n0);
 
     const int steps = a.K >> 7, NG = a.K / a.group, spg = a.group >> 7;

@@ -57,6 +57,14 @@ __device__ __forceinline__ void load_to_lds_rows_4x1k(v4i desc, unsigned lds_bas
                  : "s"(lds_base), "v"(v0), "v"(v1), "v"(v2), "v"(v3), "s"(desc), "s"(soffset)
                  : "memory");
 }
+__device__ __forceinline__ void load_to_lds_rows_2x1k(v4i desc, unsigned lds_base, int v0, int v1, int soffset) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+                 "buffer_load_dwordx4 %1, %3, %4 offen lds\n\t"
+                 "buffer_load_dwordx4 %2, %3, %4 offen offset:1024 lds"
+                 :
+                 : "s"(lds_base), "v"(v0), "v"(v1), "s"(desc), "s"(soffset)
+                 : "memory");
+}
 __device__ __forceinline__ void load_to_lds_2x1k(v4i d0, unsigned lds_base, unsigned lds_offset, int voffset, int soffset) {
     asm volatile("s_add_u32 m0, %0, %1\n\ts_nop 0\n\t"
                  "buffer_load_dwordx4 %2, %3, %4 offen lds\n\t"
@@ -109,6 +117,22 @@ __device__ __forceinline__ int lanes_up_to(int v, int lane) {
         if (lane >= d) v += below;
     }
     return v;
+}
+
+// The output tile of workgroup `block`, tiles_m x tiles_n of them: XCD x gets one contiguous range of tile numbers, and a range walks the
+// output in blocks of eight tile rows, column by column (the row tiles that share weights meet in that XCD's L2).
+struct TileAt {
+    int m, n;
+};
+__device__ __forceinline__ TileAt tile_of_block(unsigned block, int tiles_m, int tiles_n) {
+    constexpr int kXcds = 8, kRows = 8;
+    const int total = tiles_n * tiles_m, q = total / kXcds, r = total - q * kXcds;
+    const int xcd = block % kXcds;
+    const int lid = xcd * q + min(xcd, r) + block / kXcds;
+    const int gsz = kRows * tiles_n, grp = lid / gsz, in_grp = lid - grp * gsz;
+    const int gm = min(kRows, tiles_m - grp * kRows);
+    const int n = in_grp / gm;
+    return TileAt{grp * kRows + (in_grp - n * gm), n};
 }
 
 }  // namespace
