@@ -279,3 +279,53 @@ def test_int8_weights(P, M, N, K, group, wide):
     want = acc.double() * sa.double()[:, None] * (1.0 if wide else c.double()[None, :]) / 1024.0
     # two fp32 products and one rounding to fp16: 2^-11 of the value and a little more, and half a step of the smallest numbers
     assert bool(((out.double() - want).abs() <= 5e-4 * want.abs() + 2.0 ** -25)[want.abs() < 65000.0].all())
+
+
+def test_captured_calls(P):
+    """One graph of the calls whose kernels differ: few rows, K cut over workgroups (its counters; the call on the library's own scratch as well),
+    row tiles without a preparation, a mixture whose offsets change, W8A8.  Replayed with new inputs in the same buffers, the program's own work
+    in between, against the ordinary calls each time."""
+    shapes = [(16, 1000, 1024), (1, 64, 28672), (16, 64, 65536), (130, 328, 2176)]
+    data = [case(M, N, K, seed=11) for M, N, K in shapes]
+    packs = [P.is_prepack_w4(d[2], d[3], G) for d in data]
+    E, MG, NG, KG = 8, 72, 300, 1024
+    sets = [case(MG, NG, KG, seed=20 + e) for e in range(E)]
+    experts = P.is_prepack_w4_experts(torch.stack([d[2] for d in sets]), torch.stack([d[3] for d in sets]), G)
+    assert P.is_describe_grouped_prepacked(E, MG, NG, KG, G)[-1].startswith("gemm_few_grouped_pk_kernel<")
+    offsets = torch.tensor([0] + [MG] * E, dtype=torch.int32, device="cuda:0")
+    q8 = torch.randint(-128, 128, (300, 2176), dtype=torch.int8, device="cuda:0")
+    x8, s8 = torch.zeros((17, 2176), dtype=torch.int8, device="cuda:0"), torch.randint(0, 1025, (300, 17), dtype=torch.int32, device="cuda:0")
+    sa8 = torch.rand((17,), device="cuda:0")
+    sizes = [P.is_gemm_prepacked_workspace_bytes(*s, G) for s in shapes] + [P.is_gemm_grouped_prepacked_workspace_bytes(E, MG, NG, KG, G),
+                                                                              P.is_gemm_w8a8_workspace_bytes(17, 300, 2176, G)]
+    outs = [torch.empty((M, N), dtype=torch.float16, device="cuda:0") for M, N, _ in shapes + [(MG, NG, 0), (17, 300, 0), (16, 64, 0)]]
+
+    def calls(outs, ws):
+        for d, pk, out, w in zip(data, packs, outs, ws):
+            P.is_gemm_w4a8_intscale_prepacked(d[0], d[4], pk, d[5], 10, out=out, workspace=w)
+        P.is_gemm_w4a8_intscale_grouped_prepacked(sets[0][0], sets[0][4], experts, None, offsets, 10, out=outs[4], workspace=ws[4])
+        P.is_gemm_w8a8_intscale(x8, sa8, q8, s8, None, G, 10, out=outs[5], workspace=ws[5])
+        P.is_gemm_w4a8_intscale_prepacked_noalloc(data[2][0], data[2][4], packs[2], data[2][5], 10, outs[6])
+
+    ws = [torch.zeros((max(n, 16),), dtype=torch.uint8, device="cuda:0") for n in sizes]
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        calls(outs, ws)
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        calls(outs, ws)
+    for i in range(4):
+        for x in [d[0] for d in data] + [sets[0][0], x8]:
+            x.copy_(torch.randint(-128, 128, tuple(x.shape), dtype=torch.int8, device="cuda:0"))
+        ends = torch.randint(0, MG + 1, (E - 1,), device="cuda:0").sort().values.to(torch.int32)
+        offsets[1:E].copy_(ends if i else torch.zeros_like(ends))
+        graph.replay()
+        torch.cuda.synchronize()
+        want = [torch.empty_like(o) for o in outs]
+        calls(want, [torch.zeros_like(w) for w in ws])
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(outs, want)), f"replay {i}"
+    assert torch.equal(outs[2], outs[6])
